@@ -283,8 +283,7 @@ static mlmc_status enqueue_segment(mlmc_ctx* ctx, const mlmc_model& m, const mlm
         auto a = make_args<float>(m, p, l, M, N, seed, offset, stream, coupled, acc, d_pf, d_pc);
         a.spread_mask = mask;
         set_counter_words(a, dim);
-        // estimation may read the network from its table; training evaluates it
-        const bool tab = cv_tabulated(cv) && stream != kStreamTrainNormal;
+        const bool tab = cv_tabulated(cv);
         hipError_t e;
         if (l == 0) {
             // one step from (0, S0): phi is the single value phi(0, S0)

@@ -1,5 +1,5 @@
-// Learned control variate: parameters, the sampler with the control variate
-// (forward), the training backward pass, and Adam -- all device kernels.
+// Learned control variate: parameters, the samplers with the control variate
+// and the table (training: cv_train.hip).
 //
 // Level estimators with the control variate (eqs. (eq:mlmc:Yzero),
 // (eq:Yldef) with each payoff replaced by P - sum_n phi(t_n, X_n) dW1_n on
@@ -11,48 +11,12 @@
 
 #include <cmath>
 #include <cstring>
-#include <vector>
 
-#include "context.hpp"
-#include "cv.hpp"
+#include "cv_state.hpp"
 #include "cv_tab.hpp"
 #include "sampler_impl.hpp"
-#include "trace.hpp"
 
 using namespace mlmc::cvnet;
-
-struct mlmc_cv {
-    mlmc_ctx* ctx = nullptr;
-    int D = 2;                    // network inputs
-    int np = 0;                   // parameter count
-    float* d_params = nullptr;    // fp32 master
-    float* d_m1 = nullptr;        // Adam moments
-    float* d_m2 = nullptr;
-    bf16x8* d_afwd = nullptr;     // bf16 W2 operands (forward), 8 x 64 entries
-    bf16x8* d_abwd = nullptr;     // bf16 W2 operands (backward, permuted)
-    float* d_phi0 = nullptr;      // [0] phi(0, S0), [1] its tabulated value: see cv_ensure_phi0
-    int adam_t = 0;
-    uint64_t version = 0;         // bumped by every parameter change
-    uint64_t phi0_version[2] = {~0ull, ~0ull};
-    mlmc_model phi0_model[2]{};
-    hipStream_t phi0_stream[2] = {nullptr, nullptr};
-    // tabulated network (estimation launches only; training evaluates it)
-    int tabulated = 0;
-    float* d_table = nullptr;
-    size_t table_cap = 0;         // floats allocated
-    uint64_t table_version = ~0ull;
-    mlmc_model table_model{};
-    hipStream_t table_stream = nullptr;
-    // training scratch
-    float* d_gpart = nullptr;     // per-block gradient partials
-    int gpart_blocks = 0;
-    double* d_y = nullptr;        // per-sample Y of a training batch (all levels)
-    float* d_w = nullptr;         // per-sample loss weights
-    double* d_loss = nullptr;     // loss and per-level variances
-    uint64_t batch_cap = 0;
-    float* d_fpart = nullptr;     // forward runs' partial sums of one level
-    uint64_t fpart_cap = 0;       // floats allocated
-};
 
 namespace mlmc {
 
@@ -77,27 +41,6 @@ __global__ void cv_init_kernel(float* params, int D, uint64_t seed)
     params[i] = a * (2.0f * (float)u01d(word) - 1.0f);
 }
 
-// Row of the permuted backward operand: physical row rho of e1 = W2^T d2
-// holds logical unit unit_of_row(rho), chosen so that e1's accumulator
-// registers line up with the forward pass's layer-1 slots (unit_b).
-__host__ __device__ inline int unit_of_row(int rho)
-{
-    const int kt = rho / 32, rem = rho % 32;
-    const int h = (rem % 8) / 4;
-    const int r = 4 * (rem / 8) + rem % 4;
-    return 32 * kt + 16 * (r / 8) + 8 * h + r % 8;
-}
-
-// Contraction position kappa of e1's B operand (d2 straight from the layer-2
-// accumulators) holds logical output unit j_of_pos(kappa).
-__host__ __device__ inline int j_of_pos(int kappa)
-{
-    const int kb = kappa / 16, rem = kappa % 16;
-    const int h = rem / 8, i = rem % 8;
-    const int t = 8 * kb + i;            // register order within the half
-    return row_d(h, t / 16, t % 16);
-}
-
 // bf16 operand arrays from the fp32 W2 (round to nearest even).
 __global__ void cv_prepare_kernel(const float* params, int D, bf16x8* afwd, bf16x8* abwd)
 {
@@ -111,21 +54,12 @@ __global__ void cv_prepare_kernel(const float* params, int D, bf16x8* afwd, bf16
         for (int i = 0; i < 8; ++i) {
             const int j = 32 * tile + lane % 32, k = 16 * kb + 8 * hi + i;
             f[i] = (__bf16)W2[j * H + k];
-            // backward: row rho = 32 tile + lane % 32, position kappa = k
-            const int rho = 32 * tile + lane % 32;
-            b[i] = (__bf16)W2[j_of_pos(k) * H + unit_of_row(rho)];
+            b[i] = (__bf16)W2[k * H + j];    // the transposed product's operand
         }
         afwd[idx] = f;
         abwd[idx] = b;
     }
 }
-
-struct CvKernelArgs {
-    const float* params;
-    const bf16x8* afwd;
-    NetConsts nc;
-    int D;
-};
 
 // Grid of the tabulated network for a model (host): 256 time rows x 32 stock
 // values for GBM; 16 rows x 16 stock values x 32 variances for Heston (32 KiB
@@ -318,302 +252,8 @@ __global__ __launch_bounds__(256) void cv_tab_short_kernel(LevelArgs<float> a, c
     block_reduce_add(sums, nonfinite, a.acc + (blockIdx.x & a.spread_mask));
 }
 
-// Training forward of a deep level in runs (as the backward pass cuts it):
-// block (64 samples, run r) advances its paths from the start, evaluates
-// the network at the points of its run only, and writes its fp32 sums of
-// phi dW1 on the fine and the coarse path to part[2r][i], part[2r+1][i];
-// the last run also writes the two payoffs to part[2 segs], part[2 segs + 1].
-// cv_train_combine_kernel then forms Y (payoff minus the runs' sums, added
-// in run order), the per-sample dumps and the level sums.
-template <int MODEL, int PAYOFF, int M>
-__global__ __launch_bounds__(64) void cv_train_fwd_kernel(LevelArgs<float> a, CvKernelArgs c, uint32_t segs,
-                                                          float* part)
-{
-    constexpr int D = (MODEL == kGBM) ? 2 : 3;
-    __shared__ NetShared sh;
-    __shared__ bf16x8 s_afwd[8 * 64];
-    load_shared<D>(sh, c.params, c.nc);
-    for (int i = threadIdx.x; i < 8 * 64; i += blockDim.x) s_afwd[i] = c.afwd[i];
-    __syncthreads();
-    const StepParams<float>& P = a.P;
-    const uint64_t nchunks = (a.N + 63) / 64;
-    const uint32_t per_seg = a.ngroups / segs;      // segs divides ngroups (host)
-    for (uint64_t b = blockIdx.x; b < nchunks * segs; b += gridDim.x) {
-        const uint64_t ch = b / segs;
-        const uint32_t r = (uint32_t)(b % segs), g0 = r * per_seg, g1 = g0 + per_seg;
-        const uint64_t idx = ch * 64 + threadIdx.x;
-        const uint64_t s = a.offset + idx;
-        PathPair<float> q;
-        init_pair<float, MODEL, PAYOFF>(q, P);
-        float phic = 0.0f;
-        for (uint32_t g = 0; g < g1; ++g) {
-            float dw1[4], dwp[4], e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            fetch_group<MODEL, PAYOFF>(a, s, g, dw1, dwp, e);
-            const bool eval = g >= g0;                      // block-uniform
-#pragma unroll 1
-            for (int k = 0; k < 4; ++k) {
-                const int n = 4 * (int)g + k;
-                if (n >= a.nf) break;                       // wave-uniform
-                const float d1 = k == 0 ? dw1[0] : k == 1 ? dw1[1] : k == 2 ? dw1[2] : dw1[3];
-                const float dp = k == 0 ? dwp[0] : k == 1 ? dwp[1] : k == 2 ? dwp[2] : dwp[3];
-                const float ek = k == 0 ? e[0] : k == 1 ? e[1] : k == 2 ? e[2] : e[3];
-                if (eval) {
-                    const float x0 = (float)n * P.h * sh.inv_T;
-                    const float phif = phi_eval<D>(sh, s_afwd, x0, q.S, q.v);
-                    q.cvf = __builtin_fmaf(phif, d1, q.cvf);
-                    if ((n & (M - 1)) == 0) phic = phi_eval<D>(sh, s_afwd, x0, q.Sc, q.vc);
-                }
-                fine_step<float, MODEL, PAYOFF>(q, P, d1, dp, ek, n & (M - 1), true);
-                if (((n + 1) & (M - 1)) == 0) {
-                    if (eval) q.cvc = __builtin_fmaf(phic, q.dw1c, q.cvc);
-                    coarse_step<float, MODEL, PAYOFF>(q, P);
-                }
-            }
-        }
-        if (idx < a.N) {
-            part[(uint64_t)(2 * r) * a.N + idx] = q.cvf;
-            part[(uint64_t)(2 * r + 1) * a.N + idx] = q.cvc;
-            if (r + 1 == segs) {
-                part[(uint64_t)(2 * segs) * a.N + idx] =
-                    payoff_value<float, PAYOFF>(P, q.S, q.asum, q.acomp, q.mn, P.h);
-                part[(uint64_t)(2 * segs + 1) * a.N + idx] =
-                    payoff_value<float, PAYOFF>(P, q.Sc, q.csum, q.ccomp, q.mnc, P.H);
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void cv_train_combine_kernel(LevelArgs<float> a, uint32_t segs,
-                                                               const float* part)
-{
-    double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
-    unsigned nonfinite = 0;
-    for (uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < a.N;
-         idx += (uint64_t)gridDim.x * blockDim.x) {
-        float cf = 0.0f, cc = 0.0f;
-        for (uint32_t r = 0; r < segs; ++r) {
-            cf += part[(uint64_t)(2 * r) * a.N + idx];
-            cc += part[(uint64_t)(2 * r + 1) * a.N + idx];
-        }
-        const float pf = part[(uint64_t)(2 * segs) * a.N + idx] - cf;
-        const float pc = part[(uint64_t)(2 * segs + 1) * a.N + idx] - cc;
-        accumulate(a, idx, pf, pc, sums, nonfinite);
-    }
-    block_reduce_add(sums, nonfinite, a.acc);
-}
-
-// ------------------------------------------------------------ training
-// Loss over levels 0..lmax (the MLMC cost functional; total cost scales as
-// (sum_l sqrt(V_l C_l))^2):  loss = sum_l sqrt(C_l Var_batch(Y_l)),
-// dLoss/dY_i = sqrt(C_l / V_l) (Y_i - mean_l) / (B - 1).
-// One block per level: weights of every sample, the level's variance, and
-// its loss term (added into loss[0]).
-__global__ void cv_weights_kernel(const LevelAcc* rec, const double* ydump, uint64_t B, int M,
-                                  float* w, double* loss)
-{
-    const int l = blockIdx.x;
-    const double n = (double)B;
-    const double mean = rec[l].sum[0] / n;
-    double var = (rec[l].sum[1] - n * mean * mean) / (n - 1.0);
-    if (var < 0) var = 0;
-    double C = 1.0;
-    if (l > 0) {
-        double a = 1.0;
-        for (int i = 0; i < l - 1; ++i) a *= M;
-        C = a * M + a;
-    }
-    const double scale = var > 0 ? sqrt(C / var) / (n - 1.0) : 0.0;
-    const double* pf = ydump + 2 * (uint64_t)l * B;
-    const double* pc = pf + B;
-    for (uint64_t i = threadIdx.x; i < B; i += blockDim.x)
-        w[(uint64_t)l * B + i] = (float)(scale * ((pf[i] - pc[i]) - mean));
-    if (threadIdx.x == 0) {
-        loss[1 + l] = var;
-        atomicAdd(&loss[0], sqrt(C * var));
-    }
-}
-
-// Backward pass over the samples of one level (one wave per block): the
-// same paths as the forward pass, regenerated from their counters; every
-// evaluation point contributes with g = -w dW1 (fine) or +w dW1c (coarse).
-// A path's generator groups are cut into `segs` runs of whole groups, one
-// block per (64 samples, run): a block advances its paths from the start
-// (a plain step costs ~20 instructions, an evaluation point with its
-// backward pass thousands) and evaluates only the points of its run, so a
-// deep level's few samples still fill the device.
-template <int MODEL, int PAYOFF, int M>
-__global__ __launch_bounds__(64) void cv_backward_kernel(LevelArgs<float> a, CvKernelArgs c,
-                                                          const bf16x8* abwd, const float* w,
-                                                          float* gpart, uint32_t segs)
-{
-    constexpr int D = (MODEL == kGBM) ? 2 : 3;
-    __shared__ NetShared sh;
-    __shared__ bf16x8 afw[8 * 64], abw[8 * 64];
-    __shared__ Stage st;
-    load_shared<D>(sh, c.params, c.nc);
-    for (int i = threadIdx.x; i < 8 * 64; i += blockDim.x) {
-        afw[i] = c.afwd[i];
-        abw[i] = abwd[i];
-    }
-    __syncthreads();
-    GradAcc acc;
-    zero_acc(acc);
-    const StepParams<float>& P = a.P;
-    const bool coupled = a.l > 0;
-    const int lane = threadIdx.x & 63;
-    const uint64_t nchunks = (a.N + 63) / 64;
-    const uint32_t per_seg = a.ngroups / segs;      // segs divides ngroups (host)
-    for (uint64_t b = blockIdx.x; b < nchunks * segs; b += gridDim.x) {
-        const uint64_t ch = b / segs;
-        const uint32_t g0 = (uint32_t)(b % segs) * per_seg, g1 = g0 + per_seg;
-        const uint64_t idx = ch * 64 + lane;
-        const uint64_t s = a.offset + idx;
-        const float wp = idx < a.N ? w[idx] : 0.0f;
-        PathPair<float> q;
-        init_pair<float, MODEL, PAYOFF>(q, P);
-        for (uint32_t g = 0; g < g1; ++g) {
-            float dw1[4], dwp[4], e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            fetch_group<MODEL, PAYOFF>(a, s, g, dw1, dwp, e);
-            const bool eval = g >= g0;                      // block-uniform
-#pragma unroll 1
-            for (int k = 0; k < 4; ++k) {
-                const int n = 4 * (int)g + k;
-                if (n >= a.nf) break;
-                const float d1 = k == 0 ? dw1[0] : k == 1 ? dw1[1] : k == 2 ? dw1[2] : dw1[3];
-                const float dp = k == 0 ? dwp[0] : k == 1 ? dwp[1] : k == 2 ? dwp[2] : dwp[3];
-                const float ek = k == 0 ? e[0] : k == 1 ? e[1] : k == 2 ? e[2] : e[3];
-                if (eval) {
-                    const float x0 = (float)n * P.h * sh.inv_T;
-                    eval_backward<D>(sh, afw, abw, st, x0, q.S, q.v, -wp * d1, acc);
-                    if (coupled && (n & (M - 1)) == 0) {
-                        // the coarse step starting here sums the next M fine increments
-                        const float dwc = (M == 4) ? dw1[0] + dw1[1] + dw1[2] + dw1[3]
-                                                   : (k == 0 ? dw1[0] + dw1[1] : dw1[2] + dw1[3]);
-                        eval_backward<D>(sh, afw, abw, st, x0, q.Sc, q.vc, wp * dwc, acc);
-                    }
-                }
-                fine_step<float, MODEL, PAYOFF>(q, P, d1, dp, ek, n & (M - 1), coupled);
-                if (coupled && ((n + 1) & (M - 1)) == 0) coarse_step<float, MODEL, PAYOFF>(q, P);
-            }
-        }
-    }
-    // per-block partial gradient (row blockIdx.x of gpart)
-    const int np = nparams(D);
-    float* row = gpart + (uint64_t)blockIdx.x * np;
-    const int h = lane >> 5;
-    float b3 = acc.gb3;
-    for (int m = 1; m < 64; m <<= 1) b3 += __shfl_xor(b3, m);
-    if (lane == 0) row[off_b3(D)] = b3;
-#pragma unroll
-    for (int t = 0; t < 32; ++t) {
-        float v3 = acc.gw3[t], v2 = acc.gb2[t], v1 = acc.gb1[t];
-        float u0 = acc.gW1[0][t], u1 = acc.gW1[1][t], u2 = acc.gW1[2][t];
-        for (int m = 1; m < 32; m <<= 1) {     // sum over the lane's half
-            v3 += __shfl_xor(v3, m);
-            v2 += __shfl_xor(v2, m);
-            v1 += __shfl_xor(v1, m);
-            u0 += __shfl_xor(u0, m);
-            u1 += __shfl_xor(u1, m);
-            if (D == 3) u2 += __shfl_xor(u2, m);
-        }
-        if ((lane & 31) == 0) {
-            const int j = row_d(h, t / 16, t % 16);
-            row[off_w3(D) + j] = v3;
-            row[off_b2(D) + j] = v2 * sh.w3[j];
-            const int u = unit_b(h, t);
-            row[off_b1(D) + u] = v1;
-            row[u * D + 0] = u0;
-            row[u * D + 1] = u1;
-            if (D == 3) row[u * D + 2] = u2;
-        }
-    }
-#pragma unroll
-    for (int ut = 0; ut < 2; ++ut)
-#pragma unroll
-        for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int u = row_d(h, ut, r);             // rows of G are units
-                const int j = 32 * jt + (lane & 31);       // columns are layer-2 units
-                row[off_W2(D) + j * H + u] = acc.G[ut][jt][r];
-            }
-}
-
-// grad[i] = sum over the partial rows (fixed order): rows [r0, r1) of the
-// partials into one row, with the loads of a thread issued ahead of its adds.
-__global__ void cv_reduce_kernel(const float* gpart, int rows, int np, float* grad)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np) return;
-    float s = 0.0f;
-#pragma unroll 8
-    for (int r = 0; r < rows; ++r) s += gpart[(uint64_t)r * np + i];
-    grad[i] = s;
-}
-
-// First pass of the reduction: chunk blockIdx.y of kReduceRows rows into row
-// blockIdx.y of `partial` (the second pass, cv_reduce_kernel, adds those rows
-// in order; the whole sum keeps one fixed order).
-constexpr int kReduceRows = 32;
-__global__ void cv_reduce_rows_kernel(const float* gpart, int rows, int np, float* partial)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np) return;
-    const int r0 = blockIdx.y * kReduceRows;
-    const int r1 = r0 + kReduceRows < rows ? r0 + kReduceRows : rows;
-    float s = 0.0f;
-#pragma unroll 8
-    for (int r = r0; r < r1; ++r) s += gpart[(uint64_t)r * np + i];
-    partial[(uint64_t)blockIdx.y * np + i] = s;
-}
-
-// Adam (Kingma and Ba 2015) on the fp32 master parameters.
-__global__ void cv_adam_kernel(float* params, float* m1, float* m2, const float* grad, int np,
-                               float lr, float b1, float b2, float eps, float c1, float c2)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np) return;
-    const float g = grad[i];
-    const float a = b1 * m1[i] + (1.0f - b1) * g;
-    const float v = b2 * m2[i] + (1.0f - b2) * g * g;
-    m1[i] = a;
-    m2[i] = v;
-    params[i] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
-}
-
 // ----------------------------------------------------------- dispatch
 using CvFn = void (*)(LevelArgs<float>, CvKernelArgs);
-using CvBwdFn = void (*)(LevelArgs<float>, CvKernelArgs, const bf16x8*, const float*, float*, uint32_t);
-using CvTrainFwdFn = void (*)(LevelArgs<float>, CvKernelArgs, uint32_t, float*);
-
-template <int MODEL>
-static CvTrainFwdFn pick_train_fwd(int payoff, int M)
-{
-    switch (payoff) {
-    case kCall: return M == 2 ? cv_train_fwd_kernel<MODEL, kCall, 2> : cv_train_fwd_kernel<MODEL, kCall, 4>;
-    case kAsian: return M == 2 ? cv_train_fwd_kernel<MODEL, kAsian, 2> : cv_train_fwd_kernel<MODEL, kAsian, 4>;
-    case kLookback:
-        return M == 2 ? cv_train_fwd_kernel<MODEL, kLookback, 2> : cv_train_fwd_kernel<MODEL, kLookback, 4>;
-    default: return M == 2 ? cv_train_fwd_kernel<MODEL, kDigital, 2> : cv_train_fwd_kernel<MODEL, kDigital, 4>;
-    }
-}
-
-template <int MODEL, int PAYOFF>
-static CvBwdFn pick_bwd_m(int M)
-{
-    return M == 2 ? cv_backward_kernel<MODEL, PAYOFF, 2> : cv_backward_kernel<MODEL, PAYOFF, 4>;
-}
-
-template <int MODEL>
-static CvBwdFn pick_bwd_payoff(int payoff, int M)
-{
-    switch (payoff) {
-    case kCall: return pick_bwd_m<MODEL, kCall>(M);
-    case kAsian: return pick_bwd_m<MODEL, kAsian>(M);
-    case kLookback: return pick_bwd_m<MODEL, kLookback>(M);
-    default: return pick_bwd_m<MODEL, kDigital>(M);
-    }
-}
 
 template <int MODEL, int PAYOFF>
 static CvFn pick_cv_m(int M)
@@ -786,183 +426,6 @@ hipError_t cv_launch_level(const mlmc_cv* ccv, const mlmc_model& m, const mlmc_p
     return hipGetLastError();
 }
 
-// The backward launch of level l for a batch of B: segments per path (a
-// power of two dividing the level's generator groups, so that the level
-// has about kBwdBlocks blocks of 64 samples x segment) and its grid.
-constexpr uint64_t kBwdBlocks = 2048;
-struct BwdShape {
-    uint32_t segs;
-    int grid;
-};
-static BwdShape bwd_shape(uint64_t B, int l, int M)
-{
-    uint64_t nf = 1;
-    for (int i = 0; i < l; ++i) nf *= (uint64_t)M;
-    const uint64_t groups = (nf + 3) / 4, nchunks = (B + 63) / 64;
-    uint32_t segs = 1;
-    while ((uint64_t)segs * 2 <= groups && groups % ((uint64_t)segs * 2) == 0 &&
-           nchunks * segs * 2 <= kBwdBlocks)
-        segs *= 2;
-    const uint64_t units = nchunks * segs;
-    return BwdShape{segs, (int)(units < kBwdBlocks ? units : kBwdBlocks)};
-}
-
-// Rows of per-block gradient partials of one training step, and the
-// reduction's first-pass rows after them (the gradient is the row after).
-static int bwd_rows(uint64_t B, int lmax, int M)
-{
-    int rows = 0;
-    for (int l = 0; l <= lmax; ++l) rows += bwd_shape(B, l, M).grid;
-    return rows;
-}
-
-// Scratch for a training batch of B samples per level, levels 0..lmax.
-static mlmc_status ensure_train(mlmc_cv* cv, uint64_t B, int lmax, int M)
-{
-    mlmc_ctx* ctx = cv->ctx;
-    const uint64_t need = B * (uint64_t)(lmax + 1);
-    const int brows = bwd_rows(B, lmax, M);
-    const int rows = brows + (brows + kReduceRows - 1) / kReduceRows;
-    if (cv->batch_cap < need) {
-        if (cv->d_y) hipFree(cv->d_y);
-        if (cv->d_w) hipFree(cv->d_w);
-        cv->d_y = nullptr;
-        cv->d_w = nullptr;
-        MLMC_HIP(ctx, hipMalloc(&cv->d_y, sizeof(double) * 2 * need));
-        MLMC_HIP(ctx, hipMalloc(&cv->d_w, sizeof(float) * need));
-        cv->batch_cap = need;
-    }
-    // the forward runs' partials of the level with the most runs
-    uint64_t fneed = 0;
-    for (int l = 0; l <= lmax; ++l) {
-        const uint64_t segs = bwd_shape(B, l, M).segs;
-        if (segs > 1 && (2 * segs + 2) * B > fneed) fneed = (2 * segs + 2) * B;
-    }
-    if (cv->fpart_cap < fneed) {
-        if (cv->d_fpart) hipFree(cv->d_fpart);
-        cv->d_fpart = nullptr;
-        cv->fpart_cap = 0;
-        MLMC_HIP(ctx, hipMalloc(&cv->d_fpart, sizeof(float) * fneed));
-        cv->fpart_cap = fneed;
-    }
-    if (cv->gpart_blocks < rows + 1) {
-        if (cv->d_gpart) hipFree(cv->d_gpart);
-        cv->d_gpart = nullptr;
-        MLMC_HIP(ctx, hipMalloc(&cv->d_gpart, sizeof(float) * (uint64_t)(rows + 1) * cv->np));
-        cv->gpart_blocks = rows + 1;
-    }
-    return MLMC_OK;
-}
-
-// Kernel arguments of level l of a training batch (the training streams;
-// fetch_group forms every counter from the sample index, so no counter words
-// are set).
-static LevelArgs<float> train_args(const mlmc_model& m, const mlmc_payoff& p, int l, int M, uint64_t B,
-                                   uint64_t seed, uint64_t offset)
-{
-    LevelArgs<float> a;
-    a.P = make_step_params<float>(m, p, l, M);
-    a.seed = seed;
-    a.offset = offset;
-    a.N = B;
-    a.l = l;
-    int nf = 1;
-    for (int i = 0; i < l; ++i) nf *= M;
-    a.nf = nf;
-    a.ngroups = (uint32_t)((nf + 3) / 4);
-    a.stream = kStreamTrainNormal;
-    a.acc = nullptr;
-    a.pf_out = a.pc_out = nullptr;
-    a.coupled = 1;
-    a.phi0 = nullptr;
-    return a;
-}
-
-// One loss/gradient evaluation: forward pass with per-sample dumps, weights,
-// backward pass into per-block partials, reduction into the last row of
-// d_gpart.  Everything is enqueued on the context's stream.
-static mlmc_status enqueue_loss_grad(mlmc_cv* cv, const mlmc_model& m, const mlmc_payoff& p, int M,
-                                     int lmax, uint64_t B, uint64_t seed, uint64_t step,
-                                     LevelAcc* rec, float** grad_out)
-{
-    mlmc_ctx* ctx = cv->ctx;
-    mlmc_status st = ensure_train(cv, B, lmax, M);
-    if (st) return st;
-    MLMC_HIP(ctx, zero_records(rec, lmax + 1, ctx->stream));
-    MLMC_HIP(ctx, hipMemsetAsync(cv->d_loss, 0, sizeof(double) * 64, ctx->stream));
-    const uint64_t offset = step * B;
-    CvKernelArgs c{cv->d_params, cv->d_afwd, net_consts(m), cv->D};
-    for (int l = 0; l <= lmax; ++l) {
-        double* pf = cv->d_y + 2 * (uint64_t)l * B;
-        const BwdShape bs = bwd_shape(B, l, M);
-        if (bs.segs == 1) {
-            // one sample per lane (the sampler's own launch)
-            st = enqueue_level(ctx, m, p, l, M, B, seed, offset, 32, kStreamTrainNormal, 1, &rec[l],
-                               pf, pf + B, cv);
-            if (st) return st;
-            continue;
-        }
-        // a deep level in runs of generator groups, as the backward pass
-        LevelArgs<float> a = train_args(m, p, l, M, B, seed, offset);
-        a.acc = &rec[l];
-        a.pf_out = pf;
-        a.pc_out = pf + B;
-        a.coupled = 1;
-        const CvTrainFwdFn fwd = m.kind == MLMC_GBM ? pick_train_fwd<kGBM>(p.kind, M)
-                                                    : pick_train_fwd<kHeston>(p.kind, M);
-        hipLaunchKernelGGL(fwd, dim3(bs.grid), dim3(64), 0, ctx->stream, a, c, bs.segs, cv->d_fpart);
-        MLMC_HIP(ctx, hipGetLastError());
-        const int cgrid = (int)((B + 255) / 256 < 256 ? (B + 255) / 256 : 256);
-        hipLaunchKernelGGL(cv_train_combine_kernel, dim3(cgrid), dim3(256), 0, ctx->stream, a, bs.segs,
-                           (const float*)cv->d_fpart);
-        MLMC_HIP(ctx, hipGetLastError());
-    }
-    hipLaunchKernelGGL(cv_weights_kernel, dim3(lmax + 1), dim3(256), 0, ctx->stream,
-                       (const LevelAcc*)rec, (const double*)cv->d_y, B, M, cv->d_w, cv->d_loss);
-    MLMC_HIP(ctx, hipGetLastError());
-    int row0 = 0;
-    const int tix = timed_begin(ctx, 18, 0.0, 0.0);
-    for (int l = 0; l <= lmax; ++l) {
-        const LevelArgs<float> a = train_args(m, p, l, M, B, seed, offset);
-        CvBwdFn fn = m.kind == MLMC_GBM ? pick_bwd_payoff<kGBM>(p.kind, M)
-                                        : pick_bwd_payoff<kHeston>(p.kind, M);
-        const BwdShape bs = bwd_shape(B, l, M);
-        hipLaunchKernelGGL(fn, dim3(bs.grid), dim3(64), 0, ctx->stream, a, c,
-                           (const bf16x8*)cv->d_abwd, (const float*)(cv->d_w + (uint64_t)l * B),
-                           cv->d_gpart + (uint64_t)row0 * cv->np, bs.segs);
-        MLMC_HIP(ctx, hipGetLastError());
-        row0 += bs.grid;
-    }
-    // two passes in a fixed order: chunks of kReduceRows rows, then the chunks
-    const int nchunk = (row0 + kReduceRows - 1) / kReduceRows;
-    float* partial = cv->d_gpart + (uint64_t)row0 * cv->np;
-    float* grad = partial + (uint64_t)nchunk * cv->np;
-    hipLaunchKernelGGL(cv_reduce_rows_kernel, dim3((cv->np + 255) / 256, nchunk), dim3(256), 0,
-                       ctx->stream, (const float*)cv->d_gpart, row0, cv->np, partial);
-    MLMC_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL(cv_reduce_kernel, dim3((cv->np + 255) / 256), dim3(256), 0, ctx->stream,
-                       (const float*)partial, nchunk, cv->np, grad);
-    MLMC_HIP(ctx, hipGetLastError());
-    timed_end(ctx, tix);
-    *grad_out = grad;
-    return MLMC_OK;
-}
-
-static mlmc_status check_train_args(mlmc_cv* cv, const mlmc_model* m, const mlmc_payoff* p, int M,
-                                    int lmax, uint64_t B)
-{
-    mlmc_ctx* ctx = cv->ctx;
-    mlmc_status st = check_level_args(ctx, m, p, lmax < 0 ? 0 : lmax, M, 32);
-    if (st) return st;
-    if (lmax < 0 || lmax > 6) return fail(ctx, MLMC_EINVAL, "lmax must be in 0..6");
-    if (B < 2 || B > (1ull << 24)) return fail(ctx, MLMC_EINVAL, "batch must be in 2..2^24 per level");
-    if (cv->D != (m->kind == MLMC_HESTON ? 3 : 2))
-        return fail(ctx, MLMC_EINVAL, "network inputs do not match the model (2: GBM, 3: Heston)");
-    if (m->scheme != MLMC_EULER || m->antithetic || p->kind == MLMC_DIGITAL_COND)
-        return fail(ctx, MLMC_EINVAL, "the control variate trains on plain Euler paths and payoffs");
-    return MLMC_OK;
-}
-
 const float* cv_phi0_ptr(const mlmc_cv* cv, bool tab) { return cv->d_phi0 + (tab ? 1 : 0); }
 int cv_in_dim(const mlmc_cv* cv) { return cv->D; }
 
@@ -989,8 +452,8 @@ mlmc_status mlmc_cv_destroy(mlmc_cv* cv)
     if (!cv) return MLMC_OK;
     if (cv->ctx) hipSetDevice(cv->ctx->device);
     for (void* p : {(void*)cv->d_params, (void*)cv->d_m1, (void*)cv->d_m2, (void*)cv->d_afwd,
-                    (void*)cv->d_abwd, (void*)cv->d_phi0, (void*)cv->d_gpart, (void*)cv->d_y,
-                    (void*)cv->d_w, (void*)cv->d_loss, (void*)cv->d_table, (void*)cv->d_fpart})
+                    (void*)cv->d_abwd, (void*)cv->d_phi0, (void*)cv->d_train, (void*)cv->d_loss,
+                    (void*)cv->d_table})
         if (p) hipFree(p);
     delete cv;
     return MLMC_OK;
@@ -1093,86 +556,6 @@ mlmc_status mlmc_cv_get_table(mlmc_cv* cv, const mlmc_model* model, float* host,
                                  ctx->stream));
     MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return MLMC_OK;
-}
-
-mlmc_status mlmc_cv_loss_grad(mlmc_cv* cv, const mlmc_model* model, const mlmc_payoff* payoff,
-                              int M, int lmax, uint64_t batch, uint64_t seed, uint64_t step,
-                              float* grad, double* var, double* loss)
-{
-    if (!cv) return MLMC_EINVAL;
-    mlmc_ctx* ctx = cv->ctx;
-    mlmc_status st = check_train_args(cv, model, payoff, M, lmax, batch);
-    if (st) return st;
-    ctx->err.clear();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
-    float* d_grad = nullptr;
-    st = enqueue_loss_grad(cv, *model, *payoff, M, lmax, batch, seed, step, ctx->d_acc, &d_grad);
-    if (st) return st;
-    if (grad)
-        MLMC_HIP(ctx, hipMemcpyAsync(grad, d_grad, sizeof(float) * cv->np, hipMemcpyDeviceToHost,
-                                     ctx->stream));
-    double hl[64];
-    MLMC_HIP(ctx, hipMemcpyAsync(hl, cv->d_loss, sizeof(hl), hipMemcpyDeviceToHost, ctx->stream));
-    MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    harvest_timing(ctx);
-    if (loss) *loss = hl[0];
-    if (var)
-        for (int l = 0; l <= lmax; ++l) var[l] = hl[1 + l];
-    return MLMC_OK;
-}
-
-mlmc_status mlmc_cv_train(mlmc_cv* cv, const mlmc_model* model, const mlmc_payoff* payoff, int M,
-                          int lmax, int steps, uint64_t batch, double lr, uint64_t seed,
-                          float* loss_hist)
-{
-    if (!cv) return MLMC_EINVAL;
-    mlmc_ctx* ctx = cv->ctx;
-    mlmc_status st = check_train_args(cv, model, payoff, M, lmax, batch);
-    if (st) return st;
-    if (steps < 0 || !(lr > 0)) return fail(ctx, MLMC_EINVAL, "need steps >= 0 and lr > 0");
-    ctx->err.clear();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
-    double* d_hist = nullptr;
-    if (loss_hist && steps > 0) MLMC_HIP(ctx, hipMalloc(&d_hist, sizeof(double) * steps));
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    for (int k = 0; k < steps; ++k) {
-        const TraceRange step_range("mlmc_cv_train step");
-        float* d_grad = nullptr;
-        // each step draws fresh training samples: indices t * batch .. (t+1) * batch - 1
-        st = enqueue_loss_grad(cv, *model, *payoff, M, lmax, batch, seed, (uint64_t)cv->adam_t, ctx->d_acc,
-                               &d_grad);
-        if (st) break;
-        cv->adam_t += 1;
-        const float c1 = 1.0f - std::pow(b1, (float)cv->adam_t);
-        const float c2 = 1.0f - std::pow(b2, (float)cv->adam_t);
-        hipLaunchKernelGGL(cv_adam_kernel, dim3((cv->np + 255) / 256), dim3(256), 0, ctx->stream,
-                           cv->d_params, cv->d_m1, cv->d_m2, (const float*)d_grad, cv->np, (float)lr,
-                           b1, b2, eps, c1, c2);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = cv_prepare(cv, ctx->stream);
-        if (e == hipSuccess && d_hist)
-            e = hipMemcpyAsync(d_hist + k, cv->d_loss, sizeof(double), hipMemcpyDeviceToDevice,
-                               ctx->stream);
-        if (e != hipSuccess) {
-            st = hip_fail(ctx, e, "training step");
-            break;
-        }
-    }
-    if (!st && d_hist) {
-        std::vector<double> h(steps);
-        hipError_t e = hipMemcpyAsync(h.data(), d_hist, sizeof(double) * steps,
-                                      hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e != hipSuccess) st = hip_fail(ctx, e, "loss history copy");
-        for (int k = 0; k < steps; ++k) loss_hist[k] = (float)h[k];
-    }
-    if (!st) {
-        hipError_t e = hipStreamSynchronize(ctx->stream);
-        if (e != hipSuccess) st = hip_fail(ctx, e, "training");
-        harvest_timing(ctx);
-    }
-    if (d_hist) hipFree(d_hist);
-    return st;
 }
 
 }  // extern "C"
