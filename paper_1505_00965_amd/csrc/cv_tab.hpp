@@ -41,10 +41,10 @@ __device__ __forceinline__ void fetch_group(const LevelArgs<float>& a, uint64_t 
         }
         if (PAYOFF == kLookback) {
             const u32x4 u = path_block(make_path_key(a.seed, a.l, s, a.stream + 1u), g);
-            e[0] = P.lnu_scale * flog2<float>(u01f(u.x));
-            e[1] = P.lnu_scale * flog2<float>(u01f(u.y));
-            e[2] = P.lnu_scale * flog2<float>(u01f(u.z));
-            e[3] = P.lnu_scale * flog2<float>(u01f(u.w));
+            e[0] = bridge_exponent(u.x, P);
+            e[1] = bridge_exponent(u.y, P);
+            e[2] = bridge_exponent(u.z, P);
+            e[3] = bridge_exponent(u.w, P);
         }
         return;
     }
@@ -68,7 +68,7 @@ __device__ __forceinline__ void fetch_group(const LevelArgs<float>& a, uint64_t 
         for (int k = 0; k < 4; ++k) {
             const int iw = (ub + k) & 3;
             const uint32_t word = iw == 0 ? u.x : iw == 1 ? u.y : iw == 2 ? u.z : u.w;
-            e[k] = P.lnu_scale * flog2<float>(u01f(word));
+            e[k] = bridge_exponent(word, P);
         }
     }
 }
@@ -133,10 +133,10 @@ __device__ __forceinline__ void advance_group_tab(const StepParams<float>& P, co
     }
     if (PAYOFF == kLookback) {
         const u32x4 u = path_block(bkey, g);
-        e[0] = P.lnu_scale * flog2<float>(u01f(u.x));
-        e[1] = P.lnu_scale * flog2<float>(u01f(u.y));
-        e[2] = P.lnu_scale * flog2<float>(u01f(u.z));
-        e[3] = P.lnu_scale * flog2<float>(u01f(u.w));
+        e[0] = bridge_exponent(u.x, P);
+        e[1] = bridge_exponent(u.y, P);
+        e[2] = bridge_exponent(u.z, P);
+        e[3] = bridge_exponent(u.w, P);
     } else {
         e[0] = e[1] = e[2] = e[3] = 0.0f;
     }

@@ -145,6 +145,7 @@ template <typename Real>
 __global__ void normals_kernel(uint64_t seed, int level, uint64_t s0, uint32_t stream,
                                uint32_t nblocks, int total_per_path, uint64_t npaths, double* out)
 {
+    if constexpr (sizeof(Real) == 8) load_normal_tables();
     const uint64_t total = npaths * nblocks;
     for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < total;
          t += (uint64_t)gridDim.x * blockDim.x) {

@@ -20,6 +20,7 @@ namespace mlmc {
 template <int MODEL, int PAYOFF, typename Real, int M, int PPT, bool ANTI>
 __global__ __launch_bounds__(1024) void level_kernel(LevelArgs<Real> a)
 {
+    if constexpr (sizeof(Real) == 8) load_normal_tables();
     double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
     unsigned nonfinite = 0;
     const uint64_t chunk = (uint64_t)blockDim.x * PPT;
@@ -33,6 +34,7 @@ __global__ __launch_bounds__(1024) void level_kernel(LevelArgs<Real> a)
 template <int MODEL, int PAYOFF, typename Real, int NF, int M, int PPT, bool ANTI>
 __global__ __launch_bounds__(1024) void short_level_kernel(LevelArgs<Real> a)
 {
+    if constexpr (sizeof(Real) == 8) load_normal_tables();
     constexpr int Q = 4 / (NF * (one_factor(MODEL) ? 1 : 2));
     double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
     unsigned nonfinite = 0;

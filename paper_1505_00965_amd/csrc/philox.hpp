@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "normal64.hpp"
+
 namespace mlmc {
 
 enum Stream : uint32_t {
@@ -110,12 +112,14 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, float& z0, fl
     z1 = rho * __builtin_amdgcn_sinf(u2);
 }
 
-__device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& z0, double& z1)
+// In fp64 (the block's tables must have been loaded: load_normal_tables);
+// the radius is scaled by `scale`.
+__device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& z0, double& z1,
+                                           double scale = 1.0)
 {
-    const double u1 = u01d(a), u2 = u01d(b);
-    const double rho = sqrt(-2.0 * log(u1));
+    const double rho = scale * sqrt_normal(neg2_log32(u01_32(a)));
     double s, c;
-    sincospi(2.0 * u2, &s, &c);
+    cos_sin32(u01_32(b), c, s);
     z0 = rho * c;
     z1 = rho * s;
 }

@@ -52,30 +52,16 @@ template <>
 __device__ __forceinline__ double fsqrt<double>(double x) { return sqrt(x); }
 
 template <typename Real>
-__device__ __forceinline__ Real flog2(Real x);
-template <>
-__device__ __forceinline__ float flog2<float>(float x) { return __builtin_amdgcn_logf(x); }
-template <>
-__device__ __forceinline__ double flog2<double>(double x) { return log2(x); }
-
-template <typename Real>
 __device__ __forceinline__ Real fmaxT(Real a, Real b);
 template <>
 __device__ __forceinline__ float fmaxT<float>(float a, float b) { return __builtin_fmaxf(a, b); }
 template <>
 __device__ __forceinline__ double fmaxT<double>(double a, double b) { return __builtin_fmax(a, b); }
 
-template <typename Real>
-__device__ __forceinline__ Real uniform01(uint32_t x);
-template <>
-__device__ __forceinline__ float uniform01<float>(uint32_t x) { return u01f(x); }
-template <>
-__device__ __forceinline__ double uniform01<double>(uint32_t x) { return u01d(x); }
-
 // Brownian increments sqrt(h) z0, sqrt(h) z1 of one Box--Muller pair.  In
 // fp32 the step size goes into the radius, sqrt(-2 h ln u1) =
 // sqrt(lnu_scale log2 u1), which saves the two products by sqrt(h); fp64
-// scales the standard normals.
+// scales the radius.
 __device__ __forceinline__ void brownian_pair(uint32_t a, uint32_t b, const StepParams<float>& P,
                                               float& d0, float& d1)
 {
@@ -88,10 +74,17 @@ __device__ __forceinline__ void brownian_pair(uint32_t a, uint32_t b, const Step
 __device__ __forceinline__ void brownian_pair(uint32_t a, uint32_t b, const StepParams<double>& P,
                                               double& d0, double& d1)
 {
-    double z0, z1;
-    box_muller(a, b, z0, z1);
-    d0 = P.sqh * z0;
-    d1 = P.sqh * z1;
+    box_muller(a, b, d0, d1, P.sqh);
+}
+
+// Exponent -2 h ln U of a bridge minimum from its uniform's word.
+__device__ __forceinline__ float bridge_exponent(uint32_t x, const StepParams<float>& P)
+{
+    return P.lnu_scale * __builtin_amdgcn_logf(u01f(x));
+}
+__device__ __forceinline__ double bridge_exponent(uint32_t x, const StepParams<double>& P)
+{
+    return P.h * neg2_log32(u01_32(x));
 }
 
 // Compensated (Kahan) accumulation for the Asian average: the path values

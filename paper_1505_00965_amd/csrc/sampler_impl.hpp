@@ -95,10 +95,10 @@ __device__ __forceinline__ void advance_group(const StepParams<Real>& P, const P
     }
     if (PAYOFF == kLookback) {
         const u32x4 u = path_block(bkey, g);
-        e[0] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.x));
-        e[1] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.y));
-        e[2] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.z));
-        e[3] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.w));
+        e[0] = bridge_exponent(u.x, P);
+        e[1] = bridge_exponent(u.y, P);
+        e[2] = bridge_exponent(u.z, P);
+        e[3] = bridge_exponent(u.w, P);
     } else {
         e[0] = e[1] = e[2] = e[3] = Real(0);
     }
@@ -320,10 +320,10 @@ __device__ __forceinline__ void process_short(const LevelArgs<Real>& a, uint64_t
             // every sample of this generator block reads bridge block B / D
             const u32x4 u =
                 path_block(PathKey{k0, k1, (uint32_t)(B[p] / D), a.c2b, a.stream + 1u}, 0);
-            e[0] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.x));
-            e[1] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.y));
-            e[2] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.z));
-            e[3] = P.lnu_scale * flog2<Real>(uniform01<Real>(u.w));
+            e[0] = bridge_exponent(u.x, P);
+            e[1] = bridge_exponent(u.y, P);
+            e[2] = bridge_exponent(u.z, P);
+            e[3] = bridge_exponent(u.w, P);
         }
 #pragma unroll
         for (int r = 0; r < Q; ++r) {
