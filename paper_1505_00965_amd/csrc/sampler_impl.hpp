@@ -73,8 +73,8 @@ __host__ __device__ constexpr bool twin_coarse()
 // Generator block g of a path (four fine steps): its increments, advanced
 // through q's fine and coarse paths; with ANTI also through the antithetic
 // twin qa (same generator words, the increments reversed inside every
-// coarse step).
-template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI>
+// coarse step).  Without COUPLED only the fine path is advanced.
+template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
 __device__ __forceinline__ void advance_group(const StepParams<Real>& P, const PathKey& key,
                                               const PathKey& bkey, uint32_t g, PathPair<Real>& q,
                                               PathPair<Real>& qa)
@@ -104,8 +104,8 @@ __device__ __forceinline__ void advance_group(const StepParams<Real>& P, const P
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        fine_step<Real, MODEL, PAYOFF>(q, P, dw1[k], dwp[k], e[k], k % M, true);
-        if (((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(q, P);
+        fine_step<Real, MODEL, PAYOFF>(q, P, dw1[k], dwp[k], e[k], k % M, COUPLED);
+        if (COUPLED && ((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(q, P);
     }
     if (ANTI) {
 #pragma unroll
@@ -135,13 +135,23 @@ __device__ __forceinline__ void simulate(const LevelArgs<Real>& a, const uint64_
         if (ANTI) init_pair<Real, MODEL, PAYOFF>(qa[p], P);
     }
     // n_f >= 4 here (a multiple of 4): every group holds four fine steps.
-    // The coarse path is advanced even when the caller drops it (standard
-    // Monte Carlo at one level): a per-step choice would cost more lane
-    // operations on the coupled levels than the coarse steps cost there.
-    for (uint32_t g = 0; g < a.ngroups; ++g) {
+    // Standard Monte Carlo (no coarse path) has a loop of its own, chosen once
+    // per chunk: a choice per step would cost the coupled levels more lane
+    // operations than the coarse steps cost the comparator (digital, M = 2,
+    // level 6, 4e6 paths: 155 us with the coarse path advanced and dropped,
+    // 143 without it).
+    if (ANTI || a.coupled) {
+        for (uint32_t g = 0; g < a.ngroups; ++g) {
 #pragma unroll
-        for (int p = 0; p < PPT; ++p)
-            advance_group<MODEL, PAYOFF, Real, M, ANTI>(P, key[p], bkey[p], g, q[p], qa[p]);
+            for (int p = 0; p < PPT; ++p)
+                advance_group<MODEL, PAYOFF, Real, M, ANTI>(P, key[p], bkey[p], g, q[p], qa[p]);
+        }
+    } else {
+        for (uint32_t g = 0; g < a.ngroups; ++g) {
+#pragma unroll
+            for (int p = 0; p < PPT; ++p)
+                advance_group<MODEL, PAYOFF, Real, M, false, false>(P, key[p], bkey[p], g, q[p], qa[p]);
+        }
     }
 }
 
