@@ -13,8 +13,21 @@ namespace mlmc {
 
 constexpr int kMaxSlots = 4;          // payoffs per batch
 constexpr int kPairs = kMaxSlots * kMaxLevels;
-constexpr int kItemsPerBlock = 4;     // target items per resident block
-constexpr unsigned kItemsPerPair = 1024;
+// Items per resident block the plan aims at: four, or as many as hold
+// kItemSteps path steps each, up to sixteen; a pair is cut into at most 256
+// times as many.  Four-payoff batches of 3e9 steps took 2.08 ms with four items per
+// block and 1.91 with sixteen; an estimate's launches (1.4e8 steps, 5 pairs)
+// 353 us in all with four and 375 with eight: an item's decode, parameters
+// and block reduction cost ~3 us.
+constexpr double kItemsMin = 4.0, kItemsMax = 16.0, kItemSteps = 65536.0;
+// Dispensers: blocks and items are dealt to groups by their number modulo
+// kHeads, and the items past the first per block come from the group's own
+// counter, a cache line each.  One counter for all serves a block per ~10 ns,
+// so the ~3000 draws of a launch were a third of it: estimates at RMSE
+// 1e-4 S0 (GBM call, Asian, lookback) 110, 158, 163 us with one counter and
+// 79, 111, 119 with 32; at 2e-5 S0 397 and 353.
+constexpr int kHeads = 32;
+constexpr int kHeadStride = 16;       // counters of 4 bytes, one per 64
 
 struct WorkItem {
     uint64_t first;     // first sample index of the range
@@ -51,7 +64,7 @@ struct BatchDesc {
     const double* offset;
     LevelAcc* acc;                    // spread groups [slot][level][kSpread]
     PlanTable* plan;                  // written by the plan, read by the sampler
-    unsigned* head;                   // dispenser of the items past the first gridDim.x
+    unsigned* head;                   // dispensers of the items past the first gridDim.x
     unsigned resident_blocks;         // grid size of the sampler
     unsigned chunk;                   // blockDim * PPT of the sampler
     unsigned block;                   // blockDim of the sampler
@@ -281,7 +294,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
     // samples x steps over the batch (lane 0's sum: the rotations leave
     // other lanes with other association orders)
     const double total = __shfl(wave_sum(valid ? dn * per : 0.0), 0);
-    const double target = total / ((double)a.resident_blocks * kItemsPerBlock);
+    const double per_block = fmin(fmax(total / (a.resident_blocks * kItemSteps), kItemsMin), kItemsMax);
+    const double target = total / (a.resident_blocks * per_block);
+    const uint64_t most = (uint64_t)(256.0 * per_block);   // items per pair
     const uint64_t left = (uint64_t)dn;
     const uint64_t first = valid ? (uint64_t)off[s * kMaxLevels + l] : 0;
     uint64_t base = first;
@@ -307,10 +322,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
                 paths = 2 * paths >= a.block + unit ? unit : a.block;
             }
             if (paths > (1ull << 31)) paths = 1ull << 31;   // item sizes fit 32 bits
-            // at most kItemsPerPair items per pair (one more when cut on the
-            // chunk grid below): item indices stay small
-            const uint64_t min_items = (left + kItemsPerPair - 1) / kItemsPerPair;
-            per_item = paths > min_items ? paths : min_items;
+            // (one more item when cut on the chunk grid below)
+            const uint64_t min_paths = ceil_div_u53(left, most);
+            per_item = paths > min_paths ? paths : min_paths;
             if (G == 1 && per_item > a.block) {
                 // whole chunks (the sampler simulates a whole chunk, the
                 // samples past the item's end included), cut on a grid of
@@ -349,8 +363,8 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
         const int np = __popcll(active);
         t->start[np] = incl;
         t->npairs = np;
-        if (a.head) *a.head = 0;
     }
+    if (a.head && p < kHeads) a.head[p * kHeadStride] = 0;
 }
 
 // Item `it` of the plan (block-uniform).
@@ -372,8 +386,8 @@ __device__ __forceinline__ WorkItem plan_item(const PlanTable& t, unsigned it)
 // Launch flags of the sampler.
 constexpr unsigned kSeedArg = 1;   // the seed is the launch's argument (else the descriptor's)
 
-// Block b takes item b first; later items come from the dispenser until
-// none are left, so a launch with no more items than blocks (an empty one
+// Block b takes item b first; later items come from its group's dispenser
+// until that has none left, so a launch with no more items than blocks (an empty one
 // included) makes no atomics on it.  Each item ends with a block reduction
 // into its (payoff, level) spread group.
 template <int MODEL, int M, int PPT, int PAYOFF, bool CV>
@@ -415,7 +429,11 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
         block_reduce_add(sums, nonfinite, &d->acc[(w.slot * kMaxLevels + w.level) * kSpread +
                                                   (blockIdx.x & (kSpread - 1))]);
         if (count <= gridDim.x) break;
-        if (threadIdx.x == 0) s_item = gridDim.x + atomicAdd(d->head, 1u);
+        if (threadIdx.x == 0) {
+            // the group's next item: those with its number modulo kHeads, from gridDim.x on
+            const unsigned g = blockIdx.x % kHeads, past = gridDim.x % kHeads;
+            s_item = gridDim.x + (g + kHeads - past) % kHeads + kHeads * atomicAdd(d->head + g * kHeadStride, 1u);
+        }
         __syncthreads();
         it = __builtin_amdgcn_readfirstlane(s_item);
         __syncthreads();
