@@ -12,7 +12,7 @@
 //   train_paths    every path of the batch once: per point the network's
 //                  inputs and the coefficient c of phi in Y (-dW1 on the fine
 //                  path, +dW1 on the coarse one), per sample the payoffs
-//   train_forward  phi c for every point, 64 points of one time per wave
+//   train_forward  phi at every point, 64 points of one time per wave
 //   train_combine  Y per sample, the level sums; phi(0, S0) once
 //   train_backward the parameter gradient over all points, one partial row
 //                  per block
@@ -20,7 +20,7 @@
 // Points are independent units of equal cost: both network passes deal them
 // out evenly whatever the levels (a launch per level, in runs of steps, left
 // the device a fifth full: 0.50 ms per step of 16384 samples on levels 0..3,
-// now 0.19), and the paths are stepped twice a step at most instead of
+// now 0.20), and the paths are stepped twice a step at most instead of
 // once per run.  Every path starts at (0, S0), so the points at t = 0 share
 // one network evaluation: level 0 needs no other.
 //
@@ -49,6 +49,9 @@ constexpr int kTrainLevels = 7;               // lmax <= 6
 constexpr uint64_t kMaxPoints = 1ull << 24;   // points in memory at once
 constexpr int kMaxSteps = 16;                 // steps whose paths one launch makes
 constexpr int kGradRow = 4544;                // floats per partial row (>= nparams, 16-byte rows)
+// Times of the backward kernel's blocks: 34 ns per (level, sample) pair of the
+// start point, 4.8 us per 64 points (four blocks per compute unit).
+constexpr double kStartPairCost = 34.0, kTaskCost = 4800.0;
 constexpr int kBwdBlocksPerCu = 4;            // the backward kernel's residency (registers, LDS)
 constexpr int kFwdBlocksPerCu = 4;
 
@@ -57,6 +60,7 @@ struct TrainLevel {
     int nf, ngroups;
     uint32_t row0;      // first point row of the level: fine steps 1.., then coarse steps 1..
     uint32_t blk0;      // first block of the level's samples (256 per block)
+    uint32_t runs;      // runs of generator groups a sample's sums are taken in
 };
 
 // One chunk of a training batch: samples offset .. offset + n - 1 of every
@@ -71,18 +75,18 @@ struct TrainArgs {
     float S0, v0;
     float *x1, *x2;         // [nrows][stride] network inputs of each point
     float *c;               // [nrows][stride] coefficient of phi in Y
-    float *prod;            // [nrows][stride] phi c
+    float *phi;             // [nrows][stride] phi of each point
     float *x0;              // [nrows] time input
     float2 *pay;            // [nlev][stride] fine and coarse payoff
-    double *c0;             // [nlev][stride] coefficient of phi(0, S0)
+    float2 *c0;             // [nlev][stride] coefficients of phi(0, S0): fine, coarse
     double *y;              // [nlev][Bpad]
     float *phi0;            // phi(0, S0)
-    // per level: sums of Y, Y^2, Y c0, c0 over the batch
+    // per level: sums of Y and Y^2 over the batch
     LevelAcc *rec;
 };
 
 // The arguments of step k of a group: its samples and its buffers (all but
-// prod, x0, y and phi0, which every step shares).
+// phi, x0, y and phi0, which every step shares).
 __host__ __device__ __forceinline__ TrainArgs for_step(TrainArgs a, uint32_t k)
 {
     const uint64_t pts = (uint64_t)k * a.nrows * a.stride, smp = (uint64_t)k * a.nlev * a.stride;
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(256) void train_paths_kernel(TrainArgs a, NetConsts
     auto put_c = [&](uint32_t r, float c) { cs[(uint64_t)r * a.stride] = in ? c : 0.0f; };
     PathPair<float> q;
     init_pair<float, MODEL, PAYOFF>(q, P);
-    double c0 = 0.0;
+    float2 c0 = make_float2(0.0f, 0.0f);
     for (uint32_t g = 0; g < (uint32_t)L.ngroups; ++g) {
         float dw1[4], dwp[4], e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         fetch_group<MODEL, PAYOFF>(la, s, g, dw1, dwp, e);
@@ -160,13 +164,13 @@ __global__ __launch_bounds__(256) void train_paths_kernel(TrainArgs a, NetConsts
                 put_c(n - 1, -dw1[k]);
                 if (coupled && n % M == 0) put(nf - 1 + n / M - 1, q.Sc, q.vc);
             } else {
-                c0 = -(double)dw1[0];
+                c0.x = -dw1[0];
             }
             fine_step<float, MODEL, PAYOFF>(q, P, dw1[k], dwp[k], e[k], n % M, coupled);
             if (coupled && (n + 1) % M == 0) {
                 const int m = n / M;
                 if (m > 0) put_c(nf - 1 + m - 1, q.dw1c);
-                else c0 += (double)q.dw1c;
+                else c0.y = q.dw1c;
                 coarse_step<float, MODEL, PAYOFF>(q, P);
             }
         }
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(256) void train_paths_kernel(TrainArgs a, NetConsts
 }
 
 // ---------------------------------------------------------------- forward
-// phi c for 64 points of one row per wave.  Bound by the vector ALU: ~900
+// phi for 64 points of one row per wave.  Bound by the vector ALU: ~900
 // instructions a point of which 256 transcendental (two issue slots each),
 // so four waves per SIMD (128 registers: the network's constants stay in
 // LDS) keep it issuing.
@@ -208,41 +212,70 @@ __global__ __launch_bounds__(256, kFwdBlocksPerCu) void train_forward_kernel(Tra
     for (uint32_t t = blockIdx.x * (blockDim.x / 64) + wave; t < total; t += nw) {
         const uint32_t row = __builtin_amdgcn_readfirstlane(t / cw), ch = t - row * cw;
         const uint64_t at = (uint64_t)row * a.stride + ch * 64 + lane;
-        const float phi = phi_eval_x<D>(sh, s_afwd, a.x0[row], a.x1[at], D == 3 ? a.x2[at] : 0.0f);
-        a.prod[at] = phi * a.c[at];
+        a.phi[at] = phi_eval_x<D>(sh, s_afwd, a.x0[row], a.x1[at], D == 3 ? a.x2[at] : 0.0f);
     }
 }
 
-// Y of every sample: payoffs plus the points' terms, in row order and fp64,
-// plus phi(0, S0) c0; the level sums.  A lane's loads go out 32 at a time
-// (latency-bound: one wave per SIMD or less).
+// Y of every sample and the level sums.  The two paths' sums of phi dW are
+// taken in fp32 as the samplers take them, step by step with fused
+// multiply-adds, and on levels of several runs run by run, the runs' sums
+// added in order: the sums' rounding decides which way d2 rounds to bf16 in
+// the backward pass, so it does not depend on the launches' shapes.  Bound by
+// the latency of the loads: a block of four waves takes 64 samples, a run per
+// wave at a time (16384 samples on levels 0..3: 12.6 us; with a lane for all of a
+// sample's runs 27).
 __global__ __launch_bounds__(256) void train_combine_kernel(TrainArgs a)
 {
-    const int l = block_level(a, blockIdx.x);
+    __shared__ float s_run[2][4][64];
+    const uint32_t cw = a.stride / 64;
+    const int l = a.nlev - 1 - (int)(blockIdx.x / cw);          // deepest level first
     const TrainLevel& L = a.lev[l];
-    const uint32_t i = (blockIdx.x - L.blk0) * 256u + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t i = (blockIdx.x % cw) * 64 + lane;
+    const float phi0 = *a.phi0;
+    const float2 c0 = a.c0[(uint64_t)l * a.stride + i];
+    // run r of the sum of phi dW over the points s = 0 .. runs per - 1 of a
+    // path whose rows (from s = 1) start at `row`; the coefficients hold sign dW
+    auto run_of = [&](uint32_t row, int per, int r, float start, float sign) {
+        const float* ph = a.phi + (uint64_t)row * a.stride + i;
+        const float* cc = a.c + (uint64_t)row * a.stride + i;
+        float run = r ? 0.0f : __builtin_fmaf(phi0, sign * start, 0.0f);
+#pragma unroll 8
+        for (int s = r ? r * per : 1; s < (r + 1) * per; ++s) {
+            const uint64_t at = (uint64_t)(s - 1) * a.stride;
+            run = __builtin_fmaf(ph[at], sign * cc[at], run);
+        }
+        return run;
+    };
+    float cf = 0.0f, cc = 0.0f;
+    const int runs = l ? (int)L.runs : 0, nc = l ? L.nf / a.M : 0;
+    for (int r0 = 0; r0 < runs; r0 += 4) {                      // block-uniform
+        const int r = r0 + wave;
+        if (r < runs) {
+            s_run[0][wave][lane] = run_of(L.row0, L.nf / runs, r, c0.x, -1.0f);
+            s_run[1][wave][lane] = run_of(L.row0 + L.nf - 1, nc / runs, r, c0.y, 1.0f);
+        }
+        __syncthreads();
+        for (int k = 0; k < 4 && r0 + k < runs; ++k) {          // 0 + x is exact
+            cf += s_run[0][k][lane];
+            cc += s_run[1][k][lane];
+        }
+        __syncthreads();
+    }
     double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
     unsigned nonfinite = 0;
-    if (i < a.stride) {
-        const int nrow = (L.nf - 1) + (l > 0 ? L.nf / a.M - 1 : 0);
-        const float* pr = a.prod + (uint64_t)L.row0 * a.stride + i;
-        double cv = 0.0;
-#pragma unroll 32
-        for (int r = 0; r < nrow; ++r) cv += (double)pr[(uint64_t)r * a.stride];
+    if (wave == 0) {
         const float2 p = a.pay[(uint64_t)l * a.stride + i];
-        const double c0 = a.c0[(uint64_t)l * a.stride + i];
+        const float pf = l ? p.x - cf : __builtin_fmaf(phi0, c0.x, p.x);
+        const float pc = l ? p.y - cc : 0.0f;
         const bool in = i < a.n;
-        const double y = in ? ((double)p.x - (double)p.y) + __builtin_fma((double)*a.phi0, c0, cv) : 0.0;
+        const double y = in ? (double)pf - (double)pc : 0.0;
         a.y[(uint64_t)l * a.Bpad + a.first + i] = y;
-        if (in) {
-            if (isfinite(y)) {
-                sums[0] = y;
-                sums[1] = y * y;
-                sums[2] = y * c0;
-                sums[3] = c0;
-            } else {
-                nonfinite = 1;
-            }
+        if (in && isfinite(y)) {
+            sums[0] = y;
+            sums[1] = y * y;
+        } else if (in) {
+            nonfinite = 1;
         }
     }
     block_reduce_add(sums, nonfinite, &a.rec[l]);
@@ -266,7 +299,7 @@ __global__ __launch_bounds__(256) void train_combine_kernel(TrainArgs a)
 // reads them transposed (ds_read_b64_tr_b16: 24 reads a wave in place of
 // 128 two-byte ones).  Two buffers: a point's writes need no barrier after
 // the reads of the point before it.
-// 16384 samples on levels 0..3 (25344 tasks): 120 us, 74% of it issuing VALU; with one wave per block, two-byte
+// 16384 samples on levels 0..3 (25344 tasks): 127 us, 74% of it issuing VALU; with one wave per block, two-byte
 // transposed reads and a launch per level 300, with four waves of 32 x 32
 // (the constants read twice as often) 143.
 constexpr int kRowPad = 72;     // bf16 per staged row (64 + 8)
@@ -323,61 +356,90 @@ __device__ __forceinline__ void level_stats(const TrainArgs& a, int l, LevelStat
     s.scale[l] = var > 0 ? sqrt(C / var) / (n - 1.0) : 0.0;
 }
 
-// The gradient at the one point (0, S0) all paths share, g = sum over the
-// levels and samples of w c0 = scale (sum Y c0 - mean sum c0): one block on
-// the vector ALU, with W2 and (in gW2) h1 in bf16 as the matrix cores read
-// them; d2 stays in fp32.
+// The gradient at the one point (0, S0) all paths share: start block `b` of
+// `ns` takes its share of the chunk's (level, sample) pairs, fine and coarse
+// point each.  Only dy differs between them, so a pair costs the 64 units'
+// d2 = dy w3 (1 - h2^2), rounded to bf16 as at every other point and summed in
+// fp32; the products with W2 and h1 follow once from the sums.
 template <int D>
-__device__ __forceinline__ void start_point_row(const TrainArgs& a, const CvKernelArgs& c,
-                                                const NetShared& sh, const LevelStats& st, float* row)
+__device__ __forceinline__ void start_point_row(const TrainArgs& a, const CvKernelArgs& c, const NetShared& sh,
+                                                const LevelStats& st, uint32_t b, uint32_t ns, float* row)
 {
-    __shared__ float s_h1[H], s_d2[H], s_d1[H];
+    __shared__ __attribute__((aligned(16))) float s_dy[256];
+    __shared__ float s_h1[H], s_d2[2][H], s_sum[2];
     const float x1 = input_x1(sh, a.S0);
     const float x2 = D == 3 ? __builtin_fmaf(a.v0, sh.x2a, -sh.x2b) : 0.0f;
     const float* W2 = c.params + off_W2(D);
-    const int u = threadIdx.x;
-    double g = 0.0;
-    for (int l = 0; l < a.nlev; ++l)
-        g += st.scale[l] * (a.rec[l].sum[2] - st.mean[l] * a.rec[l].sum[3]);
-    const float dy = sh.scale * (float)g;
-    if (u < H) {
+    const int u = threadIdx.x & 63, half = threadIdx.x >> 6;
+    {
         // the time input is zero
         float z = __builtin_fmaf(sh.w1[u][1], x1, sh.w1[u][2]);
         if (D == 3) z = __builtin_fmaf(sh.w1[u][3], x2, z);
         s_h1[u] = tanh_fast(z);
     }
     __syncthreads();
-    if (u < H) {
-        float z = sh.b2[u];
-        for (int k = 0; k < H; ++k) z = __builtin_fmaf((float)(__bf16)W2[u * H + k], (float)(__bf16)s_h1[k], z);
-        const float hv = tanh_fast(z), dd = 1.0f - hv * hv;
-        const float d2 = dy * sh.w3[u] * dd;
-        s_d2[u] = d2;
-        row[off_w3(D) + u] = dy * hv;
-        row[off_b2(D) + u] = d2;
-        if (u == 0) row[off_b3(D)] = dy;
+    float z = sh.b2[u];
+    for (int k = 0; k < H; ++k) z = __builtin_fmaf((float)(__bf16)W2[u * H + k], (float)(__bf16)s_h1[k], z);
+    const float hv = tanh_fast(z), dd = 1.0f - hv * hv, w3 = sh.w3[u];
+    // 128 pairs at a time: a thread forms a pair's two dy, then each half
+    // block adds up one unit per thread over half of them
+    const uint32_t pairs = (uint32_t)a.nlev * a.n;
+    const uint32_t e0 = (uint32_t)((uint64_t)pairs * b / ns), e1 = (uint32_t)((uint64_t)pairs * (b + 1) / ns);
+    float d2 = 0.0f, sum = 0.0f;
+    for (uint32_t e = e0; e < e1; e += 128) {
+        const uint32_t k = e + threadIdx.x;
+        float dyf = 0.0f, dyc = 0.0f;
+        if (k < e1) {
+            const uint32_t l = k / a.n, i = k - l * a.n;
+            const float2 c0 = a.c0[(uint64_t)l * a.stride + i];
+            const float w = (float)(st.scale[l] * (a.y[(uint64_t)l * a.Bpad + a.first + i] - st.mean[l]));
+            dyf = sh.scale * (w * c0.x);
+            dyc = sh.scale * (w * c0.y);
+        }
+        sum += dyf + dyc;
+        *(float2*)&s_dy[2 * threadIdx.x] = make_float2(dyf, dyc);
+        __syncthreads();
+#pragma unroll 4
+        for (int i = 0; i < 128; i += 4) {
+            const float4 v = *(const float4*)&s_dy[128 * half + i];
+            d2 += (float)(__bf16)(v.x * w3 * dd);
+            d2 += (float)(__bf16)(v.y * w3 * dd);
+            d2 += (float)(__bf16)(v.z * w3 * dd);
+            d2 += (float)(__bf16)(v.w * w3 * dd);
+        }
+        __syncthreads();
     }
+    sum = sum32(sum);
+    sum += __shfl_xor(sum, 32);
+    s_d2[half][u] = d2;
+    if (u == 0) s_sum[half] = sum;
     __syncthreads();
-    if (u < H) {
+    const bool add = a.first != 0;              // a later chunk of the batch
+    auto put = [&](int i, float v) { row[i] = add ? row[i] + v : v; };
+    if (half == 0) {
+        const float dy = s_sum[0] + s_sum[1];
+        put(off_w3(D) + u, dy * hv);
+        put(off_b2(D) + u, dy * w3 * dd);
+        if (u == 0) put(off_b3(D), dy);
         float e = 0.0f;
-        for (int j = 0; j < H; ++j) e = __builtin_fmaf((float)(__bf16)W2[j * H + u], s_d2[j], e);
+        for (int j = 0; j < H; ++j)
+            e = __builtin_fmaf((float)(__bf16)W2[j * H + u], s_d2[0][j] + s_d2[1][j], e);
         const float d1 = e * (1.0f - s_h1[u] * s_h1[u]);
-        row[off_b1(D) + u] = d1;
-        row[u * D + 0] = 0.0f;
-        row[u * D + 1] = d1 * x1;
-        if (D == 3) row[u * D + 2] = d1 * x2;
+        put(off_b1(D) + u, d1);
+        put(u * D + 0, 0.0f);
+        put(u * D + 1, d1 * x1);
+        if (D == 3) put(u * D + 2, d1 * x2);
     }
     for (int i = threadIdx.x; i < H * H; i += blockDim.x)
-        row[off_W2(D) + i] = s_d2[i / H] * (float)(__bf16)s_h1[i % H];
+        put(off_W2(D) + i, (s_d2[0][i / H] + s_d2[1][i / H]) * (float)(__bf16)s_h1[i % H]);
 }
 
-// Block 0: the start point's row of gpart and the loss (first chunk only; a
-// chain of ~10 us, so it is dispatched first).  Block 1 + b: points of share b
-// of the (row, 64 samples) tasks into row 1 + b (added to it after the
-// batch's first chunk).
+// Blocks 0 .. ns - 1: the start point's rows of gpart and (block 0, first
+// chunk) the loss.  Block ns + b: points of share b of the (row, 64 samples)
+// tasks.  A block's row is added to after the batch's first chunk.
 template <int D>
 __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvKernelArgs c,
-                                                                const bf16x8* abwd, float* gpart,
+                                                                const bf16x8* abwd, float* gpart, uint32_t ns,
                                                                 double* loss, double* loss_hist)
 {
     __shared__ NetShared sh;
@@ -387,11 +449,9 @@ __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvK
     if (threadIdx.x < (unsigned)a.nlev) level_stats(a, (int)threadIdx.x, st);
     __syncthreads();
     float* grow = gpart + (uint64_t)blockIdx.x * kGradRow;
-    const uint32_t nb = gridDim.x - 1, b = blockIdx.x - 1;
-    if (blockIdx.x == 0) {
-        if (a.first) return;
-        start_point_row<D>(a, c, sh, st, grow);
-        if (threadIdx.x == 0) {
+    if (blockIdx.x < ns) {
+        start_point_row<D>(a, c, sh, st, blockIdx.x, ns, grow);
+        if (blockIdx.x == 0 && threadIdx.x == 0 && a.first == 0) {
             double t = 0.0;
             for (int l = 0; l < a.nlev; ++l) {
                 t += sqrt(st.cost[l] * st.var[l]);
@@ -402,6 +462,7 @@ __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvK
         }
         return;
     }
+    const uint32_t nb = gridDim.x - ns, b = blockIdx.x - ns;
     const int lane = threadIdx.x & 63, h = lane >> 5, col = lane & 31;
     const int ut = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     bf16x8 af[4], ab[4];
@@ -641,11 +702,22 @@ static TrainPathsFn pick_paths(int payoff, int M)
     }
 }
 
+// Runs a sample's sums of phi dW are taken in on a level of nf steps: a power
+// of two dividing its generator groups, while 64 samples of one run each make
+// at most 2048 pieces of the batch.
+static uint32_t sum_runs(uint64_t B, uint64_t nf)
+{
+    const uint64_t groups = (nf + 3) / 4, pieces = (B + 63) / 64;
+    uint32_t runs = 1;
+    while (2ull * runs <= groups && groups % (2ull * runs) == 0 && pieces * runs * 2 <= 2048) runs *= 2;
+    return runs;
+}
+
 // The scratch of one step, cut from cv->d_train (256-byte pieces).
 struct TrainScratch {
-    float *x1, *x2, *c, *prod, *x0;
-    float2* pay;
-    double *c0, *y;
+    float *x1, *x2, *c, *phi, *x0;
+    float2 *pay, *c0;
+    double* y;
     float* phi0;
     LevelAcc* rec;
     float *gpart, *grad;
@@ -666,10 +738,10 @@ static TrainScratch cut_scratch(char* base, uint64_t nrows, uint64_t stride, int
     s.x1 = (float*)take(group * pts);
     s.x2 = (float*)take(D == 3 ? group * pts : 0);
     s.c = (float*)take(group * pts);
-    s.prod = (float*)take(pts);
+    s.phi = (float*)take(pts);
     s.x0 = (float*)take(nrows * sizeof(float));
     s.pay = (float2*)take(group * nlev * stride * sizeof(float2));
-    s.c0 = (double*)take(group * nlev * stride * sizeof(double));
+    s.c0 = (float2*)take(group * nlev * stride * sizeof(float2));
     s.y = (double*)take(nlev * Bpad * sizeof(double));
     s.phi0 = (float*)take(sizeof(float));
     s.rec = (LevelAcc*)take(group * nlev * sizeof(LevelAcc));
@@ -686,7 +758,7 @@ struct TrainPlan {
     TrainScratch s;
     uint64_t chunk;      // samples worked off at once
     uint32_t group;      // steps whose paths one launch makes (1 with chunks)
-    int nb;              // backward blocks
+    int nb, ns;          // backward blocks: points, start point
     NetConsts nc;
     TrainPathsFn paths;
 };
@@ -707,6 +779,7 @@ static mlmc_status plan_train(mlmc_cv* cv, const mlmc_model& m, const mlmc_payof
         L.nf = (int)nf;
         L.ngroups = (int)((nf + 3) / 4);
         L.row0 = (uint32_t)nrows;
+        L.runs = sum_runs(B, nf);
         nrows += (nf - 1) + (l ? nf / M - 1 : 0);
     }
     a.nrows = (uint32_t)nrows;
@@ -723,10 +796,17 @@ static mlmc_status plan_train(mlmc_cv* cv, const mlmc_model& m, const mlmc_payof
     t.group = t.chunk < B ? 1u
                           : (uint32_t)std::max<uint64_t>(
                                 1, std::min<uint64_t>({(uint64_t)nsteps, kMaxPoints / pts, (uint64_t)kMaxSteps}));
-    // backward blocks beside the start point's: the device's residency (one
-    // more would wait for another's end), or a task each
-    t.nb = (int)std::min<uint64_t>(nrows * (t.chunk / 64), (uint64_t)ctx->num_cu * kBwdBlocksPerCu - 1);
-    t.s = cut_scratch(nullptr, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + 1, t.group);
+    // backward blocks: the start point's, and beside them what fills the
+    // device's residency (one more would wait for another's end) or a task each
+    // so that both kinds end together: one start block in fifty for
+    // 16384 samples on levels 0..3, one in four on levels 0..1
+    const uint64_t resident = (uint64_t)ctx->num_cu * kBwdBlocksPerCu, tasks = nrows * (t.chunk / 64);
+    const uint64_t pairs = t.chunk * a.nlev;
+    const double sc = kStartPairCost * (double)pairs, share = sc / (sc + kTaskCost * (double)tasks);
+    t.ns = (int)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)(share * (double)resident + 0.5),
+                                                          (pairs + 127) / 128, resident / 2}));
+    t.nb = (int)std::min<uint64_t>(tasks, resident - t.ns);
+    t.s = cut_scratch(nullptr, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + t.ns, t.group);
     if (cv->train_cap < t.s.bytes) {
         // queued launches may still use the old scratch
         MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -736,11 +816,11 @@ static mlmc_status plan_train(mlmc_cv* cv, const mlmc_model& m, const mlmc_payof
         MLMC_HIP(ctx, hipMalloc(&cv->d_train, t.s.bytes));
         cv->train_cap = t.s.bytes;
     }
-    t.s = cut_scratch(cv->d_train, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + 1, t.group);
+    t.s = cut_scratch(cv->d_train, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + t.ns, t.group);
     a.x1 = t.s.x1;
     a.x2 = t.s.x2;
     a.c = t.s.c;
-    a.prod = t.s.prod;
+    a.phi = t.s.phi;
     a.x0 = t.s.x0;
     a.pay = t.s.pay;
     a.c0 = t.s.c0;
@@ -789,7 +869,7 @@ static mlmc_status enqueue_loss_grad(mlmc_cv* cv, TrainPlan& t, uint64_t step, u
         const unsigned grid = (unsigned)std::min<uint64_t>((waves + 3) / 4, (uint64_t)ctx->num_cu * kFwdBlocksPerCu);
         hipLaunchKernelGGL(d3 ? train_forward_kernel<3> : train_forward_kernel<2>, dim3(grid), dim3(256), 0, q, a, c);
         MLMC_HIP(ctx, hipGetLastError());
-        hipLaunchKernelGGL(train_combine_kernel, dim3(blocks), dim3(256), 0, q, a);
+        hipLaunchKernelGGL(train_combine_kernel, dim3(a.stride / 64 * (uint32_t)a.nlev), dim3(256), 0, q, a);
         MLMC_HIP(ctx, hipGetLastError());
     }
     const int tix = timed_begin(ctx, 18, 0.0, 0.0);
@@ -800,12 +880,12 @@ static mlmc_status enqueue_loss_grad(mlmc_cv* cv, TrainPlan& t, uint64_t step, u
             MLMC_HIP(ctx, hipGetLastError());
         }
         const TrainArgs a = for_step(t.a, k);
-        hipLaunchKernelGGL(d3 ? train_backward_kernel<3> : train_backward_kernel<2>, dim3(t.nb + 1), dim3(128), 0, q,
-                           a, c, (const bf16x8*)cv->d_abwd, t.s.gpart, cv->d_loss, hist);
+        hipLaunchKernelGGL(d3 ? train_backward_kernel<3> : train_backward_kernel<2>, dim3(t.nb + t.ns), dim3(128), 0,
+                           q, a, c, (const bf16x8*)cv->d_abwd, t.s.gpart, (uint32_t)t.ns, cv->d_loss, hist);
         MLMC_HIP(ctx, hipGetLastError());
     }
     hipLaunchKernelGGL(train_update_kernel, dim3((cv->np + 31) / 32), dim3(1024), 0, q, (const float*)t.s.gpart,
-                       t.nb + 1, cv->D, t.s.grad, adam ? *adam : AdamArgs{}, adam ? 1 : 0);
+                       t.nb + t.ns, cv->D, t.s.grad, adam ? *adam : AdamArgs{}, adam ? 1 : 0);
     MLMC_HIP(ctx, hipGetLastError());
     timed_end(ctx, tix);
     return MLMC_OK;
