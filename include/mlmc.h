@@ -20,9 +20,10 @@
  *     context's device; all others are host pointers.
  *   - a context is not thread-safe: use one per host thread.  Calls are
  *     enqueued on the context's stream (mlmc_set_stream) and synchronise it
- *     before returning results to host memory, except mlmc_run: it returns
- *     once the device has published the final driver state (with kernel
- *     timing off, work of its own that changes nothing may still be queued;
+ *     before returning results to host memory, except mlmc_level, mlmc_stdmc,
+ *     mlmc_levels_batch, mlmc_rhee_glynn and mlmc_run: they return once the
+ *     device has published their sums or the final driver state (with kernel
+ *     timing off, work of their own that changes nothing may still be queued;
  *     later work on the stream is ordered after it).
  *   - random numbers: Philox4x32-10 keyed by the 64-bit seed; sample s of
  *     level l is a pure function of (seed, l, s), so results do not depend on
@@ -138,8 +139,9 @@ mlmc_status mlmc_set_launch(mlmc_ctx* ctx, int block, int ppt);
 
 /* Kernel timing with HIP events on the context's stream.  Slots:
  *   0..15  level sampler launches at level l (per-level entry points and
- *          per-level driver iterations), 16 persistent all-levels launches
- *          (the batch graph of mlmc_levels_batch; the sampler kernel of the
+ *          per-level driver iterations; with timing on, mlmc_rhee_glynn
+ *          runs a launch per level), 16 persistent all-levels launches
+ *          (plan and sampler of mlmc_levels_batch; the sampler kernel of the
  *          device-planned mlmc_run),
  *   17     driver update kernel (with the plan in the device-planned run),
  *   18     control-variate training steps.
@@ -215,8 +217,8 @@ mlmc_status mlmc_level(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff
  * Scratch: the partial sums go to one group of 64 records (4 KiB) in a static
  * device array, one per device, held until the process ends; that group
  * serves any N <= 2^40 (MLMC_EINVAL beyond, as for mlmc_level).  Every call
- * on a device uses the same array, cleared by a fill kernel at the start of
- * the call: calls that overlap on one device (other streams, other host
+ * on a device uses the same array and clears it at its end (a call after one
+ * that failed, at its start too): calls that overlap on one device (other streams, other host
  * threads) race and must be ordered by the caller.  Kernel launches only (no
  * memset or copy nodes), so the call can be captured into a graph.
  * err (may be NULL): a caller buffer of err_len bytes that receives the
@@ -257,7 +259,7 @@ mlmc_status mlmc_stdmc(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff
 
 /* Persistent all-levels form (fp32 paths).  Samples every (payoff, level)
  * of one MLMC iteration -- levels 0..L, npayoffs payoffs on one model -- in
- * ONE launch of a persistent kernel, replayed from a captured HIP graph:
+ * ONE launch of a persistent kernel, between a plan and a publishing launch:
  * a plan kernel cuts the samples into items of about equal cost (deepest
  * level first), resident blocks take them (block b item b, the rest from
  * atomic counters).
@@ -278,7 +280,7 @@ mlmc_status mlmc_set_persistent_launch(mlmc_ctx* ctx, int block, int ppt, int bl
  * payoffs, M and L at N_l = 2^24 M^-l (at least 1) for every block size
  * {128, 256, 512} x samples per lane {1, 2, 4} x resident blocks per compute
  * unit {2, 4, 8} with at most 2048 threads per compute unit (median of three
- * after a capture run) and sets the fastest with mlmc_set_persistent_launch.
+ * after a first run) and sets the fastest with mlmc_set_persistent_launch.
  * Results do not depend on the shape (see determinism above).  Cached like
  * mlmc_autotune's (cache_path, else $MLMC_TUNE_CACHE) under the machine key
  * and (model kind, scheme, M, L, npayoffs, every payoff kind); a cached

@@ -155,6 +155,7 @@ static float time_shape(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p
     float best[5] = {1e30f, 1e30f, 1e30f, 1e30f, 1e30f};
     for (int rep = 0; rep < 6 && !*st; ++rep) {
         hipEventRecord(a, ctx->stream);
+        ctx->acc_clean = 0;   // the timed launches leave their sums in the records
         *st = enqueue_level(ctx, m, p, l, M, N, 12345, 0, precision, kStreamNormal, 1, ctx->d_acc,
                             nullptr, nullptr, nullptr, true);
         hipEventRecord(b, ctx->stream);
@@ -276,7 +277,7 @@ mlmc_status mlmc_autotune_persistent(mlmc_ctx* ctx, const mlmc_model* model,
             for (int p : ppts) {
                 mlmc_status st = mlmc_set_persistent_launch(ctx, b, p, c);
                 double t[3] = {0, 0, 0};
-                // the first call captures the graph; then the median of three
+                // a first call, then the median of three
                 for (int rep = 0; rep < 4 && !st; ++rep) {
                     const auto t0 = std::chrono::steady_clock::now();
                     st = mlmc_levels_batch(ctx, model, payoffs, npayoffs, M, L, N.data(), nullptr,

@@ -7,6 +7,7 @@
 #include <string>
 
 #include "context.hpp"
+#include "driver.hpp"
 
 namespace mlmc {
 
@@ -150,6 +151,79 @@ hipError_t zero_records(LevelAcc* acc, int n, hipStream_t st)
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(zero_records_kernel, dim3((n + 63) / 64), dim3(64), 0, st, acc, n);
     return hipGetLastError();
+}
+
+// Wave w folds groups w, w + 16, ... (lane: record) and clears them; the sums
+// go to the host's mirror from LDS, consecutive words by consecutive lanes (a
+// store each from lane 0 of every wave took twice as long for 16 groups), and
+// the launch's number follows once every word has reached the host.  One
+// launch takes the place of a fill launch before the sampler, a copy and a
+// stream synchronisation: a call of 1000 samples 20.5 -> 15.5 us.
+__global__ __launch_bounds__(1024) void publish_groups_kernel(LevelAcc* groups, int n, unsigned long long* counts,
+                                                              PublishMirror* m, unsigned long long seq)
+{
+    static_assert(kSpread == 64, "one lane per record of a group");
+    __shared__ double s_sum[kPublishGroups * kNumSums];
+    __shared__ unsigned long long s_bad[kPublishGroups];
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    for (int g = threadIdx.x >> 6; g < n; g += nw) {
+        LevelAcc& r = groups[g * kSpread + lane];
+        double v[kNumSums];
+#pragma unroll
+        for (int k = 0; k < kNumSums; ++k) v[k] = r.sum[k];
+        double c = (double)r.n_nonfinite;
+#pragma unroll
+        for (int k = 0; k < kNumSums; ++k) r.sum[k] = 0.0;
+        r.n_nonfinite = 0;
+#pragma unroll
+        for (int k = 0; k < kNumSums; ++k) v[k] = wave_sum(v[k]);
+        c = wave_sum(c);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < kNumSums; ++k) s_sum[g * kNumSums + k] = v[k];
+            s_bad[g] = (unsigned long long)c;
+        }
+    }
+    unsigned long long drawn = 0;
+    if (counts && threadIdx.x < 16) {
+        for (int k = 0; k < kCountCopies; ++k) {
+            drawn += counts[16 * k + threadIdx.x];
+            counts[16 * k + threadIdx.x] = 0;
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n * kNumSums; i += blockDim.x) ((volatile double*)m->sum)[i] = s_sum[i];
+    if ((int)threadIdx.x < n) ((volatile unsigned long long*)m->n_nonfinite)[threadIdx.x] = s_bad[threadIdx.x];
+    if (counts && threadIdx.x < 16) ((volatile unsigned long long*)m->count)[threadIdx.x] = drawn;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(&m->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+mlmc_status publish_groups(mlmc_ctx* ctx, LevelAcc* groups, int n, unsigned long long* counts, bool sync)
+{
+    const unsigned long long want = ++ctx->pub_seq;
+    hipLaunchKernelGGL(publish_groups_kernel, dim3(1), dim3(64 * (n < 1 ? 1 : n < 16 ? n : 16)), 0, ctx->stream, groups, n,
+                       counts, ctx->h_pub_dev, want);
+    MLMC_HIP(ctx, hipGetLastError());
+    // stamped launches are read back after a synchronisation, as are errors
+    if (sync || !ctx->pending.empty()) {
+        MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        harvest_timing(ctx);
+        if (*(const volatile unsigned long long*)&ctx->h_pub->seq != want)
+            return fail(ctx, MLMC_EDEVICE, "published sums did not reach the host");
+        return MLMC_OK;
+    }
+    MLMC_HIP(ctx, wait_word(ctx->stream, &ctx->h_pub->seq, want));
+    return MLMC_OK;
+}
+
+mlmc_status claim_records(mlmc_ctx* ctx, int n, int* clean)
+{
+    *clean = ctx->acc_clean;
+    ctx->acc_clean = 0;
+    if (*clean < n) MLMC_HIP(ctx, zero_records(ctx->d_acc, n * kSpread, ctx->stream));
+    return MLMC_OK;
 }
 
 template <typename Real>
@@ -370,27 +444,27 @@ mlmc_status enqueue_level(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff&
 }
 
 static mlmc_status finish_level(mlmc_ctx* ctx, const mlmc_model& m, uint64_t N, int l, int M,
-                                int coupled, mlmc_level_result* out)
+                                int coupled, bool sync, int clean, mlmc_level_result* out)
 {
-    MLMC_HIP(ctx, hipMemcpyAsync(ctx->h_acc, ctx->d_acc, sizeof(LevelAcc) * kSpread,
-                                 hipMemcpyDeviceToHost, ctx->stream));
-    MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    harvest_timing(ctx);
-    const LevelAcc r = fold_records(ctx->h_acc, kSpread);
+    const mlmc_status st = publish_groups(ctx, ctx->d_acc, 1, nullptr, sync);
+    if (st) return st;
+    release_records(ctx, 1, clean);
+    const double* sum = ctx->h_pub->sum[0];
+    const unsigned long long nonfinite = ctx->h_pub->n_nonfinite[0];
     if (out) {
-        out->sum_y = r.sum[0];
-        out->sum_y2 = r.sum[1];
-        out->sum_pf = r.sum[2];
-        out->sum_pf2 = r.sum[3];
-        out->sum_pc = r.sum[4];
-        out->sum_pc2 = r.sum[5];
+        out->sum_y = sum[0];
+        out->sum_y2 = sum[1];
+        out->sum_pf = sum[2];
+        out->sum_pf2 = sum[3];
+        out->sum_pc = sum[4];
+        out->sum_pc2 = sum[5];
         out->cost = (double)N * (coupled ? level_cost(m, l, M) : std::pow((double)M, (double)l));
         out->n = N;
-        out->n_nonfinite = r.n_nonfinite;
+        out->n_nonfinite = nonfinite;
     }
-    if (r.n_nonfinite)
+    if (nonfinite)
         return fail(ctx, MLMC_ENONFINITE,
-                    std::to_string(r.n_nonfinite) + " non-finite samples left out of the sums");
+                    std::to_string(nonfinite) + " non-finite samples left out of the sums");
     return MLMC_OK;
 }
 
@@ -417,7 +491,9 @@ mlmc_status mlmc_ctx_create(int device, mlmc_ctx** out)
     hipError_t e = hipSetDevice(device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->own_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMalloc(&ctx->d_acc, sizeof(LevelAcc) * kAccSlots);
-    if (e == hipSuccess) e = hipHostMalloc(&ctx->h_acc, sizeof(LevelAcc) * kAccSlots);
+    if (e == hipSuccess) e = hipHostMalloc(&ctx->h_pub, sizeof(PublishMirror));
+    if (e == hipSuccess) std::memset(ctx->h_pub, 0, sizeof(PublishMirror));
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&ctx->h_pub_dev, ctx->h_pub, 0);
     if (e == hipSuccess) e = hipMalloc(&ctx->d_tmp, sizeof(double) * 4 * MLMC_MAX_LEVELS);
     if (e == hipSuccess) e = hipHostMalloc(&ctx->h_tmp, sizeof(double) * 4 * MLMC_MAX_LEVELS);
     if (e != hipSuccess) {
@@ -442,7 +518,7 @@ mlmc_status mlmc_ctx_destroy(mlmc_ctx* ctx)
     }
     for (auto e : ctx->event_pool) hipEventDestroy(e);
     if (ctx->d_acc) hipFree(ctx->d_acc);
-    if (ctx->h_acc) hipHostFree(ctx->h_acc);
+    if (ctx->h_pub) hipHostFree(ctx->h_pub);
     if (ctx->d_tmp) hipFree(ctx->d_tmp);
     if (ctx->h_tmp) hipHostFree(ctx->h_tmp);
     if (ctx->own_stream) hipStreamDestroy(ctx->own_stream);
@@ -539,11 +615,14 @@ static mlmc_status level_common(mlmc_ctx* ctx, const mlmc_model* model, const ml
     if ((path_offset + N) >> 56) return fail(ctx, MLMC_EINVAL, "path index beyond 2^56");
     ctx->err.clear();
     MLMC_HIP(ctx, hipSetDevice(ctx->device));
-    MLMC_HIP(ctx, zero_records(ctx->d_acc, kSpread, ctx->stream));
+    int clean = 0;
+    st = claim_records(ctx, 1, &clean);
+    if (st) return st;
     st = enqueue_level(ctx, *model, *payoff, l, M, N, seed, path_offset, precision, stream, coupled,
                        ctx->d_acc, d_pf, d_pc, cv, true);
     if (st) return st;
-    return finish_level(ctx, *model, N, l, M, coupled, out);
+    // dumps are read by the caller on any stream: wait for the stream itself
+    return finish_level(ctx, *model, N, l, M, coupled, d_pf != nullptr, clean, out);
 }
 
 mlmc_status mlmc_level(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoff, int l,

@@ -9,6 +9,22 @@
 #include "../../include/mlmc.h"
 #include "level.hpp"
 
+namespace mlmc {
+
+// Folded spread groups of one call, written by the device (publish_groups):
+// six sums and the non-finite count per group, sixteen counts of the
+// randomised estimator, and the launch's number, written last.
+constexpr int kPublishGroups = 64;
+constexpr int kCountCopies = 8;    // of the sixteen counts, added up when read
+struct PublishMirror {
+    double sum[kPublishGroups][kNumSums];
+    unsigned long long n_nonfinite[kPublishGroups];
+    unsigned long long count[16];
+    unsigned long long seq;
+};
+
+}  // namespace mlmc
+
 struct mlmc_ctx {
     int device = 0;
     int num_cu = 256;
@@ -18,9 +34,16 @@ struct mlmc_ctx {
     int launch_block = 0, launch_ppt = 0;   // 0: tuned/default
     int persist_block = 0, persist_ppt = 0, persist_bpc = 0;
     void* persist = nullptr;                // persistent-form buffers (persistent.hip)
-    // Level accumulators: kAccSlots records (payoff x level) + host mirror.
+    // Level accumulators: kAccSlots records (payoff x level).  The first
+    // acc_clean spread groups hold zeros (every call's publish launch folds and
+    // clears the groups it used; 0 while a call runs and after one that failed).
     mlmc::LevelAcc* d_acc = nullptr;
-    mlmc::LevelAcc* h_acc = nullptr;
+    int acc_clean = 0;
+    // published sums in pinned memory, as the host and the device see it, and
+    // the number of the last publish launch (publish_groups)
+    mlmc::PublishMirror* h_pub = nullptr;
+    mlmc::PublishMirror* h_pub_dev = nullptr;
+    uint64_t pub_seq = 0;
     // Driver state on the device and its pinned host mirror (driver.hip).
     void* d_drv = nullptr;
     void* h_drv = nullptr;        // pinned host mirror of the driver state
@@ -56,8 +79,7 @@ struct mlmc_ctx {
 namespace mlmc {
 
 // Level records: 16 spread groups (a call's level, or every level of a
-// randomised single-term estimate); also the training records and the host
-// copy of a persistent batch.
+// randomised single-term estimate).
 constexpr int kAccSlots = 16 * mlmc::kSpread;
 
 // Record an error message and return the status.
@@ -106,6 +128,15 @@ mlmc_status enqueue_level(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff&
                           const mlmc_cv* cv, bool spread = false);
 // Zero `n` records with a fill kernel (safe inside graph capture).
 hipError_t zero_records(LevelAcc* acc, int n, hipStream_t st);
+// Zeros in the first n groups of the context's level records, by a fill launch
+// unless the last call left them so; release_records once the caller's sums
+// are published.
+// Enqueue the launch that folds `n` spread groups into the context's mirror
+// and clears them (and, given counts, adds up and clears their copies), then
+// wait until the host sees it; with `sync`, for the stream instead.
+mlmc_status claim_records(mlmc_ctx* ctx, int n, int* clean);
+inline void release_records(mlmc_ctx* ctx, int n, int clean) { ctx->acc_clean = clean > n ? clean : n; }
+mlmc_status publish_groups(mlmc_ctx* ctx, LevelAcc* groups, int n, unsigned long long* counts, bool sync);
 
 // Bracket a launch with timing events when timing is on (no-op otherwise).
 // timed_begin returns an index for timed_end, or -1.
@@ -124,6 +155,14 @@ void harvest_ready(mlmc_ctx* ctx);
 // Release the driver state and the persistent batch buffers (idempotent).
 void free_driver(mlmc_ctx* ctx);
 void free_persistent(mlmc_ctx* ctx);
+
+// The randomised estimator's form in three launches after its draws
+// (persistent.hip): kCountCopies zeroed copies of sixteen device counts to draw
+// into, then the
+// samples of every level by its count, published with the counts.
+mlmc_status level_counts(mlmc_ctx* ctx, unsigned long long** counts);
+mlmc_status run_counts(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int L, int M, uint64_t seed,
+                       unsigned long long* counts);
 
 // Tuned shape of the level sampler for this problem, if the tuner ran.
 bool tuned_shape(const mlmc_ctx* ctx, const mlmc_model& m, int payoff, int precision, int M, int l,

@@ -42,15 +42,15 @@ __global__ __launch_bounds__(512) void driver_update_kernel(DriverState* st, Dri
     driver_update_block(st, mirror, s, spread, has_init ? &c : nullptr);
 }
 
-// Wait until the host mirror shows update number `want`.  Spinning on the
-// mirror saves the completion signal and wake-up of a stream synchronisation;
-// the stream is polled as well, so a failed launch ends the wait with its
-// error.
-hipError_t wait_update(hipStream_t stream, const DriverState* h, unsigned long long want)
+// Spinning on the word saves the completion signal and wake-up of a stream
+// synchronisation; the stream is polled as well, so a failed launch ends the
+// wait with its error.
+hipError_t wait_word(hipStream_t stream, const unsigned long long* word, unsigned long long want)
 {
     auto next_poll = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    const volatile unsigned long long* w = word;
     for (;;) {
-        if (mirror_updates(h) >= want) {
+        if (*w >= want) {
             std::atomic_thread_fence(std::memory_order_acquire);
             return hipSuccess;
         }
@@ -60,11 +60,17 @@ hipError_t wait_update(hipStream_t stream, const DriverState* h, unsigned long l
             const hipError_t e = hipStreamQuery(stream);
             if (e == hipSuccess) {
                 std::atomic_thread_fence(std::memory_order_acquire);
-                return mirror_updates(h) >= want ? hipSuccess : hipErrorUnknown;
+                return *w >= want ? hipSuccess : hipErrorUnknown;
             }
             if (e != hipErrorNotReady) return e;
         }
     }
+}
+
+// The mirror's word is 2 x (update count) + done (mirror_updates).
+hipError_t wait_update(hipStream_t stream, const DriverState* h, unsigned long long want)
+{
+    return wait_word(stream, &h->seq, 2 * want);
 }
 
 hipError_t launch_driver_update(DriverState* st, DriverState* mirror, LevelAcc* spread,

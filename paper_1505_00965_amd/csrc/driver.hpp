@@ -51,7 +51,9 @@ struct DriverInit {
 hipError_t launch_driver_update(DriverState* st, DriverState* mirror, LevelAcc* spread,
                                 hipStream_t stream, hipEvent_t start = nullptr,
                                 hipEvent_t stop = nullptr, const DriverInit* init = nullptr);
-// Wait until the host mirror shows update number `want` (driver.hip).
+// Wait until a word of pinned memory, written by the device, is at least
+// `want` (driver.hip), and so for the host mirror's update number `want`.
+hipError_t wait_word(hipStream_t stream, const unsigned long long* word, unsigned long long want);
 hipError_t wait_update(hipStream_t stream, const DriverState* h, unsigned long long want);
 
 // Host side: the update count and the done flag as the mirror's last

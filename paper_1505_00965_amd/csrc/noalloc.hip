@@ -8,9 +8,10 @@
 // holds its own copy for the life of the process.  Host code never passes the
 // array's name to a kernel: on a device's first call its address is taken
 // with hipGetSymbolAddress (with that device current) and kept per device.
-// Every call on a device uses that one array: a fill kernel clears it, the
-// level kernels add into it, and a one-thread kernel folds it into the
-// caller's device result, all on the caller's stream.  Calls that overlap on
+// Every call on a device uses that one array: the level kernels add into it,
+// and a one-wave kernel folds it into the caller's device result and clears it
+// for the next call (a fill kernel comes first after a call that failed), all
+// on the caller's stream.  Calls that overlap on
 // one device (other streams, other host threads) race on the array.
 #include <hip/hip_runtime.h>
 
@@ -34,6 +35,7 @@ constexpr int kMaxDevices = 64;
 
 struct DeviceScratch {
     std::atomic<int> ready{0};   // 1: ptr and num_cu are set
+    std::atomic<int> dirty{0};   // 1: a call's fold was not enqueued
     LevelAcc* ptr = nullptr;     // this device's copy of `scratch`
     int num_cu = 0;
 };
@@ -73,22 +75,34 @@ hipError_t scratch_for(int dev, DeviceScratch** out)
 
 }  // namespace
 
-// Sum of the group in record order (the order mlmc_level folds in), written
-// as the caller's result.
-__global__ void fold_to_result_kernel(const LevelAcc* group, mlmc_level_result* out, uint64_t N,
-                                      double cost)
+// Sum of the group, written as the caller's result, and zeros in its place
+// (lane: record; one thread reading 64 records in turn took 8 us, the
+// wave 4.7).
+__global__ __launch_bounds__(64) void fold_to_result_kernel(LevelAcc* group, mlmc_level_result* out, uint64_t N,
+                                                            double cost)
 {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    const LevelAcc r = fold_records(group, kScratchRecords);
-    out->sum_y = r.sum[0];
-    out->sum_y2 = r.sum[1];
-    out->sum_pf = r.sum[2];
-    out->sum_pf2 = r.sum[3];
-    out->sum_pc = r.sum[4];
-    out->sum_pc2 = r.sum[5];
+    static_assert(kScratchRecords == 64, "one lane per record");
+    LevelAcc& r = group[threadIdx.x];
+    double v[kNumSums];
+#pragma unroll
+    for (int k = 0; k < kNumSums; ++k) v[k] = r.sum[k];
+    double c = (double)r.n_nonfinite;
+#pragma unroll
+    for (int k = 0; k < kNumSums; ++k) r.sum[k] = 0.0;
+    r.n_nonfinite = 0;
+#pragma unroll
+    for (int k = 0; k < kNumSums; ++k) v[k] = wave_sum(v[k]);
+    c = wave_sum(c);
+    if (threadIdx.x != 0) return;
+    out->sum_y = v[0];
+    out->sum_y2 = v[1];
+    out->sum_pf = v[2];
+    out->sum_pf2 = v[3];
+    out->sum_pc = v[4];
+    out->sum_pc2 = v[5];
     out->cost = cost;
     out->n = N;
-    out->n_nonfinite = r.n_nonfinite;
+    out->n_nonfinite = (unsigned long long)c;
 }
 
 }  // namespace mlmc
@@ -132,7 +146,7 @@ extern "C" mlmc_status mlmc_level_noalloc(const mlmc_model* model, const mlmc_pa
     }
     const hipStream_t st = static_cast<hipStream_t>(hip_stream);
     LevelAcc* group = ds->ptr;
-    e = zero_records(group, kScratchRecords, st);
+    e = ds->dirty.exchange(1) ? zero_records(group, kScratchRecords, st) : hipSuccess;
     const mlmc_model& m = *model;
     const mlmc_payoff& p = *payoff;
     int nf = 1;
@@ -156,5 +170,6 @@ extern "C" mlmc_status mlmc_level_noalloc(const mlmc_model* model, const mlmc_pa
         put_err(err, err_len, hipGetErrorString(e));
         return MLMC_EDEVICE;
     }
+    ds->dirty.store(0);
     return MLMC_OK;
 }

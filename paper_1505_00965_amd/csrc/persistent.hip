@@ -1,5 +1,5 @@
 // Persistent all-levels sampler: every level (and payoff) of one MLMC
-// iteration in a single launch, captured once in a HIP graph.
+// iteration in a single launch.
 //
 // Levels are independent (Sec. 5, after eq. (eq:Yldef)), so one iteration's
 // work is a set of (payoff, level, sample range) items.  Their costs differ by
@@ -10,11 +10,11 @@
 // (block b item b first, then from its group's counter) until none are left, so
 // cheap levels fill in around the long deep-level items.  GBM levels with too few paths to fill the
 // device run each path on several lanes (process_split), with the per-level
-// launch's rule on the level's count.  Every parameter the launches read lives in
-// device memory and is rewritten between launches (by the driver kernel or
-// by host copies): a batch of levels is a graph captured once and replayed,
-// and the adaptive driver's run is two plain launches per iteration (the
-// sampler, then one block that absorbs the batch and plans the next).
+// launch's rule on the level's count.  The problem's parameters live in
+// device memory and are uploaded when they change; the sampler reads the plan
+// that the launch before it wrote: a batch is plan, sampler and publication,
+// the adaptive driver's run two launches per iteration (the sampler, then one
+// block that absorbs the batch and plans the next).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -30,9 +30,30 @@
 
 namespace mlmc {
 
-__global__ __launch_bounds__(256) void plan_kernel(const BatchDesc* d)
+// Outstanding samples and first indices per (slot, level) of one batch.
+struct BatchRequest {
+    double dN[kPairs], offset[kPairs];
+};
+
+__global__ __launch_bounds__(64) void plan_kernel(const BatchDesc* d, BatchRequest q)
 {
-    plan_body(plan_args(d), d->dN, d->offset);
+    __shared__ BatchRequest s;
+    s.dN[threadIdx.x] = q.dN[threadIdx.x];
+    s.offset[threadIdx.x] = q.offset[threadIdx.x];
+    __syncthreads();
+    plan_body(plan_args(d), s.dN, s.offset);
+}
+
+// The plan of a randomised estimate: the drawn samples per level, from 0.
+__global__ __launch_bounds__(64) void plan_counts_kernel(const BatchDesc* d, const unsigned long long* counts)
+{
+    __shared__ BatchRequest s;
+    unsigned long long n = 0;
+    for (int k = 0; k < kCountCopies && threadIdx.x < kMaxLevels; ++k) n += counts[k * kMaxLevels + threadIdx.x];
+    s.dN[threadIdx.x] = (double)n;
+    s.offset[threadIdx.x] = 0.0;
+    __syncthreads();
+    plan_body(plan_args(d), s.dN, s.offset);
 }
 
 // The adaptive run's first kernel when its spread groups are not known to
@@ -134,27 +155,6 @@ __global__ __launch_bounds__(512) void driver_update_plan_kernel(DriverState* st
     clear_groups(spread, L0);
 }
 
-// Fold each spread group (kSpread records) into one record, group g by
-// block g, in record order; clears the groups for the next replay.
-__global__ __launch_bounds__(64) void fold_groups_kernel(LevelAcc* groups, LevelAcc* out)
-{
-    static_assert(kSpread == 64, "one lane per record of a group");
-    LevelAcc& r = groups[blockIdx.x * kSpread + threadIdx.x];
-    double v[kNumSums];
-#pragma unroll
-    for (int k = 0; k < kNumSums; ++k) v[k] = wave_sum(r.sum[k]);
-    const double c = wave_sum((double)r.n_nonfinite);
-#pragma unroll
-    for (int k = 0; k < kNumSums; ++k) r.sum[k] = 0.0;
-    r.n_nonfinite = 0;
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < kNumSums; ++k) out[blockIdx.x].sum[k] = v[k];
-        out[blockIdx.x].n_nonfinite = (unsigned long long)c;
-        out[blockIdx.x].pad = 0;
-    }
-}
-
 extern template PersistentFn pick_persistent_variant<kGBM>(int, int, int, bool);
 extern template PersistentFn pick_persistent_variant<kGBMMil>(int, int, int, bool);
 extern template PersistentFn pick_persistent_variant<kHeston>(int, int, int, bool);
@@ -171,17 +171,16 @@ static PersistentFn pick_persistent(int variant, int M, int ppt, int payoff, boo
 
 // Device buffers of the persistent form, owned by the context.
 struct PersistentBufs {
+    char* d_all = nullptr;            // the allocation that holds the device buffers
     BatchDesc* d_desc = nullptr;
     BatchDesc* h_desc = nullptr;
     PlanTable* d_plan = nullptr;
     unsigned* d_counters = nullptr;   // head
     LevelAcc* d_acc = nullptr;        // batch spread groups [kMaxSlots][kMaxLevels][kSpread]
-    LevelAcc* d_rec = nullptr;        // their folds [kMaxSlots][kMaxLevels]
+    bool acc_clean = false;           // they hold zeros (publish_groups clears what it folds)
     unsigned* d_split = nullptr;      // lanes per path [kMaxSlots][kMaxLevels]
-    double* d_req = nullptr;          // dN[kMaxSlots][kMaxLevels], offset[...]
-    double* h_req = nullptr;
-    hipGraphExec_t graph = nullptr;   // cached batch graph
-    int graph_key[6] = {-1, -1, -1, -1, -1, -1};
+    unsigned long long* d_counts = nullptr;   // level draws of a randomised estimate
+    bool counts_clean = false;        // they hold zeros
     BatchDesc last_desc;              // the bytes of the last descriptor upload
     // 0: unknown; 1: the device descriptor holds last_desc
     int desc_state = 0;
@@ -211,19 +210,32 @@ static mlmc_status ensure_bufs(mlmc_ctx* ctx)
     auto* b = new (std::nothrow) PersistentBufs();
     if (!b) return fail(ctx, MLMC_ENOMEM, "host allocation failed");
     ctx->persist = b;
-    hipError_t e = hipMalloc(&b->d_desc, sizeof(BatchDesc));
+    // one device allocation, cut into 256-byte pieces
+    size_t at = 0;
+    auto piece = [&](size_t bytes) {
+        const size_t p = at;
+        at += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    const size_t desc = piece(sizeof(BatchDesc)), plan = piece(sizeof(PlanTable));
+    const size_t counters = piece(sizeof(unsigned) * 2 * kHeads * kHeadStride);
+    const size_t split = piece(sizeof(unsigned) * kMaxSlots * kMaxLevels);
+    const size_t counts = piece(sizeof(unsigned long long) * kCountCopies * kMaxLevels);
+    const size_t acc = piece(sizeof(LevelAcc) * kMaxSlots * kMaxLevels * kSpread);
+    hipError_t e = hipMalloc(&b->d_all, at);
     if (e == hipSuccess) e = hipHostMalloc(&b->h_desc, sizeof(BatchDesc));
-    if (e == hipSuccess) e = hipMalloc(&b->d_plan, sizeof(PlanTable));
-    if (e == hipSuccess) e = hipMalloc(&b->d_counters, sizeof(unsigned) * 2 * kHeads * kHeadStride);
-    // the dispensers start at zero (a driver run's plans leave its own there)
-    if (e == hipSuccess) e = hipMemsetAsync(b->d_counters, 0, sizeof(unsigned) * 2 * kHeads * kHeadStride, ctx->stream);
-    if (e == hipSuccess)
-        e = hipMalloc(&b->d_acc, sizeof(LevelAcc) * kMaxSlots * kMaxLevels * kSpread);
-    if (e == hipSuccess) e = hipMalloc(&b->d_rec, sizeof(LevelAcc) * kMaxSlots * kMaxLevels);
-    if (e == hipSuccess) e = hipMalloc(&b->d_split, sizeof(unsigned) * kMaxSlots * kMaxLevels);
-    if (e == hipSuccess) e = hipMalloc(&b->d_req, sizeof(double) * 2 * kMaxSlots * kMaxLevels);
-    if (e == hipSuccess)
-        e = hipHostMalloc(&b->h_req, sizeof(double) * 2 * kMaxSlots * kMaxLevels);
+    // the dispensers start at zero (a driver run's plans leave its own there),
+    // and so do the groups and the counts
+    if (e == hipSuccess) e = hipMemsetAsync(b->d_all, 0, at, ctx->stream);
+    if (e == hipSuccess) {
+        b->d_desc = (BatchDesc*)(b->d_all + desc);
+        b->d_plan = (PlanTable*)(b->d_all + plan);
+        b->d_counters = (unsigned*)(b->d_all + counters);
+        b->d_split = (unsigned*)(b->d_all + split);
+        b->d_counts = (unsigned long long*)(b->d_all + counts);
+        b->d_acc = (LevelAcc*)(b->d_all + acc);
+        b->acc_clean = b->counts_clean = true;
+    }
     if (e != hipSuccess) {
         // An incomplete set is released so that the next call starts over.
         free_persistent(ctx);
@@ -238,16 +250,8 @@ void free_persistent(mlmc_ctx* ctx)
 {
     auto* b = bufs_of(ctx);
     if (!b) return;
-    if (b->graph) hipGraphExecDestroy(b->graph);
-    if (b->d_desc) hipFree(b->d_desc);
+    if (b->d_all) hipFree(b->d_all);
     if (b->h_desc) hipHostFree(b->h_desc);
-    if (b->d_plan) hipFree(b->d_plan);
-    if (b->d_counters) hipFree(b->d_counters);
-    if (b->d_acc) hipFree(b->d_acc);
-    if (b->d_rec) hipFree(b->d_rec);
-    if (b->d_split) hipFree(b->d_split);
-    if (b->d_req) hipFree(b->d_req);
-    if (b->h_req) hipHostFree(b->h_req);
     delete b;
     ctx->persist = nullptr;
 }
@@ -256,8 +260,7 @@ void free_persistent(mlmc_ctx* ctx)
 // A driver run passes the fresh state's configuration and its own
 // dispensers (`head`); a batch passes nullptr and the batch's.
 static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const mlmc_model& m, const mlmc_payoff* p,
-                      int np, int L, int M, uint64_t seed, const double* dN, const double* off,
-                      LevelAcc* acc, unsigned* head, const DriverInit* init)
+                      int np, int L, int M, LevelAcc* acc, unsigned* head, const DriverInit* init)
 {
     auto* b = bufs_of(ctx);
     const PersistentShape s = persistent_shape(ctx);
@@ -270,9 +273,6 @@ static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const mlmc_model& m, const ml
         h->payoff_kind[k] = p[k].kind;
         for (int l = 0; l <= L; ++l) h->params[k][l] = make_step_params<float>(m, p[k], l, M);
     }
-    h->seed = seed;
-    h->dN = dN;
-    h->offset = off;
     h->acc = acc;
     h->plan = b->d_plan;
     h->head = head;
@@ -303,41 +303,6 @@ static mlmc_status upload_desc(mlmc_ctx* ctx, PersistentBufs* b, bool* uploaded 
     return MLMC_OK;
 }
 
-// Capture zero -> plan -> persistent -> fold into a graph (payoff: the kind
-// of every slot, or kAnyPayoff).
-static mlmc_status capture(mlmc_ctx* ctx, int model, int M, int payoff, hipGraphExec_t* out)
-{
-    auto* b = bufs_of(ctx);
-    const PersistentShape s = persistent_shape(ctx);
-    hipStream_t cs;
-    MLMC_HIP(ctx, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) e = zero_records(b->d_acc, kMaxSlots * kMaxLevels * kSpread, cs);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, cs, (const BatchDesc*)b->d_desc);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
-        // the seed from the descriptor (uploaded per batch), the plan from plan_kernel
-        hipLaunchKernelGGL(pick_persistent(model, M, s.ppt, payoff), dim3(ctx->num_cu * s.blocks_per_cu),
-                           dim3(s.block), 0, cs, (const BatchDesc*)b->d_desc, (uint64_t)0, 0u);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(fold_groups_kernel, dim3(kMaxSlots * kMaxLevels), dim3(kSpread), 0, cs,
-                           b->d_acc, b->d_rec);
-        e = hipGetLastError();
-    }
-    hipError_t e2 = hipStreamEndCapture(cs, &g);
-    if (e == hipSuccess) e = e2;
-    if (e == hipSuccess) e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
-    if (g) hipGraphDestroy(g);
-    hipStreamDestroy(cs);
-    if (e != hipSuccess) return hip_fail(ctx, e, "persistent graph capture");
-    return MLMC_OK;
-}
-
 // mlmc_run with persistent = 1: the start kernel (fresh state, pilot plan),
 // then per driver iteration the all-levels sampler and the update-and-plan
 // block, as plain launches on the context's stream.
@@ -363,8 +328,8 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
     // the seed goes in with each launch: runs of one problem share the
     // descriptor's bytes and upload it once.  Driver runs have dispensers
     // of their own, which their plans leave at zero.
-    fill_desc(ctx, b->h_desc, m, &p, 1, o.L_max, o.M, 0, d_st->dN, d_st->n, ctx->d_drv_spread,
-              b->d_counters + kHeads * kHeadStride, &init);
+    fill_desc(ctx, b->h_desc, m, &p, 1, o.L_max, o.M, ctx->d_drv_spread, b->d_counters + kHeads * kHeadStride,
+              &init);
     size_t lds = 0;
     if (o.cv) {
         int max_nf = 1;
@@ -408,9 +373,8 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
             hipEvent_t t0, t1;
             timed_kernel(ctx, 16, 0.0, 0.0, &t0, &t1);
             if (first_tix < 0 && t0) first_tix = (int)ctx->pending.size() - 1;
-            const unsigned flags = kSeedArg;
-            if (t0) hipExtLaunchKernelGGL(sampler, grid, block, lds, ctx->stream, t0, t1, 0, d, o.seed, flags);
-            else hipLaunchKernelGGL(sampler, grid, block, lds, ctx->stream, d, o.seed, flags);
+            if (t0) hipExtLaunchKernelGGL(sampler, grid, block, lds, ctx->stream, t0, t1, 0, d, o.seed);
+            else hipLaunchKernelGGL(sampler, grid, block, lds, ctx->stream, d, o.seed);
             hipError_t e = hipGetLastError();
             if (e == hipSuccess) {
                 timed_kernel(ctx, 17, 0.0, 0.0, &t0, &t1);
@@ -454,6 +418,65 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
     return MLMC_OK;
 }
 
+// Plan and sample one batch, then publish its groups: three launches (four
+// with a fill launch after a call that failed) on the context's stream, the
+// seed and the request in their arguments, so batches of one problem upload
+// nothing.  counts: device counts of slot 0's samples per level instead of
+// the request (then published and cleared).
+static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff* p, int np, int L, int M,
+                             uint64_t seed, const BatchRequest* req, unsigned long long* counts, double fine,
+                             double coarse)
+{
+    auto* b = bufs_of(ctx);
+    // a batch rewrites the plan table: a driver run's prepared start is gone
+    ctx->drv_pilot_ready = false;
+    fill_desc(ctx, b->h_desc, m, p, np, L, M, b->d_acc, b->d_counters, nullptr);
+    mlmc_status st = upload_desc(ctx, b);
+    if (st) return st;
+    const PersistentShape s = persistent_shape(ctx);
+    // one payoff kind in every slot: the kernel holds that payoff's code only
+    int payoff = p[0].kind;
+    for (int k = 1; k < np; ++k)
+        if (p[k].kind != payoff) payoff = kAnyPayoff;
+    if (!b->acc_clean) MLMC_HIP(ctx, zero_records(b->d_acc, kMaxSlots * kMaxLevels * kSpread, ctx->stream));
+    b->acc_clean = false;
+    const BatchDesc* d = b->d_desc;
+    const int tix = timed_begin(ctx, 16, fine, coarse);
+    if (counts) hipLaunchKernelGGL(plan_counts_kernel, dim3(1), dim3(64), 0, ctx->stream, d, counts);
+    else hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64), 0, ctx->stream, d, *req);
+    MLMC_HIP(ctx, hipGetLastError());
+    hipLaunchKernelGGL(pick_persistent(sampler_variant(m), M, s.ppt, payoff), dim3(ctx->num_cu * s.blocks_per_cu),
+                       dim3(s.block), 0, ctx->stream, d, seed);
+    MLMC_HIP(ctx, hipGetLastError());
+    timed_end(ctx, tix);
+    static_assert(kMaxSlots * kMaxLevels <= kPublishGroups, "the mirror holds every pair");
+    // the groups past the last slot's last level were not touched
+    st = publish_groups(ctx, b->d_acc, (np - 1) * kMaxLevels + L + 1, counts, false);
+    if (!st) b->acc_clean = true;
+    return st;
+}
+
+mlmc_status run_counts(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int L, int M, uint64_t seed,
+                       unsigned long long* counts)
+{
+    const mlmc_status st = run_batch(ctx, m, &p, 1, L, M, seed, nullptr, counts, 0.0, 0.0);
+    if (!st) bufs_of(ctx)->counts_clean = true;
+    return st;
+}
+
+mlmc_status level_counts(mlmc_ctx* ctx, unsigned long long** counts)
+{
+    const mlmc_status st = ensure_bufs(ctx);
+    if (st) return st;
+    auto* b = bufs_of(ctx);
+    if (!b->counts_clean)
+        MLMC_HIP(ctx, hipMemsetAsync(b->d_counts, 0, sizeof(unsigned long long) * kCountCopies * kMaxLevels,
+                                     ctx->stream));
+    b->counts_clean = false;
+    *counts = b->d_counts;
+    return MLMC_OK;
+}
+
 }  // namespace mlmc
 
 using namespace mlmc;
@@ -474,14 +497,6 @@ mlmc_status mlmc_set_persistent_launch(mlmc_ctx* ctx, int block, int ppt, int bl
         ctx->persist_block = block;
         ctx->persist_ppt = ppt;
         ctx->persist_bpc = blocks_per_cu;
-    }
-    if (auto* b = bufs_of(ctx)) {
-        // a run may have returned with its last (empty) launch queued
-        MLMC_HIP(ctx, hipSetDevice(ctx->device));
-        MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        if (b->graph) hipGraphExecDestroy(b->graph);
-        b->graph = nullptr;
-        b->graph_key[0] = -1;
     }
     return MLMC_OK;
 }
@@ -509,68 +524,36 @@ mlmc_status mlmc_levels_batch(mlmc_ctx* ctx, const mlmc_model* model, const mlmc
     MLMC_HIP(ctx, hipSetDevice(ctx->device));
     st = ensure_bufs(ctx);
     if (st) return st;
-    auto* b = bufs_of(ctx);
-    // request: dN and offsets per (slot, level)
-    std::memset(b->h_req, 0, sizeof(double) * 2 * kMaxSlots * kMaxLevels);
-    for (int k = 0; k < npayoffs; ++k)
-        for (int l = 0; l <= L; ++l) {
-            b->h_req[k * kMaxLevels + l] = (double)N[k * (L + 1) + l];
-            b->h_req[kMaxSlots * kMaxLevels + k * kMaxLevels + l] =
-                offsets ? (double)offsets[k * (L + 1) + l] : 0.0;
-        }
-    // a batch rewrites the plan table: a driver run's prepared start is gone
-    ctx->drv_pilot_ready = false;
-    fill_desc(ctx, b->h_desc, *model, payoffs, npayoffs, L, M, seed, b->d_req,
-              b->d_req + kMaxSlots * kMaxLevels, b->d_acc, b->d_counters, nullptr);
-    MLMC_HIP(ctx, hipMemcpyAsync(b->d_req, b->h_req, sizeof(double) * 2 * kMaxSlots * kMaxLevels,
-                                 hipMemcpyHostToDevice, ctx->stream));
-    st = upload_desc(ctx, b);
-    if (st) return st;
-    const PersistentShape s = persistent_shape(ctx);
-    // one payoff kind in every slot: the kernel holds that payoff's code only
-    int payoff = payoffs[0].kind;
-    for (int k = 1; k < npayoffs; ++k)
-        if (payoffs[k].kind != payoff) payoff = kAnyPayoff;
-    const int key[6] = {sampler_variant(*model), M, s.block, s.ppt, s.blocks_per_cu, payoff};
-    if (!b->graph || std::memcmp(key, b->graph_key, sizeof(key)) != 0) {
-        if (b->graph) hipGraphExecDestroy(b->graph);
-        b->graph = nullptr;
-        st = capture(ctx, sampler_variant(*model), M, payoff, &b->graph);
-        if (st) return st;
-        std::memcpy(b->graph_key, key, sizeof(key));
-    }
+    BatchRequest req;
+    std::memset(&req, 0, sizeof(req));
     double fine = 0.0, coarse = 0.0;
     for (int k = 0; k < npayoffs; ++k)
         for (int l = 0; l <= L; ++l) {
+            const uint64_t n = N[k * (L + 1) + l];
+            req.dN[k * kMaxLevels + l] = (double)n;
+            req.offset[k * kMaxLevels + l] = offsets ? (double)offsets[k * (L + 1) + l] : 0.0;
             const double nf = std::pow((double)M, (double)l);
-            fine += (double)N[k * (L + 1) + l] * nf;
-            coarse += l ? (double)N[k * (L + 1) + l] * nf / M : 0.0;
+            fine += (double)n * nf;
+            coarse += l ? (double)n * nf / M : 0.0;
         }
-    const int tix = timed_begin(ctx, 16, fine, coarse);
-    MLMC_HIP(ctx, hipGraphLaunch(b->graph, ctx->stream));
-    timed_end(ctx, tix);
-    static_assert(kMaxSlots * kMaxLevels <= kAccSlots, "the folded records fit the host copy");
-    LevelAcc* h_acc = ctx->h_acc;
-    MLMC_HIP(ctx, hipMemcpyAsync(h_acc, b->d_rec, sizeof(LevelAcc) * kMaxSlots * kMaxLevels,
-                                 hipMemcpyDeviceToHost, ctx->stream));
-    MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    harvest_timing(ctx);
+    st = run_batch(ctx, *model, payoffs, npayoffs, L, M, seed, &req, nullptr, fine, coarse);
+    if (st) return st;
     uint64_t nonfinite = 0;
     for (int k = 0; k < npayoffs; ++k)
         for (int l = 0; l <= L; ++l) {
-            const LevelAcc& r = h_acc[k * kMaxLevels + l];
+            const double* sum = ctx->h_pub->sum[k * kMaxLevels + l];
             mlmc_level_result& o = out[k * (L + 1) + l];
-            o.sum_y = r.sum[0];
-            o.sum_y2 = r.sum[1];
-            o.sum_pf = r.sum[2];
-            o.sum_pf2 = r.sum[3];
-            o.sum_pc = r.sum[4];
-            o.sum_pc2 = r.sum[5];
+            o.sum_y = sum[0];
+            o.sum_y2 = sum[1];
+            o.sum_pf = sum[2];
+            o.sum_pf2 = sum[3];
+            o.sum_pc = sum[4];
+            o.sum_pc2 = sum[5];
             const double nf = std::pow((double)M, (double)l);
             o.n = N[k * (L + 1) + l];
             o.cost = (double)o.n * (l ? nf + nf / M : 1.0);
-            o.n_nonfinite = r.n_nonfinite;
-            nonfinite += r.n_nonfinite;
+            o.n_nonfinite = ctx->h_pub->n_nonfinite[k * kMaxLevels + l];
+            nonfinite += o.n_nonfinite;
         }
     if (nonfinite) return fail(ctx, MLMC_ENONFINITE, "non-finite samples left out of the sums");
     return MLMC_OK;

@@ -13,13 +13,15 @@ namespace mlmc {
 
 constexpr int kMaxSlots = 4;          // payoffs per batch
 constexpr int kPairs = kMaxSlots * kMaxLevels;
-// Items per resident block the plan aims at: four, or as many as hold
-// kItemSteps path steps each, up to sixteen; a pair is cut into at most 256
-// times as many.  Four-payoff batches of 3e9 steps took 2.08 ms with four items per
+// Items per resident block the plan aims at: four, fewer (down to one) where
+// they would hold less than kSmallItem path steps each, more (up to sixteen)
+// where four hold more than kItemSteps; a pair is cut into at most 256 times
+// as many, or 1024.  An item's decode, parameters and block reduction cost
+// ~3 us: four-payoff batches of 3e9 steps took 2.08 ms with four items per
 // block and 1.91 with sixteen; an estimate's launches (1.4e8 steps, 5 pairs)
-// 353 us in all with four and 375 with eight: an item's decode, parameters
-// and block reduction cost ~3 us.
-constexpr double kItemsMin = 4.0, kItemsMax = 16.0, kItemSteps = 65536.0;
+// 353 us in all with four and 375 with eight; a randomised estimate of 8e6
+// steps 50 us with four and 44 with one, a batch of 3e6 steps 67 and 63.
+constexpr double kItems = 4.0, kItemsMost = 16.0, kItemSteps = 65536.0, kSmallItem = 8192.0;
 // Dispensers: blocks and items are dealt to groups by their number modulo
 // kHeads, and the items past the first per block come from the group's own
 // counter, a cache line each.  One counter for all serves a block per ~10 ns,
@@ -51,17 +53,13 @@ struct PlanTable {
 };
 static_assert(sizeof(PlanTable) % 8 == 0, "copied in 8-byte words");
 
-// Device-resident batch description (rewritten before each launch).
+// Device-resident batch description (uploaded when it changes; the seed goes
+// with each launch).
 struct BatchDesc {
     int nslots, L, M;
     int dim;                          // Brownian dimension: 1 (GBM), 2 (Heston)
     int payoff_kind[kMaxSlots];
     StepParams<float> params[kMaxSlots][kMaxLevels];
-    uint64_t seed;
-    // outstanding samples and their first index, per (slot, level); for the
-    // driver these alias DriverState::dN / n (slot 0 only)
-    const double* dN;
-    const double* offset;
     LevelAcc* acc;                    // spread groups [slot][level][kSpread]
     PlanTable* plan;                  // written by the plan, read by the sampler
     unsigned* head;                   // dispensers of the items past the first gridDim.x
@@ -294,9 +292,11 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
     // samples x steps over the batch (lane 0's sum: the rotations leave
     // other lanes with other association orders)
     const double total = __shfl(wave_sum(valid ? dn * per : 0.0), 0);
-    const double per_block = fmin(fmax(total / (a.resident_blocks * kItemSteps), kItemsMin), kItemsMax);
+    const double steps = total / a.resident_blocks;     // per block
+    const double per_block = steps < kItems * kSmallItem ? fmax(steps / kSmallItem, 1.0)
+                                                         : fmin(fmax(steps / kItemSteps, kItems), kItemsMost);
     const double target = total / (a.resident_blocks * per_block);
-    const uint64_t most = (uint64_t)(256.0 * per_block);   // items per pair
+    const uint64_t most = (uint64_t)fmax(256.0 * per_block, 1024.0);
     const uint64_t left = (uint64_t)dn;
     const uint64_t first = valid ? (uint64_t)off[s * kMaxLevels + l] : 0;
     uint64_t base = first;
@@ -383,16 +383,12 @@ __device__ __forceinline__ WorkItem plan_item(const PlanTable& t, unsigned it)
     return w;
 }
 
-// Launch flags of the sampler.
-constexpr unsigned kSeedArg = 1;   // the seed is the launch's argument (else the descriptor's)
-
 // Block b takes item b first; later items come from its group's dispenser
 // until that has none left, so a launch with no more items than blocks (an empty one
 // included) makes no atomics on it.  Each item ends with a block reduction
 // into its (payoff, level) spread group.
 template <int MODEL, int M, int PPT, int PAYOFF, bool CV>
-__device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, uint64_t seed_arg,
-                                             unsigned flags)
+__device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, uint64_t seed)
 {
     __shared__ unsigned s_item;
     // the plan in LDS: each item is decoded by a short search over its pairs
@@ -403,7 +399,6 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
         for (int i = threadIdx.x; i < (int)(sizeof(PlanTable) / 8); i += blockDim.x) dst[i] = src[i];
         __syncthreads();
     }
-    const uint64_t seed = (flags & kSeedArg) ? seed_arg : d->seed;
     int tab_level = -1;
     const unsigned count = __builtin_amdgcn_readfirstlane(s_plan.start[s_plan.npairs]);
     for (unsigned it = blockIdx.x; it < count;) {   // block-uniform
@@ -446,13 +441,13 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
 // payoff, Euler paths; launched with the deepest level's table rows of
 // dynamic LDS).
 template <int MODEL, int M, int PPT, int PAYOFF, bool CV>
-__global__ __launch_bounds__(1024) void persistent_kernel(const BatchDesc* d, uint64_t seed, unsigned flags)
+__global__ __launch_bounds__(1024) void persistent_kernel(const BatchDesc* d, uint64_t seed)
 {
     extern __shared__ __attribute__((aligned(16))) float s_tab[];
-    sample_items<MODEL, M, PPT, PAYOFF, CV>(d, s_tab, seed, flags);
+    sample_items<MODEL, M, PPT, PAYOFF, CV>(d, s_tab, seed);
 }
 
-using PersistentFn = void (*)(const BatchDesc*, uint64_t, unsigned);
+using PersistentFn = void (*)(const BatchDesc*, uint64_t);
 
 template <int MODEL, int M, int PPT>
 PersistentFn pick_persistent_payoff(int payoff, bool cv)
