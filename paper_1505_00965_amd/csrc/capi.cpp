@@ -128,6 +128,27 @@ LaunchShape default_shape(const mlmc_model& m, const mlmc_payoff& p, int l, int 
             else s.block /= 2;
         }
     }
+    // few chains (paths, or the lanes of split paths): eight waves share 64 of
+    // them (process_coop).  Beyond two such blocks a compute unit the waves
+    // get in each other's way as the plain kernel's do, and a block's start and
+    // barriers show on short chains.  mlmc_level, us, plain and shared:
+    //   chains                16384        32768        49152        65536
+    //   Heston,    16 steps   15.6  15.2   15.6  16.1   15.5  16.6   15.5  18.9
+    //   Heston,    64 steps   20.1  17.1   20.2  18.6   20.4  20.9   20.7  23.2
+    //   Heston,   256 steps   38.1  23.5   38.7  29.1   38.7  35.2   40.8  42.4
+    //   GBM fp64, 256 steps   41.4  24.1   43.4  30.4   42.1  35.6   42.6  41.7
+    //   Asian split, 64       18.6  17.7   18.5  18.0   18.4  19.7   18.7  22.9
+    //   Asian split, 1024     71.5  41.4   72.2  47.3   71.3  63.9   71.7  75.2
+    const uint64_t chains = N * (uint64_t)s.split, per_cu = nf / s.split >= 256 ? 3 : 2;
+    if (!fixed_block && N > 0 && nf / s.split >= 64 && chains <= (uint64_t)num_cu * 64 * per_cu &&
+        (s.split > 1 || !split_eligible(m, p, precision))) {
+        s.coop = true;
+        s.block = kCoopThreads;
+        s.ppt = 1;
+        s.grid = (int)((chains + 63) / 64);
+        s.num_cu = 0;
+        return s;
+    }
     const uint64_t chunk = s.split > 1 ? (uint64_t)s.block / s.split : (uint64_t)s.block * s.ppt;
     const uint64_t chunks = (units + chunk - 1) / chunk;
     const uint64_t cap = (uint64_t)num_cu * (2048 / s.block);

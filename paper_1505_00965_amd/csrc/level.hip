@@ -50,12 +50,12 @@ template StepParams<double> make_step_params<double>(const mlmc_model&, const ml
 
 // ------------------------------------------------------------ dispatch
 // Instantiated in the per-variant translation units.
-extern template KernelFn<float> pick_variant<kGBM, float>(int, int, int, int, bool, bool);
-extern template KernelFn<double> pick_variant<kGBM, double>(int, int, int, int, bool, bool);
-extern template KernelFn<float> pick_variant<kGBMMil, float>(int, int, int, int, bool, bool);
-extern template KernelFn<double> pick_variant<kGBMMil, double>(int, int, int, int, bool, bool);
-extern template KernelFn<float> pick_variant<kHeston, float>(int, int, int, int, bool, bool);
-extern template KernelFn<double> pick_variant<kHeston, double>(int, int, int, int, bool, bool);
+extern template KernelFn<float> pick_variant<kGBM, float>(int, int, int, int, bool, bool, bool);
+extern template KernelFn<double> pick_variant<kGBM, double>(int, int, int, int, bool, bool, bool);
+extern template KernelFn<float> pick_variant<kGBMMil, float>(int, int, int, int, bool, bool, bool);
+extern template KernelFn<double> pick_variant<kGBMMil, double>(int, int, int, int, bool, bool, bool);
+extern template KernelFn<float> pick_variant<kHeston, float>(int, int, int, int, bool, bool, bool);
+extern template KernelFn<double> pick_variant<kHeston, double>(int, int, int, int, bool, bool, bool);
 
 int sampler_variant(const mlmc_model& m)
 {
@@ -64,13 +64,13 @@ int sampler_variant(const mlmc_model& m)
 }
 
 template <typename Real>
-static KernelFn<Real> pick(const mlmc_model& m, int payoff, int M, int ppt, int nf, bool split)
+static KernelFn<Real> pick(const mlmc_model& m, int payoff, int M, int ppt, int nf, bool split, bool coop)
 {
     const bool anti = m.antithetic != 0 && nf > 1;
     switch (sampler_variant(m)) {
-    case kGBMMil: return pick_variant<kGBMMil, Real>(payoff, M, ppt, nf, anti, split);
-    case kHeston: return pick_variant<kHeston, Real>(payoff, M, ppt, nf, anti, split);
-    default: return pick_variant<kGBM, Real>(payoff, M, ppt, nf, anti, split);
+    case kGBMMil: return pick_variant<kGBMMil, Real>(payoff, M, ppt, nf, anti, split, coop);
+    case kHeston: return pick_variant<kHeston, Real>(payoff, M, ppt, nf, anti, split, coop);
+    default: return pick_variant<kGBM, Real>(payoff, M, ppt, nf, anti, split, coop);
     }
 }
 
@@ -111,12 +111,12 @@ hipError_t launch_level(const mlmc_model& m, const mlmc_payoff& p, int M, int pr
     dim3 block(shape.block);
     if (precision == 64) {
         const auto& a = *(const LevelArgs<double>*)args;
-        auto fn = pick<double>(m, p.kind, M, 1, a.nf, false);
+        auto fn = pick<double>(m, p.kind, M, 1, a.nf, false, shape.coop);
         hipExtLaunchKernelGGL(fn, resident_grid((const void*)fn, shape), block, 0, stream, start,
                               stop, 0, a);
     } else {
         const auto& a = *(const LevelArgs<float>*)args;
-        auto fn = pick<float>(m, p.kind, M, shape.ppt, a.nf, a.split > 1);
+        auto fn = pick<float>(m, p.kind, M, shape.ppt, a.nf, a.split > 1, shape.coop);
         hipExtLaunchKernelGGL(fn, resident_grid((const void*)fn, shape), block, 0, stream, start,
                               stop, 0, a);
     }

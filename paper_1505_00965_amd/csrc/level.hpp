@@ -31,6 +31,10 @@ struct LevelArgs {
     uint32_t split = 1;   // lanes per path (split_lanes); 1: one path per lane
 };
 
+// Waves that share the work of 64 chains (process_coop).
+constexpr int kCoopWaves = 8;
+constexpr int kCoopThreads = 64 * kCoopWaves;
+
 // Philox counter word 2 of generator unit u (a block index on one- and
 // two-step levels, a sample index otherwise) at level l: l + 256 (u >> 32),
 // the same word make_path_key forms.
@@ -99,6 +103,7 @@ struct LaunchShape {
     int block, ppt, grid;
     int num_cu = 0;
     int split = 1;        // lanes per path (split_lanes)
+    bool coop = false;    // few chains: kCoopWaves waves share 64 of them (process_coop)
 };
 
 // Enqueue one level's sampler on `stream` (accumulating into args.acc).

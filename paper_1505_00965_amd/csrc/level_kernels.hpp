@@ -70,6 +70,19 @@ __global__ __launch_bounds__(1024) void split_level_kernel(LevelArgs<float> a)
     block_reduce_add(sums, nonfinite, a.acc + (blockIdx.x & a.spread_mask));
 }
 
+// Few chains: a block takes 64 of them at a time (process_coop).
+template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool SPLIT>
+__global__ __launch_bounds__(kCoopThreads) void coop_level_kernel(LevelArgs<Real> a)
+{
+    if constexpr (sizeof(Real) == 8) load_normal_tables();
+    double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
+    unsigned nonfinite = 0;
+    const uint64_t chains = a.N * (SPLIT ? a.split : 1u);
+    for (uint64_t c = (uint64_t)blockIdx.x * 64; c < chains; c += (uint64_t)gridDim.x * 64)
+        process_coop<MODEL, PAYOFF, Real, M, ANTI, SPLIT>(a, c, sums, nonfinite);
+    block_reduce_add(sums, nonfinite, a.acc + (blockIdx.x & a.spread_mask));
+}
+
 template <typename Real>
 using KernelFn = void (*)(LevelArgs<Real>);
 
@@ -77,12 +90,21 @@ using KernelFn = void (*)(LevelArgs<Real>);
 // The antithetic twin exists on coupled levels (n_f >= 2); fp64 paths run
 // one sample per lane (register budget); the twin runs at most two.
 template <int MODEL, int PAYOFF, typename Real, int M>
-KernelFn<Real> pick_ppt(int ppt, int nf, bool anti, bool split)
+KernelFn<Real> pick_ppt(int ppt, int nf, bool anti, bool split, bool coop)
 {
     if constexpr (sizeof(Real) == 4 && MODEL != kHeston && PAYOFF != kDigitalCond) {
-        if (split) return split_level_kernel<MODEL, PAYOFF, M>;
+        if (split) return coop ? coop_level_kernel<MODEL, PAYOFF, Real, M, false, true>
+                               : split_level_kernel<MODEL, PAYOFF, M>;
     }
     (void)split;
+    // unsplit chains: variants that cannot be split (fp32 GBM paths of a plain
+    // payoff are split wherever their chains are few)
+    if constexpr (sizeof(Real) == 8 || MODEL == kHeston || PAYOFF == kDigitalCond) {
+        if (coop) return anti ? coop_level_kernel<MODEL, PAYOFF, Real, M, true, false>
+                              : coop_level_kernel<MODEL, PAYOFF, Real, M, false, false>;
+    } else {
+        if (coop && anti) return coop_level_kernel<MODEL, PAYOFF, Real, M, true, false>;
+    }
     if constexpr (sizeof(Real) == 8) {
         (void)ppt;
         if (nf == 1) return short_level_kernel<MODEL, PAYOFF, Real, 1, M, 1, false>;
@@ -114,23 +136,23 @@ KernelFn<Real> pick_ppt(int ppt, int nf, bool anti, bool split)
 }
 
 template <int MODEL, int PAYOFF, typename Real>
-KernelFn<Real> pick_m(int M, int ppt, int nf, bool anti, bool split)
+KernelFn<Real> pick_m(int M, int ppt, int nf, bool anti, bool split, bool coop)
 {
-    return M == 2 ? pick_ppt<MODEL, PAYOFF, Real, 2>(ppt, nf, anti, split)
-                  : pick_ppt<MODEL, PAYOFF, Real, 4>(ppt, nf, anti, split);
+    return M == 2 ? pick_ppt<MODEL, PAYOFF, Real, 2>(ppt, nf, anti, split, coop)
+                  : pick_ppt<MODEL, PAYOFF, Real, 4>(ppt, nf, anti, split, coop);
 }
 
 // The kernel of one sampler variant for (payoff, M, samples per lane, n_f,
-// antithetic, split paths).  Defined here, instantiated once per variant.
+// antithetic, split paths, few chains).  Defined here, instantiated once per variant.
 template <int MODEL, typename Real>
-KernelFn<Real> pick_variant(int payoff, int M, int ppt, int nf, bool anti, bool split)
+KernelFn<Real> pick_variant(int payoff, int M, int ppt, int nf, bool anti, bool split, bool coop)
 {
     switch (payoff) {
-    case kCall: return pick_m<MODEL, kCall, Real>(M, ppt, nf, anti, split);
-    case kAsian: return pick_m<MODEL, kAsian, Real>(M, ppt, nf, anti, split);
-    case kLookback: return pick_m<MODEL, kLookback, Real>(M, ppt, nf, anti, split);
-    case kDigitalCond: return pick_m<MODEL, kDigitalCond, Real>(M, ppt, nf, anti, split);
-    default: return pick_m<MODEL, kDigital, Real>(M, ppt, nf, anti, split);
+    case kCall: return pick_m<MODEL, kCall, Real>(M, ppt, nf, anti, split, coop);
+    case kAsian: return pick_m<MODEL, kAsian, Real>(M, ppt, nf, anti, split, coop);
+    case kLookback: return pick_m<MODEL, kLookback, Real>(M, ppt, nf, anti, split, coop);
+    case kDigitalCond: return pick_m<MODEL, kDigitalCond, Real>(M, ppt, nf, anti, split, coop);
+    default: return pick_m<MODEL, kDigital, Real>(M, ppt, nf, anti, split, coop);
     }
 }
 

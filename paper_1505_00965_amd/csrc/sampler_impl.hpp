@@ -70,41 +70,51 @@ __host__ __device__ constexpr bool twin_coarse()
     return PAYOFF == kLookback || PAYOFF == kDigitalCond;
 }
 
-// Generator block g of a path (four fine steps): its increments, advanced
-// through q's fine and coarse paths; with ANTI also through the antithetic
-// twin qa (same generator words, the increments reversed inside every
-// coarse step).  Without COUPLED only the fine path is advanced.
-template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
-__device__ __forceinline__ void advance_group(const StepParams<Real>& P, const PathKey& key,
-                                              const PathKey& bkey, uint32_t g, PathPair<Real>& q,
-                                              PathPair<Real>& qa)
-{
+// The increments of generator block g of a path (four fine steps): both
+// factors (the second for Heston) and the lookback's bridge exponents.
+template <typename Real>
+struct Increments {
     Real dw1[4], dwp[4], e[4];
+};
+
+template <int MODEL, int PAYOFF, typename Real>
+__device__ __forceinline__ void draw_group(const StepParams<Real>& P, const PathKey& key, const PathKey& bkey,
+                                           uint32_t g, Increments<Real>& x)
+{
     if (one_factor(MODEL)) {
         const u32x4 w = path_block(key, g);
-        brownian_pair(w.x, w.y, P, dw1[0], dw1[1]);
-        brownian_pair(w.z, w.w, P, dw1[2], dw1[3]);
-        dwp[0] = dwp[1] = dwp[2] = dwp[3] = Real(0);
+        brownian_pair(w.x, w.y, P, x.dw1[0], x.dw1[1]);
+        brownian_pair(w.z, w.w, P, x.dw1[2], x.dw1[3]);
+        x.dwp[0] = x.dwp[1] = x.dwp[2] = x.dwp[3] = Real(0);
     } else {
         const u32x4 wa = path_block(key, 2 * g);
         const u32x4 wb = path_block(key, 2 * g + 1);
-        brownian_pair(wa.x, wa.y, P, dw1[0], dwp[0]);
-        brownian_pair(wa.z, wa.w, P, dw1[1], dwp[1]);
-        brownian_pair(wb.x, wb.y, P, dw1[2], dwp[2]);
-        brownian_pair(wb.z, wb.w, P, dw1[3], dwp[3]);
+        brownian_pair(wa.x, wa.y, P, x.dw1[0], x.dwp[0]);
+        brownian_pair(wa.z, wa.w, P, x.dw1[1], x.dwp[1]);
+        brownian_pair(wb.x, wb.y, P, x.dw1[2], x.dwp[2]);
+        brownian_pair(wb.z, wb.w, P, x.dw1[3], x.dwp[3]);
     }
     if (PAYOFF == kLookback) {
         const u32x4 u = path_block(bkey, g);
-        e[0] = bridge_exponent(u.x, P);
-        e[1] = bridge_exponent(u.y, P);
-        e[2] = bridge_exponent(u.z, P);
-        e[3] = bridge_exponent(u.w, P);
+        x.e[0] = bridge_exponent(u.x, P);
+        x.e[1] = bridge_exponent(u.y, P);
+        x.e[2] = bridge_exponent(u.z, P);
+        x.e[3] = bridge_exponent(u.w, P);
     } else {
-        e[0] = e[1] = e[2] = e[3] = Real(0);
+        x.e[0] = x.e[1] = x.e[2] = x.e[3] = Real(0);
     }
+}
+
+// Four fine steps with the increments x through q's fine and coarse paths;
+// with ANTI also through the antithetic twin qa (the increments reversed
+// inside every coarse step).  Without COUPLED only the fine path is advanced.
+template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
+__device__ __forceinline__ void step_group(const StepParams<Real>& P, const Increments<Real>& x, PathPair<Real>& q,
+                                           PathPair<Real>& qa)
+{
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        fine_step<Real, MODEL, PAYOFF>(q, P, dw1[k], dwp[k], e[k], k % M, COUPLED);
+        fine_step<Real, MODEL, PAYOFF>(q, P, x.dw1[k], x.dwp[k], x.e[k], k % M, COUPLED);
         if (COUPLED && ((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(q, P);
     }
     if (ANTI) {
@@ -112,10 +122,21 @@ __device__ __forceinline__ void advance_group(const StepParams<Real>& P, const P
         for (int k = 0; k < 4; ++k) {
             constexpr bool tc = twin_coarse<PAYOFF>();
             const int j = twin_index<M>(k);
-            fine_step<Real, MODEL, PAYOFF>(qa, P, dw1[j], dwp[j], e[j], k % M, tc);
+            fine_step<Real, MODEL, PAYOFF>(qa, P, x.dw1[j], x.dwp[j], x.e[j], k % M, tc);
             if (tc && ((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(qa, P);
         }
     }
+}
+
+// Both, for one generator block of a path.
+template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
+__device__ __forceinline__ void advance_group(const StepParams<Real>& P, const PathKey& key,
+                                              const PathKey& bkey, uint32_t g, PathPair<Real>& q,
+                                              PathPair<Real>& qa)
+{
+    Increments<Real> x;
+    draw_group<MODEL, PAYOFF, Real>(P, key, bkey, g, x);
+    step_group<MODEL, PAYOFF, Real, M, ANTI, COUPLED>(P, x, q, qa);
 }
 
 // Advance PPT coupled pairs through all n_f >= 4 fine steps of the level;
@@ -211,40 +232,16 @@ __device__ __forceinline__ void process_chunk(const LevelArgs<Real>& a, uint64_t
     }
 }
 
-// GBM paths split across G = a.split consecutive lanes (a power of two up to
-// 64), for levels whose paths are too few to fill the device.  Lane j of a
-// path runs fine steps [j n_f/G, (j+1) n_f/G) from a unit start: the Euler
-// and Milstein GBM steps, both coarse constructions and every payoff
-// functional are linear in the start value (the terminal value is a product
-// of segment factors, the sum of S_n adds the next segment's sum scaled by
-// the product so far, the bridge minima scale the same way).  The segment
-// summaries (P, Sigma, m) of fine and coarse path combine in path order,
-// (P1, S1, m1) o (P2, S2, m2) = (P1 P2, S1 + P1 S2, min(m1, P1 m2)), in fp64
-// over a shuffle tree, and the path's first lane forms the payoffs at scale
-// S0.  n_f / G is a multiple of 4, so segments hold whole generator blocks
-// and whole coarse steps.  base indexes paths; a block takes blockDim / G.
-template <int MODEL, int PAYOFF, int M>
-__device__ __forceinline__ void process_split(const LevelArgs<float>& a, uint64_t base,
-                                              double (&sums)[kNumSums], unsigned& nonfinite)
+// Segment summaries of a split path (lane seg of G holds q, run from a unit
+// start) combined in path order over the path's lanes; its first lane forms
+// the payoffs of sample idx.
+template <int PAYOFF>
+__device__ __forceinline__ void finish_split(const LevelArgs<float>& a, const PathPair<float>& q, uint64_t idx,
+                                             int seg, double (&sums)[kNumSums], unsigned& nonfinite)
 {
-    static_assert(MODEL != kHeston, "the variance step is not linear in the start value");
-    static_assert(PAYOFF != kDigitalCond, "the conditional payoff needs the last step's state");
     const int G = (int)a.split;
-    const int seg = (int)threadIdx.x & (G - 1);
-    const uint64_t idx = base + threadIdx.x / (uint32_t)G;
-    const uint64_t s = a.offset + idx;
     const bool coupled = a.coupled && a.l > 0;
     const StepParams<float>& P = a.P;
-    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-    const PathKey key{k0, k1, (uint32_t)s, a.c2, a.stream};
-    const PathKey bkey{k0, k1, (uint32_t)s, a.c2b, a.stream + 1u};
-    PathPair<float> q, qa;
-    init_pair<float, MODEL, PAYOFF>(q, P);
-    q.S = 1.0f;
-    q.Sc = 1.0f;
-    const uint32_t per = a.ngroups / (uint32_t)G;     // generator blocks per lane
-    for (uint32_t g = (uint32_t)seg * per; g < (uint32_t)(seg + 1) * per; ++g)
-        advance_group<MODEL, PAYOFF, float, M, false>(P, key, bkey, g, q, qa);
     double pf = q.S, sf = (double)q.asum - (double)q.acomp, mf = q.mn;
     double pc = q.Sc, sc = (double)q.csum - (double)q.ccomp, mc = q.mnc;
     for (int off = 1; off < G; off <<= 1) {
@@ -280,6 +277,176 @@ __device__ __forceinline__ void process_split(const LevelArgs<float>& a, uint64_
                                                            0.0f, (float)(S0 * mc), P.H)
                              : 0.0f;
     if (idx < a.N) accumulate(a, idx, vf, vc, sums, nonfinite);
+}
+
+// GBM paths split across G = a.split consecutive lanes (a power of two up to
+// 64), for levels whose paths are too few to fill the device.  Lane j of a
+// path runs fine steps [j n_f/G, (j+1) n_f/G) from a unit start: the Euler
+// and Milstein GBM steps, both coarse constructions and every payoff
+// functional are linear in the start value (the terminal value is a product
+// of segment factors, the sum of S_n adds the next segment's sum scaled by
+// the product so far, the bridge minima scale the same way).  The segment
+// summaries (P, Sigma, m) of fine and coarse path combine in path order,
+// (P1, S1, m1) o (P2, S2, m2) = (P1 P2, S1 + P1 S2, min(m1, P1 m2)), in fp64
+// over a shuffle tree, and the path's first lane forms the payoffs at scale
+// S0.  n_f / G is a multiple of 4, so segments hold whole generator blocks
+// and whole coarse steps.  base indexes paths; a block takes blockDim / G.
+template <int MODEL, int PAYOFF, int M>
+__device__ __forceinline__ void process_split(const LevelArgs<float>& a, uint64_t base,
+                                              double (&sums)[kNumSums], unsigned& nonfinite)
+{
+    static_assert(MODEL != kHeston, "the variance step is not linear in the start value");
+    static_assert(PAYOFF != kDigitalCond, "the conditional payoff needs the last step's state");
+    const int G = (int)a.split;
+    const int seg = (int)threadIdx.x & (G - 1);
+    const uint64_t idx = base + threadIdx.x / (uint32_t)G;
+    const uint64_t s = a.offset + idx;
+    const StepParams<float>& P = a.P;
+    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+    const PathKey key{k0, k1, (uint32_t)s, a.c2, a.stream};
+    const PathKey bkey{k0, k1, (uint32_t)s, a.c2b, a.stream + 1u};
+    PathPair<float> q, qa;
+    init_pair<float, MODEL, PAYOFF>(q, P);
+    q.S = 1.0f;
+    q.Sc = 1.0f;
+    const uint32_t per = a.ngroups / (uint32_t)G;     // generator blocks per lane
+    for (uint32_t g = (uint32_t)seg * per; g < (uint32_t)(seg + 1) * per; ++g)
+        advance_group<MODEL, PAYOFF, float, M, false>(P, key, bkey, g, q, qa);
+    finish_split<PAYOFF>(a, q, idx, seg, sums, nonfinite);
+}
+
+// Launches of too few chains (paths, or segments of split paths) to give every
+// SIMD several waves.  A wave that has its SIMD to itself issues an
+// instruction every 8 cycles, so a chain takes as long as its instructions;
+// here the instructions of 64 chains go to eight waves instead of one: the
+// fine path, the coarse path and the twin are a wave each (they share only the
+// increments), the other waves draw the increments, a generator block of every
+// chain per wave and round, handed over through LDS (two rounds' worth: one
+// barrier a round).  Each path's operations are those of step_group, in order;
+// what a wave computes of the other paths is dead code.
+// mlmc_level of 331 samples, before and after: 16384 Heston steps 1623 -> 528
+// us, 16384 fp64 GBM steps 1290 -> 539 us; 331 Milstein Asian paths of 65536
+// steps on 64 lanes each 71 -> 46 us.
+enum { kFinePath, kCoarsePath, kTwinPath };
+
+template <int ROLE, int MODEL, int PAYOFF, typename Real, int M>
+__device__ __forceinline__ void step_path(const StepParams<Real>& P, const Increments<Real>& x, PathPair<Real>& q)
+{
+    constexpr bool coarse = ROLE == kCoarsePath || (ROLE == kTwinPath && twin_coarse<PAYOFF>());
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int j = ROLE == kTwinPath ? twin_index<M>(k) : k;
+        fine_step<Real, MODEL, PAYOFF>(q, P, x.dw1[j], x.dwp[j], x.e[j], k % M, coarse);
+        if (coarse && ((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(q, P);
+    }
+}
+
+template <typename Real>
+using Quad = Real __attribute__((ext_vector_type(4)));
+
+// n generator blocks from a round's increments (D waves' blocks, V quadruples each).
+template <int ROLE, int MODEL, int PAYOFF, typename Real, int M, int D, int V>
+__device__ __forceinline__ void step_round(const StepParams<Real>& P, const Quad<Real> (*from)[V][64], int lane,
+                                           int n, PathPair<Real>& q)
+{
+    auto one = [&](int j) {
+        Increments<Real> x;
+        const Quad<Real> d = from[j][0][lane];
+        const Quad<Real> p = one_factor(MODEL) ? Quad<Real>{0, 0, 0, 0} : from[j][V > 1 ? 1 : 0][lane];
+        const Quad<Real> e = PAYOFF == kLookback ? from[j][V - 1][lane] : Quad<Real>{0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x.dw1[k] = d[k];
+            x.dwp[k] = p[k];
+            x.e[k] = e[k];
+        }
+        step_path<ROLE, MODEL, PAYOFF, Real, M>(P, x, q);
+    };
+    if (n == D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) one(j);
+    } else {
+#pragma unroll 1
+        for (int j = 0; j < n; ++j) one(j);
+    }
+}
+
+template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool SPLIT>
+__device__ __forceinline__ void process_coop(const LevelArgs<Real>& a, uint64_t chain0, double (&sums)[kNumSums],
+                                             unsigned& nonfinite)
+{
+    constexpr int S = ANTI ? 3 : 2, D = kCoopWaves - S;   // waves that step, waves that draw
+    constexpr int V = 1 + (one_factor(MODEL) ? 0 : 1) + (PAYOFF == kLookback ? 1 : 0);
+    __shared__ Quad<Real> s_inc[2][D][V][64];
+    __shared__ Real s_end[4][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t G = SPLIT ? a.split : 1u;
+    const uint64_t chain = chain0 + lane, idx = chain / G;
+    const int seg = (int)(chain % G);
+    const bool coupled = a.coupled && a.l > 0;
+    const StepParams<Real>& P = a.P;
+    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32), s = (uint32_t)(a.offset + idx);
+    const PathKey key{k0, k1, s, a.c2, a.stream};
+    const PathKey bkey{k0, k1, s, a.c2b, a.stream + 1u};
+    const uint32_t per = a.ngroups / G, g0 = (uint32_t)seg * per;
+    const uint32_t rounds = (per + D - 1) / D;
+    PathPair<Real> q, qc, qa;
+    init_pair<Real, MODEL, PAYOFF>(q, P);
+    if (SPLIT) q.S = q.Sc = Real(1);
+    qc = qa = q;
+    // the paths' chains are the longer ones: they go first on a shared SIMD
+    if (wave < S) __builtin_amdgcn_s_setprio(3);
+    // round r's blocks are stepped, those of round r + 1 drawn
+    for (uint32_t r = 0; r <= rounds; ++r) {
+        if (wave >= S) {
+            const uint32_t g = r * D + (uint32_t)(wave - S);
+            if (g < per) {
+                Increments<Real> x;
+                draw_group<MODEL, PAYOFF, Real>(P, key, bkey, g0 + g, x);
+                Quad<Real>(*to)[64] = s_inc[r & 1][wave - S];
+                to[0][lane] = Quad<Real>{x.dw1[0], x.dw1[1], x.dw1[2], x.dw1[3]};
+                if (!one_factor(MODEL)) to[V > 1 ? 1 : 0][lane] = Quad<Real>{x.dwp[0], x.dwp[1], x.dwp[2], x.dwp[3]};
+                if (PAYOFF == kLookback) to[V - 1][lane] = Quad<Real>{x.e[0], x.e[1], x.e[2], x.e[3]};
+            }
+        } else if (r > 0) {
+            const uint32_t left = per - (r - 1) * D;
+            const int n = (int)(left < D ? left : D);
+            const Quad<Real>(*from)[V][64] = s_inc[(r - 1) & 1];
+            if (wave == 0) step_round<kFinePath, MODEL, PAYOFF, Real, M, D, V>(P, from, lane, n, q);
+            else if (ANTI && wave == 2) step_round<kTwinPath, MODEL, PAYOFF, Real, M, D, V>(P, from, lane, n, qa);
+            else if (coupled) step_round<kCoarsePath, MODEL, PAYOFF, Real, M, D, V>(P, from, lane, n, qc);
+        }
+        __syncthreads();
+    }
+    if (wave == 1) {
+        if (SPLIT) {
+            s_end[0][lane] = qc.Sc;
+            s_end[1][lane] = qc.csum;
+            s_end[2][lane] = qc.ccomp;
+            s_end[3][lane] = qc.mnc;
+        } else {
+            s_end[0][lane] = coupled ? coarse_payoff<MODEL, PAYOFF>(P, qc) : Real(0);
+        }
+    } else if (ANTI && wave == 2) {
+        s_end[1][lane] = fine_payoff<MODEL, PAYOFF>(P, qa);
+        if (twin_coarse<PAYOFF>()) s_end[2][lane] = coarse_payoff<MODEL, PAYOFF>(P, qa);
+    }
+    __syncthreads();
+    if (wave) return;
+    if constexpr (SPLIT) {
+        q.Sc = s_end[0][lane];
+        q.csum = s_end[1][lane];
+        q.ccomp = s_end[2][lane];
+        q.mnc = s_end[3][lane];
+        finish_split<PAYOFF>(a, q, idx, seg, sums, nonfinite);
+    } else {
+        Real pf = fine_payoff<MODEL, PAYOFF>(P, q), pc = s_end[0][lane];
+        if (ANTI) {
+            pf = Real(0.5) * (pf + s_end[1][lane]);
+            if (twin_coarse<PAYOFF>()) pc = Real(0.5) * (pc + s_end[2][lane]);
+        }
+        if (idx < a.N) accumulate(a, idx, pf, pc, sums, nonfinite);
+    }
 }
 
 // Levels with n_f = NF in {1, 2}: Q = 4/(NF d) consecutive samples share one
