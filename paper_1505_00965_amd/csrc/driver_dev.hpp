@@ -186,29 +186,32 @@ __device__ __forceinline__ void driver_update_wave(DriverState& s)
         const double v = in ? sum2 / n - mr * mr : 0.0;
         const double est = ordered_sum(mr, L);
         const double var = ordered_sum(in ? (v > 0 ? v : 0) / n : 0.0, L);
-        // fitted rates over l = 1..L of |E_l|, V_l and C_l
-        const double lm = log((double)M);
-        double rate[3];
-        for (int f = 0; f < 3; ++f) {
-            const double y = f == 0 ? fabs(mr) : (f == 1 ? v : C);
-            const bool use = in && lane >= 1 && y > 0;
-            const double vy = use ? log(y) / lm : 0.0;
-            const unsigned long long used = __ballot(use);
-            double sx = 0, sy = 0, sxx = 0, sxy = 0;
-            int cnt = 0;
-            for (int l = 1; l <= L; ++l) {
-                if (!((used >> l) & 1ull)) continue;
-                const double x = l, w = lane_f64(vy, l);
+        // fitted rates over l = 1..L of |E_l|, V_l and C_l, 16 lanes each: the
+        // logarithms and the ordered sums of the three run side by side
+        // (one after the other they were 1.7 us of the finishing update's 3.7)
+        static_assert(kMaxLevels == 16, "a fit's levels in 16 lanes");
+        const int fl = lane & 15, f0 = lane & 48;
+        const double ym = __shfl(fabs(mr), fl), yv = __shfl(v, fl), yc = __shfl(C, fl);
+        const double y = f0 == 0 ? ym : (f0 == 16 ? yv : yc);
+        const bool use = fl >= 1 && fl <= L && y > 0;
+        const double vy = use ? log(y) / log((double)M) : 0.0;
+        const unsigned used = (unsigned)(__ballot(use) >> f0) & 0xffffu;
+        double sx = 0, sy = 0, sxx = 0, sxy = 0;
+        int cnt = 0;
+        for (int l = 1; l <= L; ++l) {
+            const double x = l, w = __shfl(vy, f0 | l);
+            if ((used >> l) & 1u) {
                 sx += x; sy += w; sxx += x * x; sxy += x * w; ++cnt;
             }
-            rate[f] = cnt < 2 ? nan("") : (cnt * sxy - sx * sy) / (cnt * sxx - sx * sx);
         }
+        const double rate = cnt < 2 ? nan("") : (cnt * sxy - sx * sy) / (cnt * sxx - sx * sx);
+        const double rate0 = lane_f64(rate, 0), rate1 = lane_f64(rate, 16), rate2 = lane_f64(rate, 32);
         if (lane == 0) {
             s.estimate = est;
             s.var_est = var;
-            s.alpha_fit = -rate[0];
-            s.beta_fit = -rate[1];
-            s.gamma_fit = rate[2];
+            s.alpha_fit = -rate0;
+            s.beta_fit = -rate1;
+            s.gamma_fit = rate2;
         }
     }
     // write back: every level the update touched (the finished state has

@@ -76,8 +76,9 @@ __global__ __launch_bounds__(256) void driver_start_kernel(DriverState* st, Leve
 }
 
 // One iteration's end: sum the spread groups, absorb the batch, re-plan
-// (update_state), plan the next batch's items from the new state in LDS,
-// then write the state back and clear the groups.  The host reads the
+// (update_state), plan the next batch's items from the new state in LDS
+// (nothing for a finished one, whose result the host waits for), then write
+// the state back and clear the groups.  The host reads the
 // update count every iteration and the state once, at the end: the mirror
 // is written whole by the finishing update only.  Every load goes out at
 // the start, none waiting for another: the state (one word per thread), the
@@ -116,9 +117,11 @@ __global__ __launch_bounds__(512) void driver_update_plan_kernel(DriverState* st
     y0 = wave_sum(y0);
     q0 = wave_sum(q0);
     c0 = wave_sum(c0);
-    y1 = wave_sum(y1);
-    q1 = wave_sum(q1);
-    c1 = wave_sum(c1);
+    if (L0 >= 8) {   // above it the second level's records are zeros
+        y1 = wave_sum(y1);
+        q1 = wave_sum(q1);
+        c1 = wave_sum(c1);
+    }
     if (done) {   // block-uniform
         // The update queued past a run's finishing one: the state becomes
         // the fresh state of a next run of this descriptor and the plan its
@@ -150,7 +153,8 @@ __global__ __launch_bounds__(512) void driver_update_plan_kernel(DriverState* st
     }
     __syncthreads();
     update_state(s);   // ends with a barrier
-    plan_body(pa, s.dN, s.n);
+    if (s.done) plan_nothing(pa);
+    else plan_body(pa, s.dN, s.n);
     publish_state(st, mirror, s, false);
     clear_groups(spread, L0);
 }

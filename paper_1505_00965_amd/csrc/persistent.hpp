@@ -367,6 +367,16 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
     if (a.head && p < kHeads) a.head[p * kHeadStride] = 0;
 }
 
+// The plan of a finished state: no items.
+__device__ __forceinline__ void plan_nothing(const PlanArgs& a)
+{
+    if (threadIdx.x == 0) {
+        a.plan->start[0] = 0;
+        a.plan->npairs = 0;
+    }
+    if (a.head && threadIdx.x < kHeads) a.head[threadIdx.x * kHeadStride] = 0;
+}
+
 // Item `it` of the plan (block-uniform).
 __device__ __forceinline__ WorkItem plan_item(const PlanTable& t, unsigned it)
 {
