@@ -34,6 +34,7 @@ def test_unsplit_samples_equal_plain_kernel(gctx, case, N):
         out = []
         for c in (gctx, plain):
             d = torch.full((2, N), -1.0, dtype=torch.float64, device="cuda")
+            torch.cuda.synchronize()              # the fill runs on another stream
             r = c.mlmc_level_paths(m, p, l, M, N, 3, d[0], d[1], path_offset=77, precision=prec)
             out.append((d.cpu().numpy(), r))
     assert np.array_equal(out[0][0], out[1][0])
@@ -51,6 +52,7 @@ def test_unsplit_samples_equal_plain_kernel(gctx, case, N):
 def test_split_samples_equal_plain_kernel(gctx, pay, scheme, M, l, N):
     m, p = A.model(A.GBM, scheme=scheme), A.payoff(pay)
     d = torch.full((4, N), -1.0, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()              # the fill runs on another stream
     gctx.mlmc_level_paths(m, p, l, M, N, 5, d[0], d[1], path_offset=9)
     with A.Context(0) as plain:
         plain.set_launch(64, 1)

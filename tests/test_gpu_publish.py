@@ -57,6 +57,7 @@ def test_randomised_estimate_by_plan_and_by_level(gctx, M, L, q, N):
     # the draws: level l above l - 1 when the uniform is at least F_(l-1)
     import torch
     w = torch.zeros(4 * ((N + 3) // 4), dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()              # the fill runs on another stream than the words
     gctx.mlmc_philox_words(11, 0, 0, 7, 1, (N + 3) // 4, w)
     u = ((w.cpu().numpy().view(np.uint32)[:N] >> 8) + 0.5) * 2.0 ** -24
     F = np.cumsum(a["p"])[:-1]
