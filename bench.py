@@ -405,8 +405,8 @@ def time_to_accuracy(ctx, mlmc, W, args, seeds=range(1, 33)):
 
 
 def persistent_batch(ctx, mlmc, W, reps=3):
-    """All levels 0..8 of four payoffs (N_l = 2^26 4^-l) in one graph-replayed
-    persistent launch with the autotuned shape (and the default one), against
+    """All levels 0..8 of four payoffs (N_l = 2^26 4^-l) in one batch, one
+    persistent launch with the autotuned shape (or the default one), against
     the sum of the 36 per-level launches."""
     import torch
     gm = mlmc.model(**W.GBM_MODEL)
