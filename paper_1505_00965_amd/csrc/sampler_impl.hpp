@@ -70,51 +70,41 @@ __host__ __device__ constexpr bool twin_coarse()
     return PAYOFF == kLookback || PAYOFF == kDigitalCond;
 }
 
-// The increments of generator block g of a path (four fine steps): both
-// factors (the second for Heston) and the lookback's bridge exponents.
-template <typename Real>
-struct Increments {
-    Real dw1[4], dwp[4], e[4];
-};
-
-template <int MODEL, int PAYOFF, typename Real>
-__device__ __forceinline__ void draw_group(const StepParams<Real>& P, const PathKey& key, const PathKey& bkey,
-                                           uint32_t g, Increments<Real>& x)
+// Generator block g of a path (four fine steps): its increments, advanced
+// through q's fine and coarse paths; with ANTI also through the antithetic
+// twin qa (same generator words, the increments reversed inside every
+// coarse step).  Without COUPLED only the fine path is advanced.
+template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
+__device__ __forceinline__ void advance_group(const StepParams<Real>& P, const PathKey& key,
+                                              const PathKey& bkey, uint32_t g, PathPair<Real>& q,
+                                              PathPair<Real>& qa)
 {
+    Real dw1[4], dwp[4], e[4];
     if (one_factor(MODEL)) {
         const u32x4 w = path_block(key, g);
-        brownian_pair(w.x, w.y, P, x.dw1[0], x.dw1[1]);
-        brownian_pair(w.z, w.w, P, x.dw1[2], x.dw1[3]);
-        x.dwp[0] = x.dwp[1] = x.dwp[2] = x.dwp[3] = Real(0);
+        brownian_pair(w.x, w.y, P, dw1[0], dw1[1]);
+        brownian_pair(w.z, w.w, P, dw1[2], dw1[3]);
+        dwp[0] = dwp[1] = dwp[2] = dwp[3] = Real(0);
     } else {
         const u32x4 wa = path_block(key, 2 * g);
         const u32x4 wb = path_block(key, 2 * g + 1);
-        brownian_pair(wa.x, wa.y, P, x.dw1[0], x.dwp[0]);
-        brownian_pair(wa.z, wa.w, P, x.dw1[1], x.dwp[1]);
-        brownian_pair(wb.x, wb.y, P, x.dw1[2], x.dwp[2]);
-        brownian_pair(wb.z, wb.w, P, x.dw1[3], x.dwp[3]);
+        brownian_pair(wa.x, wa.y, P, dw1[0], dwp[0]);
+        brownian_pair(wa.z, wa.w, P, dw1[1], dwp[1]);
+        brownian_pair(wb.x, wb.y, P, dw1[2], dwp[2]);
+        brownian_pair(wb.z, wb.w, P, dw1[3], dwp[3]);
     }
     if (PAYOFF == kLookback) {
         const u32x4 u = path_block(bkey, g);
-        x.e[0] = bridge_exponent(u.x, P);
-        x.e[1] = bridge_exponent(u.y, P);
-        x.e[2] = bridge_exponent(u.z, P);
-        x.e[3] = bridge_exponent(u.w, P);
+        e[0] = bridge_exponent(u.x, P);
+        e[1] = bridge_exponent(u.y, P);
+        e[2] = bridge_exponent(u.z, P);
+        e[3] = bridge_exponent(u.w, P);
     } else {
-        x.e[0] = x.e[1] = x.e[2] = x.e[3] = Real(0);
+        e[0] = e[1] = e[2] = e[3] = Real(0);
     }
-}
-
-// Four fine steps with the increments x through q's fine and coarse paths;
-// with ANTI also through the antithetic twin qa (the increments reversed
-// inside every coarse step).  Without COUPLED only the fine path is advanced.
-template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
-__device__ __forceinline__ void step_group(const StepParams<Real>& P, const Increments<Real>& x, PathPair<Real>& q,
-                                           PathPair<Real>& qa)
-{
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        fine_step<Real, MODEL, PAYOFF>(q, P, x.dw1[k], x.dwp[k], x.e[k], k % M, COUPLED);
+        fine_step<Real, MODEL, PAYOFF>(q, P, dw1[k], dwp[k], e[k], k % M, COUPLED);
         if (COUPLED && ((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(q, P);
     }
     if (ANTI) {
@@ -122,21 +112,10 @@ __device__ __forceinline__ void step_group(const StepParams<Real>& P, const Incr
         for (int k = 0; k < 4; ++k) {
             constexpr bool tc = twin_coarse<PAYOFF>();
             const int j = twin_index<M>(k);
-            fine_step<Real, MODEL, PAYOFF>(qa, P, x.dw1[j], x.dwp[j], x.e[j], k % M, tc);
+            fine_step<Real, MODEL, PAYOFF>(qa, P, dw1[j], dwp[j], e[j], k % M, tc);
             if (tc && ((k + 1) % M) == 0) coarse_step<Real, MODEL, PAYOFF>(qa, P);
         }
     }
-}
-
-// Both, for one generator block of a path.
-template <int MODEL, int PAYOFF, typename Real, int M, bool ANTI, bool COUPLED = true>
-__device__ __forceinline__ void advance_group(const StepParams<Real>& P, const PathKey& key,
-                                              const PathKey& bkey, uint32_t g, PathPair<Real>& q,
-                                              PathPair<Real>& qa)
-{
-    Increments<Real> x;
-    draw_group<MODEL, PAYOFF, Real>(P, key, bkey, g, x);
-    step_group<MODEL, PAYOFF, Real, M, ANTI, COUPLED>(P, x, q, qa);
 }
 
 // Advance PPT coupled pairs through all n_f >= 4 fine steps of the level;
@@ -315,6 +294,41 @@ __device__ __forceinline__ void process_split(const LevelArgs<float>& a, uint64_
     finish_split<PAYOFF>(a, q, idx, seg, sums, nonfinite);
 }
 
+// The increments of generator block g of a path (four fine steps): both
+// factors (the second for Heston) and the lookback's bridge exponents.
+template <typename Real>
+struct Increments {
+    Real dw1[4], dwp[4], e[4];
+};
+
+template <int MODEL, int PAYOFF, typename Real>
+__device__ __forceinline__ void draw_group(const StepParams<Real>& P, const PathKey& key, const PathKey& bkey,
+                                           uint32_t g, Increments<Real>& x)
+{
+    if (one_factor(MODEL)) {
+        const u32x4 w = path_block(key, g);
+        brownian_pair(w.x, w.y, P, x.dw1[0], x.dw1[1]);
+        brownian_pair(w.z, w.w, P, x.dw1[2], x.dw1[3]);
+        x.dwp[0] = x.dwp[1] = x.dwp[2] = x.dwp[3] = Real(0);
+    } else {
+        const u32x4 wa = path_block(key, 2 * g);
+        const u32x4 wb = path_block(key, 2 * g + 1);
+        brownian_pair(wa.x, wa.y, P, x.dw1[0], x.dwp[0]);
+        brownian_pair(wa.z, wa.w, P, x.dw1[1], x.dwp[1]);
+        brownian_pair(wb.x, wb.y, P, x.dw1[2], x.dwp[2]);
+        brownian_pair(wb.z, wb.w, P, x.dw1[3], x.dwp[3]);
+    }
+    if (PAYOFF == kLookback) {
+        const u32x4 u = path_block(bkey, g);
+        x.e[0] = bridge_exponent(u.x, P);
+        x.e[1] = bridge_exponent(u.y, P);
+        x.e[2] = bridge_exponent(u.z, P);
+        x.e[3] = bridge_exponent(u.w, P);
+    } else {
+        x.e[0] = x.e[1] = x.e[2] = x.e[3] = Real(0);
+    }
+}
+
 // Launches of too few chains (paths, or segments of split paths) to give every
 // SIMD several waves.  A wave that has its SIMD to itself issues an
 // instruction every 8 cycles, so a chain takes as long as its instructions;
@@ -322,7 +336,7 @@ __device__ __forceinline__ void process_split(const LevelArgs<float>& a, uint64_
 // fine path, the coarse path and the twin are a wave each (they share only the
 // increments), the other waves draw the increments, a generator block of every
 // chain per wave and round, handed over through LDS (two rounds' worth: one
-// barrier a round).  Each path's operations are those of step_group, in order;
+// barrier a round).  Each path's operations are those of advance_group, in order;
 // what a wave computes of the other paths is dead code.
 // mlmc_level of 331 samples, before and after: 16384 Heston steps 1623 -> 528
 // us, 16384 fp64 GBM steps 1290 -> 539 us; 331 Milstein Asian paths of 65536
