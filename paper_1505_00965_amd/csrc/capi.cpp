@@ -127,6 +127,24 @@ LaunchShape default_shape(const mlmc_model& m, const mlmc_payoff& p, int l, int 
             if (s.ppt > 1) s.ppt /= 2;
             else s.block /= 2;
         }
+        // A compute unit's blocks run side by side, so a launch that is
+        // resident whole takes as long as its fullest unit: fewer samples per
+        // lane where that unit then holds fewer of them (4% less at least:
+        // what one sample per lane costs over two).  One round of 256 x 2 on
+        // 256 units is 131072 samples; us with two and with one per lane:
+        //   samples            270000       347000       420000       600000
+        //   Heston, 64 steps   46.6  42.4   46.8  47.6   56.7  53.1   67.7  68.9
+        //   GBM lookback, 64   48.5  43.6   48.6  49.3   60.2  55.3   70.6  71.8
+        //   GBM call, 64       27.5  26.2   27.7  28.5   31.6  31.3   35.5  37.0
+        // (shorter paths than 32 steps lose that to the larger number of blocks)
+        if (nf >= 32) {
+            auto per_cu = [&](int ppt) {
+                const uint64_t c = (uint64_t)s.block * ppt, blocks = (units + c - 1) / c;
+                return (blocks + num_cu - 1) / num_cu;
+            };
+            for (int q = s.ppt / 2; q >= 1; q /= 2)
+                if (per_cu(q) * s.block <= 2048 && 104 * per_cu(q) * q < 100 * per_cu(s.ppt) * s.ppt) s.ppt = q;
+        }
     }
     // few chains (paths, or the lanes of split paths): eight waves share 64 of
     // them (process_coop).  Beyond two such blocks a compute unit the waves

@@ -70,3 +70,19 @@ def test_uncoupled_paths_equal_plain_kernel(gctx):
             for k in ("sum_y", "sum_y2", "sum_pf", "sum_pc"):
                 # 300 positive summands in another order
                 assert abs(r[0][k] - r[1][k]) <= 300 * 2.3e-16 * abs(r[1][k])
+
+
+# sample counts on both sides of a change of the default samples per lane
+@pytest.mark.parametrize("kind,l", [(A.GBM, 3), (A.HESTON, 3)])
+@pytest.mark.parametrize("N", [262144, 262145, 327680, 327681, 393217, 458753])
+def test_sums_do_not_depend_on_samples_per_lane(gctx, kind, l, N):
+    m, p = A.model(kind), A.payoff(A.LOOKBACK)
+    r = gctx.mlmc_level(m, p, l, 4, N, 21, path_offset=5)
+    with A.Context(0) as plain:
+        plain.set_launch(256, 2)
+        ref = plain.mlmc_level(m, p, l, 4, N, 21, path_offset=5)
+    assert r["n"] == ref["n"] == N
+    for k, k2 in (("sum_y", "sum_y2"), ("sum_pf", "sum_pf2"), ("sum_pc", "sum_pc2")):
+        # N summands in another order, their absolute sum at most sqrt(N sum x^2)
+        assert abs(r[k] - ref[k]) <= 2 * N * 2.0 ** -53 * (N * ref[k2]) ** 0.5
+        assert abs(r[k2] - ref[k2]) <= 2 * N * 2.0 ** -53 * ref[k2]
