@@ -35,20 +35,6 @@ __device__ inline void optimal_n_dev(int L, const double* V, const double* C, do
     for (int l = 0; l <= L; ++l) N[l] = ceil(2.0 / (eps * eps) * sqrt(V[l] / C[l]) * total);
 }
 
-__device__ inline double fit_rate_dev(int L, const double* y, int M)
-{
-    double sx = 0, sy = 0, sxx = 0, sxy = 0;
-    int n = 0;
-    const double lm = log((double)M);
-    for (int l = 1; l <= L; ++l) {
-        if (!(y[l] > 0)) continue;
-        const double x = l, v = log(y[l]) / lm;
-        sx += x; sy += v; sxx += x * x; sxy += x * v; ++n;
-    }
-    if (n < 2) return nan("");
-    return (n * sxy - sx * sy) / (n * sxx - sx * sx);
-}
-
 // A fresh state in `s` (global or LDS): zeros, the configuration, the pilot
 // batch.  Every thread of the block must call it; it ends with a barrier.
 __device__ __forceinline__ void init_state(DriverState& s, const DriverInit& c)
@@ -84,7 +70,7 @@ __device__ __forceinline__ double lane_f64(double v, int l)
 }
 
 // sum_{k <= L} v_k in level order (the order of the one-lane loops above),
-// so every sum over levels rounds as optimal_n_dev and fit_rate_dev round it.
+// so every sum over levels rounds as a loop over them rounds it.
 __device__ __forceinline__ double ordered_sum(double v, int L)
 {
     double t = 0.0;
