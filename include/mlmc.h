@@ -218,9 +218,10 @@ mlmc_status mlmc_level(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff
  * device array, one per device, held until the process ends; that group
  * serves any N <= 2^40 (MLMC_EINVAL beyond, as for mlmc_level).  Every call
  * on a device uses the same array and clears it at its end (a call after one
- * that failed, at its start too): calls that overlap on one device (other streams, other host
- * threads) race and must be ordered by the caller.  Kernel launches only (no
- * memset or copy nodes), so the call can be captured into a graph.
+ * that failed, and a captured call, at its start too): calls and graph replays
+ * that overlap on one device (other streams, other host threads) race and must
+ * be ordered by the caller.  Kernel launches only (no memset or copy nodes), so
+ * the call can be captured into a graph.
  * err (may be NULL): a caller buffer of err_len bytes that receives the
  * reason of a failure ("" on success).  MLMC_EINVAL for bad arguments,
  * MLMC_EDEVICE for a HIP error (no current device, launch failure).        */

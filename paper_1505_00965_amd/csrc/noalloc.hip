@@ -10,9 +10,10 @@
 // with hipGetSymbolAddress (with that device current) and kept per device.
 // Every call on a device uses that one array: the level kernels add into it,
 // and a one-wave kernel folds it into the caller's device result and clears it
-// for the next call (a fill kernel comes first after a call that failed), all
-// on the caller's stream.  Calls that overlap on
-// one device (other streams, other host threads) race on the array.
+// for the next call, all on the caller's stream.  A fill kernel comes first
+// after a call that failed, and always in a call that is being captured: when
+// its graph will be replayed, and after what, is not known here.  Calls that
+// overlap on one device (other streams, other host threads) race on the array.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -35,7 +36,7 @@ constexpr int kMaxDevices = 64;
 
 struct DeviceScratch {
     std::atomic<int> ready{0};   // 1: ptr and num_cu are set
-    std::atomic<int> dirty{0};   // 1: a call's fold was not enqueued
+    std::atomic<int> dirty{0};   // 1: a call failed, its sums may be in the array
     LevelAcc* ptr = nullptr;     // this device's copy of `scratch`
     int num_cu = 0;
 };
@@ -71,6 +72,16 @@ hipError_t scratch_for(int dev, DeviceScratch** out)
     }
     *out = &d;
     return hipSuccess;
+}
+
+// True if work enqueued on `st` is recorded into a graph (or the runtime
+// cannot say).
+bool is_captured(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 }  // namespace
@@ -146,7 +157,9 @@ extern "C" mlmc_status mlmc_level_noalloc(const mlmc_model* model, const mlmc_pa
     }
     const hipStream_t st = static_cast<hipStream_t>(hip_stream);
     LevelAcc* group = ds->ptr;
-    e = ds->dirty.exchange(1) ? zero_records(group, kScratchRecords, st) : hipSuccess;
+    // A recorded clear has not run, so it does not settle the mark of a failed
+    // call; only an eager one does, and every failure sets it again.
+    e = is_captured(st) || ds->dirty.exchange(0) ? zero_records(group, kScratchRecords, st) : hipSuccess;
     const mlmc_model& m = *model;
     const mlmc_payoff& p = *payoff;
     int nf = 1;
@@ -167,9 +180,9 @@ extern "C" mlmc_status mlmc_level_noalloc(const mlmc_model* model, const mlmc_pa
         e = hipGetLastError();
     }
     if (e != hipSuccess) {
+        ds->dirty.store(1);
         put_err(err, err_len, hipGetErrorString(e));
         return MLMC_EDEVICE;
     }
-    ds->dirty.store(0);
     return MLMC_OK;
 }
