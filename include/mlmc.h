@@ -24,7 +24,9 @@
  *     mlmc_levels_batch, mlmc_rhee_glynn and mlmc_run: they return once the
  *     device has published their sums or the final driver state (with kernel
  *     timing off, work of their own that changes nothing may still be queued;
- *     later work on the stream is ordered after it).
+ *     later work on the stream is ordered after it).  While that stream is
+ *     being captured into a graph they return MLMC_EDEVICE and record nothing
+ *     (mlmc_level_noalloc can be captured).
  *   - random numbers: Philox4x32-10 keyed by the 64-bit seed; sample s of
  *     level l is a pure function of (seed, l, s), so results do not depend on
  *     the launch configuration except for the order of FP64 atomic additions

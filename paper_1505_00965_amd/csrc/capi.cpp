@@ -22,6 +22,16 @@ mlmc_status hip_fail(mlmc_ctx* ctx, hipError_t e, const char* what)
     return fail(ctx, MLMC_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+mlmc_status enter_call(mlmc_ctx* ctx)
+{
+    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    MLMC_HIP(ctx, hipStreamIsCapturing(ctx->stream, &s));
+    if (s != hipStreamCaptureStatusNone)
+        return fail(ctx, MLMC_EDEVICE, "the context's stream is being captured (mlmc_level_noalloc can be captured)");
+    return MLMC_OK;
+}
+
 static int level_steps(int l, int M)
 {
     int nf = 1;
@@ -653,7 +663,7 @@ static mlmc_status level_common(mlmc_ctx* ctx, const mlmc_model* model, const ml
     if (N > (1ull << 40)) return fail(ctx, MLMC_EINVAL, "N too large (max 2^40 per call)");
     if ((path_offset + N) >> 56) return fail(ctx, MLMC_EINVAL, "path index beyond 2^56");
     ctx->err.clear();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     int clean = 0;
     st = claim_records(ctx, 1, &clean);
     if (st) return st;
@@ -698,7 +708,7 @@ mlmc_status mlmc_philox_words(mlmc_ctx* ctx, uint64_t seed, int level, uint64_t 
     if (!ctx) return MLMC_EINVAL;
     if (!d_out && npaths && nblocks) return fail(ctx, MLMC_EINVAL, "d_out must not be NULL");
     if (level < 0 || level > 255) return fail(ctx, MLMC_EINVAL, "level must be in 0..255");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     MLMC_HIP(ctx, launch_philox_words(seed, level, s0, stream, nblocks, npaths, d_out, ctx->stream));
     MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return MLMC_OK;
@@ -711,7 +721,7 @@ mlmc_status mlmc_normals(mlmc_ctx* ctx, uint64_t seed, int level, uint64_t s0, u
     if ((dim != 1 && dim != 2) || nsteps < 0 || (precision != 32 && precision != 64))
         return fail(ctx, MLMC_EINVAL, "dim must be 1 or 2, precision 32 or 64");
     if (!d_out && npaths && nsteps) return fail(ctx, MLMC_EINVAL, "d_out must not be NULL");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     MLMC_HIP(ctx, launch_normals(seed, level, s0, stream, dim, nsteps, npaths, precision, d_out,
                                  ctx->stream));
     MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));

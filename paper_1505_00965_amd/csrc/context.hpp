@@ -92,6 +92,18 @@ mlmc_status hip_fail(mlmc_ctx* ctx, hipError_t e, const char* what);
         if (e__ != hipSuccess) return ::mlmc::hip_fail((ctx), e__, #expr); \
     } while (0)
 
+// The context's device made current for a call that returns results to the
+// host; refused while the context's stream is being captured (recorded work
+// has not run when the call would read its results, and what the context notes
+// as done -- an uploaded descriptor, a table, zeroed buffers -- would not be).
+mlmc_status enter_call(mlmc_ctx* ctx);
+
+#define MLMC_ENTER(ctx)                                              \
+    do {                                                             \
+        const mlmc_status s__ = ::mlmc::enter_call(ctx);             \
+        if (s__ != MLMC_OK) return s__;                              \
+    } while (0)
+
 // Argument validation shared by the level entry points.
 // Path steps per sample of level l (n_f + n_c; 2 n_f + n_c with the twin).
 double level_cost(const mlmc_model& m, int l, int M);

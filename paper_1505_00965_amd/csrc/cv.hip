@@ -466,7 +466,7 @@ mlmc_status mlmc_cv_create(mlmc_ctx* ctx, int in_dim, int hidden, uint64_t init_
     *out = nullptr;
     if ((in_dim != 2 && in_dim != 3) || hidden != H)
         return fail(ctx, MLMC_EINVAL, "in_dim must be 2 (GBM) or 3 (Heston) and hidden 64");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     mlmc_cv* cv = new (std::nothrow) mlmc_cv();
     if (!cv) return fail(ctx, MLMC_ENOMEM, "host allocation failed");
     cv->ctx = ctx;
@@ -501,7 +501,7 @@ mlmc_status mlmc_cv_get_params(const mlmc_cv* cv, float* host, size_t n)
     if (!cv) return MLMC_EINVAL;
     mlmc_ctx* ctx = cv->ctx;
     if (!host || n != (size_t)cv->np) return fail(ctx, MLMC_EINVAL, "need a host array of nparams floats");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     MLMC_HIP(ctx, hipMemcpyAsync(host, cv->d_params, sizeof(float) * n, hipMemcpyDeviceToHost,
                                  ctx->stream));
     MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -515,7 +515,7 @@ mlmc_status mlmc_cv_set_params(mlmc_cv* cv, const float* host, size_t n)
     if (!host || n != (size_t)cv->np) return fail(ctx, MLMC_EINVAL, "need a host array of nparams floats");
     for (size_t i = 0; i < n; ++i)
         if (!std::isfinite(host[i])) return fail(ctx, MLMC_EINVAL, "parameters must be finite");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     MLMC_HIP(ctx, hipMemcpyAsync(cv->d_params, host, sizeof(float) * n, hipMemcpyHostToDevice,
                                  ctx->stream));
     MLMC_HIP(ctx, cv_prepare(cv, ctx->stream));
@@ -550,7 +550,7 @@ mlmc_status mlmc_cv_get_table(mlmc_cv* cv, const mlmc_model* model, float* host,
     }
     if (!host) return MLMC_OK;
     if (n != table_size(g)) return fail(ctx, MLMC_EINVAL, "need a host array of rows * nv * ns floats");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     MLMC_HIP(ctx, cv_ensure_table(cv, *model, ctx->stream));
     MLMC_HIP(ctx, hipMemcpyAsync(host, cv->d_table, sizeof(float) * n, hipMemcpyDeviceToHost,
                                  ctx->stream));

@@ -921,7 +921,7 @@ mlmc_status mlmc_cv_loss_grad(mlmc_cv* cv, const mlmc_model* model, const mlmc_p
     mlmc_status st = check_train_args(cv, model, payoff, M, lmax, batch);
     if (st) return st;
     ctx->err.clear();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     TrainPlan t;
     st = plan_train(cv, *model, *payoff, M, lmax, batch, seed, 1, &t);
     if (!st) st = enqueue_loss_grad(cv, t, step, 0, 1, nullptr, nullptr);
@@ -949,7 +949,7 @@ mlmc_status mlmc_cv_train(mlmc_cv* cv, const mlmc_model* model, const mlmc_payof
     if (st) return st;
     if (steps < 0 || !(lr > 0)) return fail(ctx, MLMC_EINVAL, "need steps >= 0 and lr > 0");
     ctx->err.clear();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     double* d_hist = nullptr;
     if (loss_hist && steps > 0) MLMC_HIP(ctx, hipMalloc(&d_hist, sizeof(double) * steps));
     AdamArgs adam{cv->d_params, cv->d_m1, cv->d_m2, cv->d_afwd, cv->d_abwd, (float)lr,

@@ -135,7 +135,7 @@ mlmc_status mlmc_optimal_n(mlmc_ctx* ctx, int L, const double* V, const double* 
         return fail(ctx, MLMC_EINVAL, "need 0 <= L < 16, eps > 0 and non-NULL arrays");
     for (int l = 0; l <= L; ++l)
         if (!(V[l] >= 0) || !(C[l] > 0)) return fail(ctx, MLMC_EINVAL, "need V >= 0 and C > 0");
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     const size_t n = (size_t)(L + 1);
     double* dV = ctx->d_tmp;
     double* dC = ctx->d_tmp + MLMC_MAX_LEVELS;
@@ -178,7 +178,7 @@ mlmc_status mlmc_run(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* 
     ctx->err.clear();
     const TraceRange run_range("mlmc_run");
     const auto t0 = std::chrono::steady_clock::now();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     st = ensure_driver(ctx);
     if (st) return st;
     DriverState* h = (DriverState*)ctx->h_drv;

@@ -525,7 +525,7 @@ mlmc_status mlmc_levels_batch(mlmc_ctx* ctx, const mlmc_model* model, const mlmc
             return fail(ctx, MLMC_EINVAL, "path index beyond 2^56");
     }
     ctx->err.clear();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     st = ensure_bufs(ctx);
     if (st) return st;
     BatchRequest req;

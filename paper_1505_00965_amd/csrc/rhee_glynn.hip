@@ -120,7 +120,7 @@ mlmc_status mlmc_rhee_glynn(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_p
     if (N == 0 || N > (1ull << 40)) return fail(ctx, MLMC_EINVAL, "N must be in 1..2^40");
     ctx->err.clear();
     const auto t0 = std::chrono::steady_clock::now();
-    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    MLMC_ENTER(ctx);
     std::memset(out, 0, sizeof(*out));
     // the law and its cumulative sums, in the same order as the oracle's
     RgLaw law;
