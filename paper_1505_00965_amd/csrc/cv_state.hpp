@@ -8,6 +8,9 @@
 #include "context.hpp"
 #include "cv.hpp"
 
+// Samples a training chunk holds at least (cv_train.hip).
+constexpr uint64_t kTrainChunk = 32768;
+
 struct mlmc_cv {
     mlmc_ctx* ctx = nullptr;
     int D = 2;                    // network inputs
@@ -33,6 +36,7 @@ struct mlmc_cv {
     // training scratch: one allocation, cut up by each step (cv_train.hip)
     char* d_train = nullptr;
     size_t train_cap = 0;         // bytes allocated
+    uint64_t train_least = kTrainChunk;   // halved while the device refuses the memory
     double* d_loss = nullptr;     // loss and per-level variances
 };
 

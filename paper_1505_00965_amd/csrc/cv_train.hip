@@ -28,7 +28,14 @@
 // of several Adam steps in one launch (as many as fit kMaxPoints), whose
 // time is one path's chain of steps whatever their number.  A batch whose
 // points exceed kMaxPoints is worked off in chunks of samples instead (the
-// points of a chunk are made again for the backward pass).
+// points of a chunk are made again for the backward pass), of kTrainChunk
+// samples at least: every chunk takes the deepest level's chain twice, 0.5 ms
+// (Heston 0.9) at 4096 steps however few its samples, and kMaxPoints alone
+// holds 2432 of them there.  Adam step on levels 0..6, M = 4, ms, by
+// kMaxPoints alone, with at least 16384, 32768 and 65536 samples:
+//   16384 samples, GBM   20.9  11.3  11.3  11.3     131072, GBM  175  98  91  88
+//   16384, Heston        27.1  12.4  12.4  12.4     131072, Heston 223 111 100 95
+// 32768 there need 2.7 GB (Heston 3.6) of scratch, kept by the network.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -763,6 +770,29 @@ struct TrainPlan {
     TrainPathsFn paths;
 };
 
+// Samples per chunk (`most` of them at most, rounded down to whole waves), the
+// steps in a group and the backward blocks.
+static void size_chunk(TrainPlan& t, int num_cu, uint64_t most, int nsteps)
+{
+    const TrainArgs& a = t.a;
+    const uint64_t nrows = a.nrows;
+    t.chunk = std::min<uint64_t>(a.Bpad, std::max<uint64_t>(64, most / 64 * 64));
+    const uint64_t pts = std::max<uint64_t>(t.chunk * std::max<uint64_t>(nrows, (uint64_t)a.nlev), 1);
+    t.group = t.chunk < a.B ? 1u
+                            : (uint32_t)std::max<uint64_t>(
+                                  1, std::min<uint64_t>({(uint64_t)nsteps, kMaxPoints / pts, (uint64_t)kMaxSteps}));
+    // backward blocks: the start point's, and beside them what fills the
+    // device's residency (one more would wait for another's end) or a task each
+    // so that both kinds end together: one start block in fifty for
+    // 16384 samples on levels 0..3, one in four on levels 0..1
+    const uint64_t resident = (uint64_t)num_cu * kBwdBlocksPerCu, tasks = nrows * (t.chunk / 64);
+    const uint64_t pairs = t.chunk * a.nlev;
+    const double sc = kStartPairCost * (double)pairs, share = sc / (sc + kTaskCost * (double)tasks);
+    t.ns = (int)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)(share * (double)resident + 0.5),
+                                                          (pairs + 127) / 128, resident / 2}));
+    t.nb = (int)std::min<uint64_t>(tasks, resident - t.ns);
+}
+
 static mlmc_status plan_train(mlmc_cv* cv, const mlmc_model& m, const mlmc_payoff& p, int M, int lmax, uint64_t B,
                               uint64_t seed, int nsteps, TrainPlan* out)
 {
@@ -788,33 +818,28 @@ static mlmc_status plan_train(mlmc_cv* cv, const mlmc_model& m, const mlmc_payof
     a.seed = seed;
     a.S0 = (float)m.S0;
     a.v0 = (float)m.v0;
-    // samples per chunk: whole waves, at most kMaxPoints points (one wave of
-    // the deepest batch is 4.4e5)
-    t.chunk = a.Bpad;
-    if (t.chunk * nrows > kMaxPoints) t.chunk = std::max<uint64_t>(64, kMaxPoints / nrows / 64 * 64);
-    const uint64_t pts = std::max<uint64_t>(t.chunk * std::max<uint64_t>(nrows, (uint64_t)a.nlev), 1);
-    t.group = t.chunk < B ? 1u
-                          : (uint32_t)std::max<uint64_t>(
-                                1, std::min<uint64_t>({(uint64_t)nsteps, kMaxPoints / pts, (uint64_t)kMaxSteps}));
-    // backward blocks: the start point's, and beside them what fills the
-    // device's residency (one more would wait for another's end) or a task each
-    // so that both kinds end together: one start block in fifty for
-    // 16384 samples on levels 0..3, one in four on levels 0..1
-    const uint64_t resident = (uint64_t)ctx->num_cu * kBwdBlocksPerCu, tasks = nrows * (t.chunk / 64);
-    const uint64_t pairs = t.chunk * a.nlev;
-    const double sc = kStartPairCost * (double)pairs, share = sc / (sc + kTaskCost * (double)tasks);
-    t.ns = (int)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)(share * (double)resident + 0.5),
-                                                          (pairs + 127) / 128, resident / 2}));
-    t.nb = (int)std::min<uint64_t>(tasks, resident - t.ns);
-    t.s = cut_scratch(nullptr, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + t.ns, t.group);
-    if (cv->train_cap < t.s.bytes) {
+    // Samples per chunk: whole waves, as many as fit kMaxPoints, but kTrainChunk
+    // at least while the memory is there (halved on each refusal, for the
+    // network's later steps as well).
+    for (;; cv->train_least /= 2) {
+        const uint64_t least = cv->train_least;
+        size_chunk(t, ctx->num_cu, std::max<uint64_t>(least, kMaxPoints / std::max<uint64_t>(nrows, 1)), nsteps);
+        t.s = cut_scratch(nullptr, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + t.ns, t.group);
+        if (cv->train_cap >= t.s.bytes) break;
         // queued launches may still use the old scratch
         MLMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
         if (cv->d_train) hipFree(cv->d_train);
         cv->d_train = nullptr;
         cv->train_cap = 0;
-        MLMC_HIP(ctx, hipMalloc(&cv->d_train, t.s.bytes));
-        cv->train_cap = t.s.bytes;
+        const hipError_t e = hipMalloc(&cv->d_train, t.s.bytes);
+        if (e == hipSuccess) {
+            cv->train_cap = t.s.bytes;
+            break;
+        }
+        cv->d_train = nullptr;
+        if (e != hipErrorOutOfMemory || least <= 64 || t.chunk * nrows <= kMaxPoints)
+            return hip_fail(ctx, e, "training scratch allocation");
+        (void)hipGetLastError();
     }
     t.s = cut_scratch(cv->d_train, nrows, t.chunk, a.nlev, a.Bpad, cv->D, t.nb + t.ns, t.group);
     a.x1 = t.s.x1;
