@@ -196,6 +196,20 @@ mlmc_status mlmc_autotune(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_pay
 mlmc_status mlmc_tuned_shape(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoff,
                              int l, int M, int precision, int* block, int* ppt);
 
+/* The launch that mlmc_level makes for N samples with this context's present
+ * shapes (mlmc_set_launch, the tuner, else the default), without making it. */
+typedef struct {
+    int block, ppt;      /* threads per block, samples per lane */
+    int split;           /* lanes per path (GBM paths too few to fill the device) */
+    int few_chains;      /* 1: the kernel for few long chains (paths, or the lanes
+                            of split paths), eight waves to 64 of them: chosen from
+                            N, never under a fixed shape */
+    int grid;            /* blocks */
+    int resident;        /* blocks of the kernel that a compute unit holds at once */
+} mlmc_launch_shape;
+mlmc_status mlmc_level_shape(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoff, int l, int M,
+                             uint64_t N, int precision, mlmc_launch_shape* out);
+
 /* Level estimator sums (eqs. (eq:mlmc:Yzero), (eq:Yldef)).
  *   l >= 0, M in {2, 4}, M^l <= 4^8 * 4 (262144 steps), N >= 0 paths
  *   seed: Philox key; path_offset: index of the first sample, so further

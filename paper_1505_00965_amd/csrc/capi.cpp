@@ -649,6 +649,25 @@ mlmc_status mlmc_set_launch(mlmc_ctx* ctx, int block, int ppt)
     return MLMC_OK;
 }
 
+mlmc_status mlmc_level_shape(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoff, int l, int M,
+                             uint64_t N, int precision, mlmc_launch_shape* out)
+{
+    if (!out) return fail(ctx, MLMC_EINVAL, "out must not be NULL");
+    const mlmc_status st = check_level_args(ctx, model, payoff, l, M, precision);
+    if (st) return st;
+    if (N > (1ull << 40)) return fail(ctx, MLMC_EINVAL, "N too large (max 2^40 per call)");
+    MLMC_HIP(ctx, hipSetDevice(ctx->device));
+    const LaunchShape s = choose_shape(ctx, *model, *payoff, l, M, precision, N);
+    out->block = s.block;
+    out->ppt = s.ppt;
+    out->split = s.split;
+    out->few_chains = s.coop;
+    out->resident = level_resident(*model, *payoff, M, precision, level_steps(l, M), s);
+    out->grid = s.grid;
+    if (s.num_cu > 0 && out->resident > 0) out->grid = std::min(s.grid, s.num_cu * out->resident);
+    return MLMC_OK;
+}
+
 static mlmc_status level_common(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoff,
                                 int l, int M, uint64_t N, uint64_t seed, uint64_t path_offset,
                                 int precision, const mlmc_cv* cv, double* d_pf, double* d_pc,

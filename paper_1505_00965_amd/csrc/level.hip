@@ -104,6 +104,14 @@ static dim3 resident_grid(const void* fn, const LaunchShape& shape)
     return dim3(g);
 }
 
+int level_resident(const mlmc_model& m, const mlmc_payoff& p, int M, int precision, int nf,
+                   const LaunchShape& shape)
+{
+    const void* fn = precision == 64 ? (const void*)pick<double>(m, p.kind, M, 1, nf, false, shape.coop)
+                                     : (const void*)pick<float>(m, p.kind, M, shape.ppt, nf, shape.split > 1, shape.coop);
+    return resident_blocks(fn, shape.block);
+}
+
 hipError_t launch_level(const mlmc_model& m, const mlmc_payoff& p, int M, int precision,
                         const void* args, LaunchShape shape, hipStream_t stream, hipEvent_t start,
                         hipEvent_t stop)

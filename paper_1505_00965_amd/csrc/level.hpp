@@ -117,4 +117,9 @@ hipError_t launch_level(const mlmc_model& m, const mlmc_payoff& p, int M, int pr
                         const void* args, LaunchShape shape, hipStream_t stream,
                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
+// Blocks of the kernel that launch_level takes for this shape that a compute
+// unit holds at once (0 if the runtime cannot say).
+int level_resident(const mlmc_model& m, const mlmc_payoff& p, int M, int precision, int nf,
+                   const LaunchShape& shape);
+
 }  // namespace mlmc

@@ -27,7 +27,7 @@ EXPORTED = [
     "mlmc_autotune_persistent",
     "mlmc_tuned_shape", "mlmc_rhee_glynn", "mlmc_set_timing_mask", "mlmc_level_noalloc",
     "mlmc_cv_set_tabulated", "mlmc_cv_get_table", "mlmc_set_timing_stride", "mlmc_autotune_run",
-    "mlmc_set_timing_paused",
+    "mlmc_set_timing_paused", "mlmc_level_shape",
 ]
 STAT_SLOTS = 20
 STAT_PERSISTENT, STAT_DRIVER, STAT_CV_TRAIN = 16, 17, 18
@@ -54,6 +54,14 @@ class LevelResult(C.Structure):
     _fields_ = [("sum_y", C.c_double), ("sum_y2", C.c_double), ("sum_pf", C.c_double),
                 ("sum_pf2", C.c_double), ("sum_pc", C.c_double), ("sum_pc2", C.c_double),
                 ("cost", C.c_double), ("n", C.c_uint64), ("n_nonfinite", C.c_uint64)]
+
+    def as_dict(self):
+        return {k: getattr(self, k) for k, _ in self._fields_}
+
+
+class LaunchShape(C.Structure):
+    _fields_ = [("block", C.c_int), ("ppt", C.c_int), ("split", C.c_int), ("few_chains", C.c_int),
+                ("grid", C.c_int), ("resident", C.c_int)]
 
     def as_dict(self):
         return {k: getattr(self, k) for k, _ in self._fields_}
@@ -127,6 +135,7 @@ def lib():
     L.mlmc_last_error.argtypes = [vp]
     L.mlmc_last_error.restype = C.c_char_p
     L.mlmc_set_launch.argtypes = [vp, i32, i32]
+    L.mlmc_level_shape.argtypes = [vp, M_, P_, i32, i32, u64, i32, C.POINTER(LaunchShape)]
     L.mlmc_level.argtypes = [vp, M_, P_, i32, i32, u64, u64, u64, i32, vp, C.POINTER(LevelResult)]
     L.mlmc_level_paths.argtypes = [vp, M_, P_, i32, i32, u64, u64, u64, i32, vp, vp, vp,
                                    C.POINTER(LevelResult)]
@@ -306,6 +315,12 @@ class Context:
 
     def set_launch(self, block=0, ppt=0):
         self._check(self._lib.mlmc_set_launch(self.h, block, ppt))
+
+    def level_shape(self, m, p, l, M, N, precision=32):
+        """The launch mlmc_level makes for N samples (nothing is launched)."""
+        r = LaunchShape()
+        self._check(self._lib.mlmc_level_shape(self.h, C.byref(m), C.byref(p), l, M, N, precision, C.byref(r)))
+        return r.as_dict()
 
     def mlmc_level(self, m, p, l, M, N, seed, path_offset=0, precision=32, cv=None,
                    allow_nonfinite=False):
