@@ -84,6 +84,18 @@ static bool split_eligible(const mlmc_model& m, const mlmc_payoff& p, int precis
     return precision == 32 && m.kind == MLMC_GBM && !m.antithetic && p.kind != MLMC_DIGITAL_COND;
 }
 
+// Blocks of the few-chains kernel that a compute unit holds at once, three at
+// most (all the rule below asks for): by its registers and LDS two fit for
+// fp64 Heston paths and the fp64 lookback, one for the fp64 conditional digital
+// (but two of Milstein's without the twin).  Known here because the
+// allocation-free entry does not query the runtime.
+static int coop_resident(const mlmc_model& m, const mlmc_payoff& p, int precision)
+{
+    if (precision == 32) return 3;
+    if (p.kind == MLMC_DIGITAL_COND) return m.scheme == MLMC_MILSTEIN && !m.antithetic ? 2 : 1;
+    return m.kind == MLMC_HESTON || p.kind == MLMC_LOOKBACK ? 2 : 3;
+}
+
 LaunchShape choose_shape(const mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int l,
                          int M, int precision, uint64_t N, uint64_t n_call)
 {
@@ -91,7 +103,7 @@ LaunchShape choose_shape(const mlmc_ctx* ctx, const mlmc_model& m, const mlmc_pa
     if (ctx->launch_block || !tuned_shape(ctx, m, p.kind, precision, M, l, &tb, &tp)) tb = tp = 0;
     LaunchShape s = default_shape(m, p, l, M, precision, N, n_call, ctx->num_cu, ctx->launch_block,
                                   ctx->launch_ppt, tb, tp);
-    s.num_cu = ctx->num_cu;
+    if (!s.coop) s.num_cu = ctx->num_cu;
     return s;
 }
 
@@ -167,13 +179,23 @@ LaunchShape default_shape(const mlmc_model& m, const mlmc_payoff& p, int l, int 
     //   GBM fp64, 256 steps   41.4  24.1   43.4  30.4   42.1  35.6   42.6  41.7
     //   Asian split, 64       18.6  17.7   18.5  18.0   18.4  19.7   18.7  22.9
     //   Asian split, 1024     71.5  41.4   72.2  47.3   71.3  63.9   71.7  75.2
-    const uint64_t chains = N * (uint64_t)s.split, per_cu = nf / s.split >= 256 ? 3 : 2;
+    // Three blocks a unit in two rounds of resident ones still gain, in three
+    // rounds they do not, so a variant takes two rounds at most.  256 steps:
+    //   fp64 Heston lookback  131   56.1   134   84.2   132  110
+    //   fp64 cond., GBM       42.0  24.8   43.7  34.2   42.5  43.5
+    //   fp64 cond., twin      44.9  27.0   46.3  38.5   45.6  50.1
+    //   fp64 cond., Heston t. 105   48.4   108   81.2   108  115
+    //   fp64 cond., Milstein  46.0  26.4   47.8  33.3   47.1  39.2
+    const int resident = coop_resident(m, p, precision);
+    const uint64_t chains = N * (uint64_t)s.split, per_cu = nf / s.split >= 256 ? std::min(3, 2 * resident) : 2;
     if (!fixed_block && N > 0 && nf / s.split >= 64 && chains <= (uint64_t)num_cu * 64 * per_cu &&
         (s.split > 1 || !split_eligible(m, p, precision))) {
         s.coop = true;
         s.block = kCoopThreads;
         s.ppt = 1;
-        s.grid = (int)((chains + 63) / 64);
+        // the resident blocks take the rest in turn: a block each, started as
+        // others end, took 122 us for 110 (Heston lookback, 49152 x 256 steps)
+        s.grid = (int)std::min<uint64_t>((chains + 63) / 64, (uint64_t)num_cu * resident);
         s.num_cu = 0;
         return s;
     }

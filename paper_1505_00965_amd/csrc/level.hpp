@@ -98,7 +98,8 @@ int sampler_variant(const mlmc_model& m);
 // Launch shape actually used.  `grid` is an upper bound: the launcher lowers
 // it to the number of blocks the device holds at once for the chosen kernel
 // (num_cu compute units, 0 = no cap), so that no block waits for another to
-// finish and the grid-stride loop gives every resident block the same share.
+// finish and the grid-stride loop gives every resident block the same share
+// (the few-chains kernel's grid is capped by its rule, num_cu 0).
 struct LaunchShape {
     int block, ppt, grid;
     int num_cu = 0;

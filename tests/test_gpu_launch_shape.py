@@ -54,6 +54,30 @@ def test_thresholds_of_few_chains(gctx, kind, anti, pay, l, prec, per_cu):
     assert s["few_chains"] == 0
 
 
+# as many blocks a compute unit as can be resident in two rounds: by its
+# registers one block of the fp64 conditional digital fits, but for Milstein's
+# without the twin; every other variant holds two at least
+@pytest.mark.parametrize("kind,scheme,anti", [(A.GBM, 0, 0), (A.GBM, 0, 1), (A.GBM, 1, 0), (A.GBM, 1, 1),
+                                              (A.HESTON, 0, 0), (A.HESTON, 0, 1)])
+@pytest.mark.parametrize("pay", [A.CALL, A.ASIAN, A.LOOKBACK, A.DIGITAL, A.DIGITAL_COND])
+@pytest.mark.parametrize("prec", [32, 64])
+@pytest.mark.parametrize("M,l,most", [(4, 3, 2), (4, 4, 3), (2, 10, 3)])
+def test_few_chains_within_two_rounds(gctx, kind, scheme, anti, pay, prec, M, l, most):
+    m, p, cu = A.model(kind, scheme=scheme, antithetic=anti), A.payoff(pay), cus()
+    for blocks in (1, 2, 3):
+        N = 64 * cu * blocks
+        s = gctx.level_shape(m, p, l, M, N, prec)
+        if s["split"] > 1 or prec == 32 and kind == A.GBM and not anti and pay != A.DIGITAL_COND:
+            continue                            # decided by the split paths' lanes
+        assert s["resident"] >= 1
+        if s["few_chains"]:
+            assert blocks <= min(most, 2 * s["resident"]), (blocks, s)
+            # capped at the blocks that fit, as the rule knows without asking
+            assert s["grid"] == cu * min(blocks, s["resident"]), (blocks, s)
+        else:
+            assert blocks > 2, (blocks, s)
+
+
 @pytest.mark.parametrize("kind", [A.GBM, A.HESTON])
 def test_samples_per_lane(gctx, kind):
     # 256 threads with two samples a lane: 512 samples a block
