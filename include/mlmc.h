@@ -289,13 +289,21 @@ mlmc_status mlmc_levels_batch(mlmc_ctx* ctx, const mlmc_model* model, const mlmc
                               int npayoffs, int M, int L, const uint64_t* N,
                               const uint64_t* offsets, uint64_t seed, mlmc_level_result* out);
 /* Launch shape of the persistent kernel: block in {64..1024}, ppt in
- * {1,2,4}, blocks_per_cu resident blocks per compute unit; block = 0 returns
- * to the tuned/default shape.                                               */
+ * {1,2,4}, blocks_per_cu blocks per compute unit, each of which takes part;
+ * block = 0 returns to the tuned/default shape (256 threads, one sample per
+ * lane, five blocks per compute unit, of which small launches use those that
+ * are resident at once).                                                    */
 mlmc_status mlmc_set_persistent_launch(mlmc_ctx* ctx, int block, int ppt, int blocks_per_cu);
+/* The persistent launch of a batch (or of a run: one payoff, L = L_max; cv: a
+ * tabulated control variate or NULL) with the present shape, without making
+ * it; resident: the blocks per compute unit that small launches use (split 1,
+ * few_chains 0).                                                            */
+mlmc_status mlmc_persistent_shape(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoffs,
+                                  int npayoffs, int M, int L, const mlmc_cv* cv, mlmc_launch_shape* out);
 
 /* Autotuner of the persistent form: times mlmc_levels_batch for these
  * payoffs, M and L at N_l = 2^24 M^-l (at least 1) for every block size
- * {128, 256, 512} x samples per lane {1, 2, 4} x resident blocks per compute
+ * {128, 256, 512} x samples per lane {1, 2, 4} x blocks per compute
  * unit {2, 4, 8} with at most 2048 threads per compute unit (median of three
  * after a first run) and sets the fastest with mlmc_set_persistent_launch.
  * Results do not depend on the shape (see determinism above).  Cached like

@@ -3,6 +3,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <tuple>
 #include <utility>
 
 #include <hip/hip_ext.h>
@@ -74,19 +75,16 @@ static KernelFn<Real> pick(const mlmc_model& m, int payoff, int M, int ppt, int 
     }
 }
 
-// Blocks of `fn` with `block` threads that one compute unit holds at once
-// (its register count decides), cached per kernel and block size; 0 if the
-// runtime cannot say.
-static int resident_blocks(const void* fn, int block)
+int resident_blocks(const void* fn, int block, size_t lds)
 {
     static std::mutex mu;
-    static std::map<std::pair<const void*, int>, int> cache;
+    static std::map<std::tuple<const void*, int, size_t>, int> cache;
     std::lock_guard<std::mutex> lock(mu);
-    const auto key = std::make_pair(fn, block);
+    const auto key = std::make_tuple(fn, block, lds);
     const auto it = cache.find(key);
     if (it != cache.end()) return it->second;
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, 0) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, lds) != hipSuccess) {
         (void)hipGetLastError();
         n = 0;
     }

@@ -118,6 +118,9 @@ hipError_t launch_level(const mlmc_model& m, const mlmc_payoff& p, int M, int pr
                         const void* args, LaunchShape shape, hipStream_t stream,
                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
+// Blocks of `fn` with `block` threads and `lds` bytes of dynamic LDS that one
+// compute unit holds at once, cached; 0 if the runtime cannot say.
+int resident_blocks(const void* fn, int block, size_t lds = 0);
 // Blocks of the kernel that launch_level takes for this shape that a compute
 // unit holds at once (0 if the runtime cannot say).
 int level_resident(const mlmc_model& m, const mlmc_payoff& p, int M, int precision, int nf,

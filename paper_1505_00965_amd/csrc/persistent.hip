@@ -6,8 +6,8 @@
 // orders of magnitude: level l costs M^l + M^(l-1) steps per sample (the
 // paper's cost measure, Sec. 3) and N_l falls with l.  A plan kernel cuts the
 // outstanding samples into items of roughly equal cost, deepest levels first
-// (longest-processing-time order), and a resident grid of blocks takes items
-// (block b item b first, then from its group's counter) until none are left, so
+// (longest-processing-time order), and a grid that about fills the device takes
+// items (block b item b first, then from its group's counter) until none are left, so
 // cheap levels fill in around the long deep-level items.  GBM levels with too few paths to fill the
 // device run each path on several lanes (process_split), with the per-level
 // launch's rule on the level's count.  The problem's parameters live in
@@ -18,6 +18,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(512) void driver_update_plan_kernel(DriverState* st
     // only the plan reads the descriptor's fields, at the end: taking them
     // into registers here keeps their loads beside the others
     asm volatile("" ::"s"(pa.L), "s"(pa.M), "s"(pa.nslots), "s"(pa.dim), "s"(pa.split_ok), "s"(pa.num_cu),
-                 "s"(pa.resident_blocks), "s"(pa.chunk), "s"(pa.block), "s"(pa.cond_slots), "s"(pa.plan),
+                 "s"(pa.grid_blocks), "s"(pa.fit_blocks), "s"(pa.chunk), "s"(pa.block), "s"(pa.cond_slots), "s"(pa.plan),
                  "s"(pa.head), "s"(pa.split));
     // the sums of each group, in record order as the per-level form folds them
     y0 = wave_sum(y0);
@@ -193,18 +194,26 @@ struct PersistentBufs {
 static PersistentBufs* bufs_of(mlmc_ctx* ctx);
 
 struct PersistentShape {
-    int block, ppt, blocks_per_cu;
+    int block, ppt, blocks_per_cu, fit_per_cu;
 };
 
-static PersistentShape persistent_shape(const mlmc_ctx* ctx)
+static int persistent_ppt(const mlmc_ctx* ctx) { return ctx->persist_ppt ? ctx->persist_ppt : 1; }
+
+// The launch of sampler `fn` with `lds` bytes of dynamic LDS: the shape that
+// was set, or five blocks of 256 per compute unit -- 346 us for the estimate
+// at RMSE 2e-5 S0 against 353 with four and 366 with eight -- and how many of
+// those a unit holds at once (see kItems).
+static PersistentShape persistent_shape(const mlmc_ctx* ctx, PersistentFn fn, size_t lds)
 {
     PersistentShape s;
     s.block = ctx->persist_block ? ctx->persist_block : 256;
-    s.ppt = ctx->persist_ppt ? ctx->persist_ppt : 1;
-    // five blocks of 256 per compute unit: 346 us for the estimate at RMSE
-    // 2e-5 S0 against 353 with four and 366 with eight; four payoffs 1.91-1.92
-    // ms with any of them
-    s.blocks_per_cu = ctx->persist_bpc ? ctx->persist_bpc : 5;
+    s.ppt = persistent_ppt(ctx);
+    s.blocks_per_cu = s.fit_per_cu = ctx->persist_bpc;
+    if (!s.blocks_per_cu) {
+        const int fit = resident_blocks((const void*)fn, s.block, lds);
+        s.blocks_per_cu = 5;
+        s.fit_per_cu = fit > 0 ? std::min(fit, 5) : 5;
+    }
     return s;
 }
 
@@ -263,11 +272,11 @@ void free_persistent(mlmc_ctx* ctx)
 // Fill the host copy of the descriptor (parameters for every slot and level).
 // A driver run passes the fresh state's configuration and its own
 // dispensers (`head`); a batch passes nullptr and the batch's.
-static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const mlmc_model& m, const mlmc_payoff* p,
-                      int np, int L, int M, LevelAcc* acc, unsigned* head, const DriverInit* init)
+static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const PersistentShape& s, const mlmc_model& m,
+                      const mlmc_payoff* p, int np, int L, int M, LevelAcc* acc, unsigned* head,
+                      const DriverInit* init)
 {
     auto* b = bufs_of(ctx);
-    const PersistentShape s = persistent_shape(ctx);
     std::memset(h, 0, sizeof(*h));
     h->nslots = np;
     h->L = L;
@@ -280,7 +289,8 @@ static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const mlmc_model& m, const ml
     h->acc = acc;
     h->plan = b->d_plan;
     h->head = head;
-    h->resident_blocks = (unsigned)(ctx->num_cu * s.blocks_per_cu);
+    h->grid_blocks = (unsigned)(ctx->num_cu * s.blocks_per_cu);
+    h->fit_blocks = (unsigned)(ctx->num_cu * s.fit_per_cu);
     h->chunk = (unsigned)(s.block * s.ppt);
     h->split = b->d_split;
     h->split_ok = m.kind == MLMC_GBM && !m.antithetic;
@@ -329,26 +339,32 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
     mlmc_status st = ensure_bufs(ctx);
     if (st) return st;
     auto* b = bufs_of(ctx);
-    // the seed goes in with each launch: runs of one problem share the
-    // descriptor's bytes and upload it once.  Driver runs have dispensers
-    // of their own, which their plans leave at zero.
-    fill_desc(ctx, b->h_desc, m, &p, 1, o.L_max, o.M, ctx->d_drv_spread, b->d_counters + kHeads * kHeadStride,
-              &init);
+    const auto sampler = pick_persistent(sampler_variant(m), o.M, persistent_ppt(ctx), p.kind, o.cv != nullptr);
+    if (!sampler) return fail(ctx, MLMC_EINVAL, "no persistent sampler for this model and payoff");
+    const float *cv_table = nullptr, *cv_phi0 = nullptr;
+    TableSpec cv_spec{};
     size_t lds = 0;
     if (o.cv) {
         int max_nf = 1;
         for (int l = 0; l < o.L_max; ++l) max_nf *= o.M;
-        const hipError_t e = cv_table_view(o.cv, m, ctx->stream, max_nf, &b->h_desc->cv_table,
-                                           &b->h_desc->cv_spec, &b->h_desc->cv_phi0, &lds);
+        const hipError_t e = cv_table_view(o.cv, m, ctx->stream, max_nf, &cv_table, &cv_spec, &cv_phi0, &lds);
         if (e != hipSuccess) return hip_fail(ctx, e, "control-variate table");
+    }
+    const PersistentShape s = persistent_shape(ctx, sampler, lds);
+    // the seed goes in with each launch: runs of one problem share the
+    // descriptor's bytes and upload it once.  Driver runs have dispensers
+    // of their own, which their plans leave at zero.
+    fill_desc(ctx, b->h_desc, s, m, &p, 1, o.L_max, o.M, ctx->d_drv_spread,
+              b->d_counters + kHeads * kHeadStride, &init);
+    if (o.cv) {
+        b->h_desc->cv_table = cv_table;
+        b->h_desc->cv_spec = cv_spec;
+        b->h_desc->cv_phi0 = cv_phi0;
         b->h_desc->cv_levels = o.cv_levels;
     }
     bool uploaded = false;
     st = upload_desc(ctx, b, &uploaded);
     if (st) return st;
-    const PersistentShape s = persistent_shape(ctx);
-    const auto sampler = pick_persistent(sampler_variant(m), o.M, s.ppt, p.kind, o.cv != nullptr);
-    if (!sampler) return fail(ctx, MLMC_EINVAL, "no persistent sampler for this model and payoff");
     const dim3 grid(ctx->num_cu * s.blocks_per_cu), block(s.block);
     const BatchDesc* d = b->d_desc;
     DriverState* mirror = (DriverState*)ctx->h_drv_dev;
@@ -422,6 +438,15 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
     return MLMC_OK;
 }
 
+// One payoff kind in every slot: a kernel that holds that payoff's code only.
+static PersistentFn batch_sampler(const mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff* p, int np, int M)
+{
+    int payoff = p[0].kind;
+    for (int k = 1; k < np; ++k)
+        if (p[k].kind != payoff) payoff = kAnyPayoff;
+    return pick_persistent(sampler_variant(m), M, persistent_ppt(ctx), payoff);
+}
+
 // Plan and sample one batch, then publish its groups: three launches (four
 // with a fill launch after a call that failed) on the context's stream, the
 // seed and the request in their arguments, so batches of one problem upload
@@ -434,14 +459,11 @@ static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payo
     auto* b = bufs_of(ctx);
     // a batch rewrites the plan table: a driver run's prepared start is gone
     ctx->drv_pilot_ready = false;
-    fill_desc(ctx, b->h_desc, m, p, np, L, M, b->d_acc, b->d_counters, nullptr);
+    const PersistentFn sampler = batch_sampler(ctx, m, p, np, M);
+    const PersistentShape s = persistent_shape(ctx, sampler, 0);
+    fill_desc(ctx, b->h_desc, s, m, p, np, L, M, b->d_acc, b->d_counters, nullptr);
     mlmc_status st = upload_desc(ctx, b);
     if (st) return st;
-    const PersistentShape s = persistent_shape(ctx);
-    // one payoff kind in every slot: the kernel holds that payoff's code only
-    int payoff = p[0].kind;
-    for (int k = 1; k < np; ++k)
-        if (p[k].kind != payoff) payoff = kAnyPayoff;
     if (!b->acc_clean) MLMC_HIP(ctx, zero_records(b->d_acc, kMaxSlots * kMaxLevels * kSpread, ctx->stream));
     b->acc_clean = false;
     const BatchDesc* d = b->d_desc;
@@ -449,8 +471,7 @@ static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payo
     if (counts) hipLaunchKernelGGL(plan_counts_kernel, dim3(1), dim3(64), 0, ctx->stream, d, counts);
     else hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64), 0, ctx->stream, d, *req);
     MLMC_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL(pick_persistent(sampler_variant(m), M, s.ppt, payoff), dim3(ctx->num_cu * s.blocks_per_cu),
-                       dim3(s.block), 0, ctx->stream, d, seed);
+    hipLaunchKernelGGL(sampler, dim3(ctx->num_cu * s.blocks_per_cu), dim3(s.block), 0, ctx->stream, d, seed);
     MLMC_HIP(ctx, hipGetLastError());
     timed_end(ctx, tix);
     static_assert(kMaxSlots * kMaxLevels <= kPublishGroups, "the mirror holds every pair");
@@ -502,6 +523,40 @@ mlmc_status mlmc_set_persistent_launch(mlmc_ctx* ctx, int block, int ppt, int bl
         ctx->persist_ppt = ppt;
         ctx->persist_bpc = blocks_per_cu;
     }
+    return MLMC_OK;
+}
+
+mlmc_status mlmc_persistent_shape(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* payoffs, int npayoffs,
+                                  int M, int L, const mlmc_cv* cv, mlmc_launch_shape* out)
+{
+    if (!ctx) return MLMC_EINVAL;
+    if (!payoffs || !out) return fail(ctx, MLMC_EINVAL, "payoffs and out must not be NULL");
+    if (npayoffs < 1 || npayoffs > kMaxSlots) return fail(ctx, MLMC_EINVAL, "npayoffs must be in 1..4");
+    for (int k = 0; k < npayoffs; ++k) {
+        const mlmc_status st = check_level_args(ctx, model, &payoffs[k], L, M, 32);
+        if (st) return st;
+    }
+    MLMC_ENTER(ctx);
+    PersistentFn fn = batch_sampler(ctx, *model, payoffs, npayoffs, M);
+    size_t lds = 0;
+    if (cv) {
+        fn = pick_persistent(sampler_variant(*model), M, persistent_ppt(ctx), payoffs[0].kind, true);
+        if (!fn || npayoffs != 1 || cv_in_dim(cv) != (model->kind == MLMC_HESTON ? 3 : 2))
+            return fail(ctx, MLMC_EINVAL, "no persistent sampler with this control variate");
+        int max_nf = 1;
+        for (int l = 0; l < L; ++l) max_nf *= M;
+        const float *table, *phi0;
+        TableSpec spec;
+        const hipError_t e = cv_table_view(cv, *model, ctx->stream, max_nf, &table, &spec, &phi0, &lds);
+        if (e != hipSuccess) return hip_fail(ctx, e, "control-variate table");
+    }
+    const PersistentShape s = persistent_shape(ctx, fn, lds);
+    out->block = s.block;
+    out->ppt = s.ppt;
+    out->split = 1;
+    out->few_chains = 0;
+    out->grid = ctx->num_cu * s.blocks_per_cu;
+    out->resident = s.fit_per_cu;
     return MLMC_OK;
 }
 

@@ -13,14 +13,28 @@ namespace mlmc {
 
 constexpr int kMaxSlots = 4;          // payoffs per batch
 constexpr int kPairs = kMaxSlots * kMaxLevels;
-// Items per resident block the plan aims at: four, fewer (down to one) where
-// they would hold less than kSmallItem path steps each, more (up to sixteen)
-// where four hold more than kItemSteps; a pair is cut into at most 256 times
-// as many, or 1024.  An item's decode, parameters and block reduction cost
-// ~3 us: four-payoff batches of 3e9 steps took 2.08 ms with four items per
-// block and 1.91 with sixteen; an estimate's launches (1.4e8 steps, 5 pairs)
-// 353 us in all with four and 375 with eight; a randomised estimate of 8e6
-// steps 50 us with four and 44 with one, a batch of 3e6 steps 67 and 63.
+// Items per block the plan aims at: four, fewer (down to one) where they
+// would hold less than kSmallItem path steps each, more (up to sixteen) where
+// four hold more than kItemSteps; a pair is cut into at most 256 times as many,
+// or 1024.  An item's decode, parameters and block reduction cost ~3 us:
+// four-payoff batches of 3e9 steps took 2.08 ms with four items per block and
+// 1.91 with sixteen; an estimate's launches (1.4e8 steps, 5 pairs) 353 us in
+// all with four and 375 with eight; a randomised estimate of 8e6 steps 50 us
+// with four and 44 with one, a batch of 3e6 steps 67 and 63.
+//
+// The grid is five blocks a compute unit, of which four fit at once where a
+// block takes more than 96 registers a lane (M = 2, batches of several payoff
+// kinds, Heston lookback) or 32 KB of LDS (the tabulated control variate); the
+// others start as blocks end.  In a plan of fewer than kItems items a block the
+// item of such a block would be a second round of the launch: the items are cut
+// for the blocks that fit, and the others leave.  us with every block taking an
+// item and so:
+//   batch of 1e6 samples, lookback, lookback and Asian       46.4  43.0   68.2  65.1
+//   tabulated GBM, M = 2, RMSE 1e-4 S0, call and Asian       158   149    236   223
+// With more items each, the blocks that come later take theirs at the end,
+// where the deep levels' items, shorter than their steps say, close the launch
+// better than level 0's; grids of four took 554 -> 575 us (GBM call, M = 2,
+// RMSE 2e-5 S0) and 2330 -> 2408 (Heston lookback, M = 2, 5e-5).
 constexpr double kItems = 4.0, kItemsMost = 16.0, kItemSteps = 65536.0, kSmallItem = 8192.0;
 // Dispensers: blocks and items are dealt to groups by their number modulo
 // kHeads, and the items past the first per block come from the group's own
@@ -49,7 +63,7 @@ struct PlanTable {
     unsigned start[kPairs + 1];
     int npairs;
     uint8_t slot[kPairs], level[kPairs];
-    uint32_t pad[1];
+    unsigned own;       // blocks that work: block b < own takes item b first
 };
 static_assert(sizeof(PlanTable) % 8 == 0, "copied in 8-byte words");
 
@@ -62,8 +76,9 @@ struct BatchDesc {
     StepParams<float> params[kMaxSlots][kMaxLevels];
     LevelAcc* acc;                    // spread groups [slot][level][kSpread]
     PlanTable* plan;                  // written by the plan, read by the sampler
-    unsigned* head;                   // dispensers of the items past the first gridDim.x
-    unsigned resident_blocks;         // grid size of the sampler
+    unsigned* head;                   // dispensers of the items past the first one per block
+    unsigned grid_blocks;             // grid size of the sampler
+    unsigned fit_blocks;              // those of them that the device holds at once
     unsigned chunk;                   // blockDim * PPT of the sampler
     unsigned block;                   // blockDim of the sampler
     unsigned* split;                  // lanes per path per (slot, level), set by the plan
@@ -231,7 +246,7 @@ __device__ __forceinline__ void run_item(const BatchDesc* d, uint64_t seed, cons
 // kernel's start, so the loads overlap the kernel's other reads.
 struct PlanArgs {
     int L, M, nslots, dim, split_ok, num_cu;
-    unsigned resident_blocks, chunk, block;
+    unsigned grid_blocks, fit_blocks, chunk, block;
     unsigned cond_slots;              // bit k: slot k holds the conditional digital
     PlanTable* plan;
     unsigned* head;
@@ -247,7 +262,8 @@ __device__ __forceinline__ PlanArgs plan_args(const BatchDesc* d)
     a.dim = d->dim;
     a.split_ok = d->split_ok;
     a.num_cu = d->num_cu;
-    a.resident_blocks = d->resident_blocks;
+    a.grid_blocks = d->grid_blocks;
+    a.fit_blocks = d->fit_blocks;
     a.chunk = d->chunk;
     a.block = d->block;
     a.cond_slots = 0;
@@ -292,10 +308,11 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
     // samples x steps over the batch (lane 0's sum: the rotations leave
     // other lanes with other association orders)
     const double total = __shfl(wave_sum(valid ? dn * per : 0.0), 0);
-    const double steps = total / a.resident_blocks;     // per block
-    const double per_block = steps < kItems * kSmallItem ? fmax(steps / kSmallItem, 1.0)
-                                                         : fmin(fmax(steps / kItemSteps, kItems), kItemsMost);
-    const double target = total / (a.resident_blocks * per_block);
+    const bool few = total < kItems * kSmallItem * a.grid_blocks;   // items
+    const unsigned own = few ? a.fit_blocks : a.grid_blocks;
+    const double steps = total / own;                   // per block
+    const double per_block = few ? fmax(steps / kSmallItem, 1.0) : fmin(fmax(steps / kItemSteps, kItems), kItemsMost);
+    const double target = total / (own * per_block);
     const uint64_t most = (uint64_t)fmax(256.0 * per_block, 1024.0);
     const uint64_t left = (uint64_t)dn;
     const uint64_t first = valid ? (uint64_t)off[s * kMaxLevels + l] : 0;
@@ -363,6 +380,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
         const int np = __popcll(active);
         t->start[np] = incl;
         t->npairs = np;
+        t->own = own;
     }
     if (a.head && p < kHeads) a.head[p * kHeadStride] = 0;
 }
@@ -393,10 +411,10 @@ __device__ __forceinline__ WorkItem plan_item(const PlanTable& t, unsigned it)
     return w;
 }
 
-// Block b takes item b first; later items come from its group's dispenser
-// until that has none left, so a launch with no more items than blocks (an empty one
-// included) makes no atomics on it.  Each item ends with a block reduction
-// into its (payoff, level) spread group.
+// Block b < own takes item b first (the rest take none); later items come from
+// its group's dispenser until that has none left, so a launch with no more items
+// than such blocks (an empty one included) makes no atomics on it.  Each item
+// ends with a block reduction into its (payoff, level) spread group.
 template <int MODEL, int M, int PPT, int PAYOFF, bool CV>
 __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, uint64_t seed)
 {
@@ -411,6 +429,8 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
     }
     int tab_level = -1;
     const unsigned count = __builtin_amdgcn_readfirstlane(s_plan.start[s_plan.npairs]);
+    const unsigned own = __builtin_amdgcn_readfirstlane(s_plan.own);
+    if (blockIdx.x >= own) return;
     for (unsigned it = blockIdx.x; it < count;) {   // block-uniform
         const WorkItem w = wave_uniform(plan_item(s_plan, it));
         double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
@@ -433,11 +453,11 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
         if (w.level == 0) copy_y_sums(sums);
         block_reduce_add(sums, nonfinite, &d->acc[(w.slot * kMaxLevels + w.level) * kSpread +
                                                   (blockIdx.x & (kSpread - 1))]);
-        if (count <= gridDim.x) break;
+        if (count <= own) break;
         if (threadIdx.x == 0) {
-            // the group's next item: those with its number modulo kHeads, from gridDim.x on
-            const unsigned g = blockIdx.x % kHeads, past = gridDim.x % kHeads;
-            s_item = gridDim.x + (g + kHeads - past) % kHeads + kHeads * atomicAdd(d->head + g * kHeadStride, 1u);
+            // the group's next item: those with its number modulo kHeads, from `own` on
+            const unsigned g = blockIdx.x % kHeads, past = own % kHeads;
+            s_item = own + (g + kHeads - past) % kHeads + kHeads * atomicAdd(d->head + g * kHeadStride, 1u);
         }
         __syncthreads();
         it = __builtin_amdgcn_readfirstlane(s_item);

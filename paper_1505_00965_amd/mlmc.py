@@ -27,7 +27,7 @@ EXPORTED = [
     "mlmc_autotune_persistent",
     "mlmc_tuned_shape", "mlmc_rhee_glynn", "mlmc_set_timing_mask", "mlmc_level_noalloc",
     "mlmc_cv_set_tabulated", "mlmc_cv_get_table", "mlmc_set_timing_stride", "mlmc_autotune_run",
-    "mlmc_set_timing_paused", "mlmc_level_shape",
+    "mlmc_set_timing_paused", "mlmc_level_shape", "mlmc_persistent_shape",
 ]
 STAT_SLOTS = 20
 STAT_PERSISTENT, STAT_DRIVER, STAT_CV_TRAIN = 16, 17, 18
@@ -136,6 +136,7 @@ def lib():
     L.mlmc_last_error.restype = C.c_char_p
     L.mlmc_set_launch.argtypes = [vp, i32, i32]
     L.mlmc_level_shape.argtypes = [vp, M_, P_, i32, i32, u64, i32, C.POINTER(LaunchShape)]
+    L.mlmc_persistent_shape.argtypes = [vp, M_, P_, i32, i32, i32, vp, C.POINTER(LaunchShape)]
     L.mlmc_level.argtypes = [vp, M_, P_, i32, i32, u64, u64, u64, i32, vp, C.POINTER(LevelResult)]
     L.mlmc_level_paths.argtypes = [vp, M_, P_, i32, i32, u64, u64, u64, i32, vp, vp, vp,
                                    C.POINTER(LevelResult)]
@@ -378,6 +379,13 @@ class Context:
         self._check(self._lib.mlmc_levels_batch(self.h, C.byref(m), P, npay, M, L, Na, Oa, seed, R),
                     allow)
         return [[R[k * (L + 1) + l].as_dict() for l in range(L + 1)] for k in range(npay)]
+
+    def persistent_shape(self, m, payoffs, M, L, cv=None):
+        """The persistent launch of a batch or run (nothing is launched)."""
+        r = LaunchShape()
+        arr = (Payoff * len(payoffs))(*payoffs)
+        self._check(self._lib.mlmc_persistent_shape(self.h, C.byref(m), arr, len(payoffs), M, L, _cvh(cv), C.byref(r)))
+        return r.as_dict()
 
     def set_persistent_launch(self, block=0, ppt=0, blocks_per_cu=0):
         self._check(self._lib.mlmc_set_persistent_launch(self.h, block, ppt, blocks_per_cu))
