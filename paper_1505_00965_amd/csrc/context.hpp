@@ -54,7 +54,7 @@ struct mlmc_ctx {
     // updates folded and cleared every group it used)
     bool drv_clean = false;
     // the driver state and the plan table hold a fresh start for the next
-    // device-planned run of the same descriptor (the last call was one, and
+    // device-planned run of the same descriptor (the last run was one, and
     // the update queued past its end prepared it)
     bool drv_pilot_ready = false;
     double* d_tmp = nullptr;                // small fp64 scratch (optimal_n)

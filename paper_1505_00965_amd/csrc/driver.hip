@@ -214,7 +214,7 @@ mlmc_status mlmc_run(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* 
     // When the spread groups are known to hold zeros, the per-level form
     // lets its first update build the state (one launch fewer on the pilot's
     // path), and the device-planned form skips its start kernel if the last
-    // call, a device-planned run, left the next run's start prepared;
+    // run, a device-planned one, left the next run's start prepared;
     // otherwise a kernel clears both first (in the device-planned form, its
     // start kernel).  Until this run ends normally neither is known.
     const bool fused_init = ctx->drv_clean && !o.persistent;

@@ -174,21 +174,29 @@ static PersistentFn pick_persistent(int variant, int M, int ppt, int payoff, boo
     return pick_persistent_variant<kHeston>(M, ppt, payoff, cv);
 }
 
-// Device buffers of the persistent form, owned by the context.
-struct PersistentBufs {
-    char* d_all = nullptr;            // the allocation that holds the device buffers
+// A problem's descriptor and the plan made from it.  Batches and driver runs
+// have one each: a batch between two runs of one problem leaves the plan that
+// the first run's end prepared for the second, and neither uploads again.
+struct PlannedProblem {
     BatchDesc* d_desc = nullptr;
     BatchDesc* h_desc = nullptr;
     PlanTable* d_plan = nullptr;
-    unsigned* d_counters = nullptr;   // head
-    LevelAcc* d_acc = nullptr;        // batch spread groups [kMaxSlots][kMaxLevels][kSpread]
-    bool acc_clean = false;           // they hold zeros (publish_groups clears what it folds)
+    unsigned* d_head = nullptr;       // dispensers
     unsigned* d_split = nullptr;      // lanes per path [kMaxSlots][kMaxLevels]
-    unsigned long long* d_counts = nullptr;   // level draws of a randomised estimate
-    bool counts_clean = false;        // they hold zeros
     BatchDesc last_desc;              // the bytes of the last descriptor upload
     // 0: unknown; 1: the device descriptor holds last_desc
     int desc_state = 0;
+};
+
+// Device buffers of the persistent form, owned by the context.
+struct PersistentBufs {
+    char* d_all = nullptr;            // the allocation that holds the device buffers
+    BatchDesc* h_desc = nullptr;      // both host descriptors
+    PlannedProblem run, batch;
+    LevelAcc* d_acc = nullptr;        // batch spread groups [kMaxSlots][kMaxLevels][kSpread]
+    bool acc_clean = false;           // they hold zeros (publish_groups clears what it folds)
+    unsigned long long* d_counts = nullptr;   // level draws of a randomised estimate
+    bool counts_clean = false;        // they hold zeros
 };
 
 static PersistentBufs* bufs_of(mlmc_ctx* ctx);
@@ -230,21 +238,28 @@ static mlmc_status ensure_bufs(mlmc_ctx* ctx)
         at += (bytes + 255) / 256 * 256;
         return p;
     };
-    const size_t desc = piece(sizeof(BatchDesc)), plan = piece(sizeof(PlanTable));
-    const size_t counters = piece(sizeof(unsigned) * 2 * kHeads * kHeadStride);
-    const size_t split = piece(sizeof(unsigned) * kMaxSlots * kMaxLevels);
+    size_t desc[2], plan[2], head[2], split[2];
+    for (int k = 0; k < 2; ++k) {
+        desc[k] = piece(sizeof(BatchDesc));
+        plan[k] = piece(sizeof(PlanTable));
+        head[k] = piece(sizeof(unsigned) * kHeads * kHeadStride);
+        split[k] = piece(sizeof(unsigned) * kMaxSlots * kMaxLevels);
+    }
     const size_t counts = piece(sizeof(unsigned long long) * kCountCopies * kMaxLevels);
     const size_t acc = piece(sizeof(LevelAcc) * kMaxSlots * kMaxLevels * kSpread);
     hipError_t e = hipMalloc(&b->d_all, at);
-    if (e == hipSuccess) e = hipHostMalloc(&b->h_desc, sizeof(BatchDesc));
-    // the dispensers start at zero (a driver run's plans leave its own there),
-    // and so do the groups and the counts
+    if (e == hipSuccess) e = hipHostMalloc(&b->h_desc, 2 * sizeof(BatchDesc));
+    // the groups and the counts start at zero (the dispensers at each plan)
     if (e == hipSuccess) e = hipMemsetAsync(b->d_all, 0, at, ctx->stream);
     if (e == hipSuccess) {
-        b->d_desc = (BatchDesc*)(b->d_all + desc);
-        b->d_plan = (PlanTable*)(b->d_all + plan);
-        b->d_counters = (unsigned*)(b->d_all + counters);
-        b->d_split = (unsigned*)(b->d_all + split);
+        for (int k = 0; k < 2; ++k) {
+            PlannedProblem& p = k ? b->batch : b->run;
+            p.d_desc = (BatchDesc*)(b->d_all + desc[k]);
+            p.h_desc = b->h_desc + k;
+            p.d_plan = (PlanTable*)(b->d_all + plan[k]);
+            p.d_head = (unsigned*)(b->d_all + head[k]);
+            p.d_split = (unsigned*)(b->d_all + split[k]);
+        }
         b->d_counts = (unsigned long long*)(b->d_all + counts);
         b->d_acc = (LevelAcc*)(b->d_all + acc);
         b->acc_clean = b->counts_clean = true;
@@ -270,13 +285,11 @@ void free_persistent(mlmc_ctx* ctx)
 }
 
 // Fill the host copy of the descriptor (parameters for every slot and level).
-// A driver run passes the fresh state's configuration and its own
-// dispensers (`head`); a batch passes nullptr and the batch's.
-static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const PersistentShape& s, const mlmc_model& m,
-                      const mlmc_payoff* p, int np, int L, int M, LevelAcc* acc, unsigned* head,
-                      const DriverInit* init)
+// A driver run passes the fresh state's configuration, a batch nullptr.
+static void fill_desc(mlmc_ctx* ctx, const PlannedProblem& q, const PersistentShape& s, const mlmc_model& m,
+                      const mlmc_payoff* p, int np, int L, int M, LevelAcc* acc, const DriverInit* init)
 {
-    auto* b = bufs_of(ctx);
+    BatchDesc* h = q.h_desc;
     std::memset(h, 0, sizeof(*h));
     h->nslots = np;
     h->L = L;
@@ -287,12 +300,12 @@ static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const PersistentShape& s, con
         for (int l = 0; l <= L; ++l) h->params[k][l] = make_step_params<float>(m, p[k], l, M);
     }
     h->acc = acc;
-    h->plan = b->d_plan;
-    h->head = head;
+    h->plan = q.d_plan;
+    h->head = q.d_head;
     h->grid_blocks = (unsigned)(ctx->num_cu * s.blocks_per_cu);
     h->fit_blocks = (unsigned)(ctx->num_cu * s.fit_per_cu);
     h->chunk = (unsigned)(s.block * s.ppt);
-    h->split = b->d_split;
+    h->split = q.d_split;
     h->split_ok = m.kind == MLMC_GBM && !m.antithetic;
     h->num_cu = ctx->num_cu;
     h->block = (unsigned)s.block;
@@ -303,17 +316,15 @@ static void fill_desc(mlmc_ctx* ctx, BatchDesc* h, const PersistentShape& s, con
 // context carried the same bytes (repeated runs of one problem skip it: a
 // driver run passes its seed with each launch, not in the descriptor).
 // *uploaded (if given) tells which.
-static mlmc_status upload_desc(mlmc_ctx* ctx, PersistentBufs* b, bool* uploaded = nullptr)
+static mlmc_status upload_desc(mlmc_ctx* ctx, PlannedProblem& q, bool* uploaded = nullptr)
 {
     if (uploaded) *uploaded = false;
-    if (b->desc_state == 1 && std::memcmp(&b->last_desc, b->h_desc, sizeof(BatchDesc)) == 0)
-        return MLMC_OK;
+    if (q.desc_state == 1 && std::memcmp(&q.last_desc, q.h_desc, sizeof(BatchDesc)) == 0) return MLMC_OK;
     if (uploaded) *uploaded = true;
-    b->desc_state = 0;
-    MLMC_HIP(ctx, hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(BatchDesc), hipMemcpyHostToDevice,
-                                 ctx->stream));
-    std::memcpy(&b->last_desc, b->h_desc, sizeof(BatchDesc));
-    b->desc_state = 1;
+    q.desc_state = 0;
+    MLMC_HIP(ctx, hipMemcpyAsync(q.d_desc, q.h_desc, sizeof(BatchDesc), hipMemcpyHostToDevice, ctx->stream));
+    std::memcpy(&q.last_desc, q.h_desc, sizeof(BatchDesc));
+    q.desc_state = 1;
     return MLMC_OK;
 }
 
@@ -338,7 +349,7 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
     }
     mlmc_status st = ensure_bufs(ctx);
     if (st) return st;
-    auto* b = bufs_of(ctx);
+    PlannedProblem& prob = bufs_of(ctx)->run;
     const auto sampler = pick_persistent(sampler_variant(m), o.M, persistent_ppt(ctx), p.kind, o.cv != nullptr);
     if (!sampler) return fail(ctx, MLMC_EINVAL, "no persistent sampler for this model and payoff");
     const float *cv_table = nullptr, *cv_phi0 = nullptr;
@@ -352,23 +363,21 @@ mlmc_status run_persistent(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff
     }
     const PersistentShape s = persistent_shape(ctx, sampler, lds);
     // the seed goes in with each launch: runs of one problem share the
-    // descriptor's bytes and upload it once.  Driver runs have dispensers
-    // of their own, which their plans leave at zero.
-    fill_desc(ctx, b->h_desc, s, m, &p, 1, o.L_max, o.M, ctx->d_drv_spread,
-              b->d_counters + kHeads * kHeadStride, &init);
+    // descriptor's bytes and upload it once
+    fill_desc(ctx, prob, s, m, &p, 1, o.L_max, o.M, ctx->d_drv_spread, &init);
     if (o.cv) {
-        b->h_desc->cv_table = cv_table;
-        b->h_desc->cv_spec = cv_spec;
-        b->h_desc->cv_phi0 = cv_phi0;
-        b->h_desc->cv_levels = o.cv_levels;
+        prob.h_desc->cv_table = cv_table;
+        prob.h_desc->cv_spec = cv_spec;
+        prob.h_desc->cv_phi0 = cv_phi0;
+        prob.h_desc->cv_levels = o.cv_levels;
     }
     bool uploaded = false;
-    st = upload_desc(ctx, b, &uploaded);
+    st = upload_desc(ctx, prob, &uploaded);
     if (st) return st;
     const dim3 grid(ctx->num_cu * s.blocks_per_cu), block(s.block);
-    const BatchDesc* d = b->d_desc;
+    const BatchDesc* d = prob.d_desc;
     DriverState* mirror = (DriverState*)ctx->h_drv_dev;
-    // prepared: the context's last call was a device-planned run that ended
+    // prepared: the context's last run was a device-planned one that ended
     // normally, so the update queued past its end has built a fresh state
     // and planned its pilot batch, and its updates left the spread groups at
     // zero; if the descriptor is that run's, this run starts with its
@@ -457,16 +466,14 @@ static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payo
                              double coarse)
 {
     auto* b = bufs_of(ctx);
-    // a batch rewrites the plan table: a driver run's prepared start is gone
-    ctx->drv_pilot_ready = false;
     const PersistentFn sampler = batch_sampler(ctx, m, p, np, M);
     const PersistentShape s = persistent_shape(ctx, sampler, 0);
-    fill_desc(ctx, b->h_desc, s, m, p, np, L, M, b->d_acc, b->d_counters, nullptr);
-    mlmc_status st = upload_desc(ctx, b);
+    fill_desc(ctx, b->batch, s, m, p, np, L, M, b->d_acc, nullptr);
+    mlmc_status st = upload_desc(ctx, b->batch);
     if (st) return st;
     if (!b->acc_clean) MLMC_HIP(ctx, zero_records(b->d_acc, kMaxSlots * kMaxLevels * kSpread, ctx->stream));
     b->acc_clean = false;
-    const BatchDesc* d = b->d_desc;
+    const BatchDesc* d = b->batch.d_desc;
     const int tix = timed_begin(ctx, 16, fine, coarse);
     if (counts) hipLaunchKernelGGL(plan_counts_kernel, dim3(1), dim3(64), 0, ctx->stream, d, counts);
     else hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64), 0, ctx->stream, d, *req);

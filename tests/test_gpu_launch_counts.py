@@ -1,0 +1,57 @@
+"""What calls in turn launch: a call of another kind in between adds no upload
+and no start or fill launch to the next one."""
+from collections import Counter
+
+import pytest
+
+from paper_1505_00965_amd import mlmc as A
+from paper_1505_00965_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CALL, MIL = A.payoff(**W.CALL), A.model(**dict(W.GBM_MODEL), scheme=1)
+GBM = A.model(**W.GBM_MODEL)
+
+
+def launched(*calls):
+    """Kernels and copies on the device during the calls, by name."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        for f in calls:
+            f()
+        torch.cuda.synchronize()
+    names = Counter()
+    for e in p.events():
+        n = e.name.replace("void ", "").replace("mlmc::", "").split("(")[0].split("<")[0].strip()
+        if n.endswith("_kernel") or n.startswith("Mem"):
+            names[n] += 1
+    return names
+
+
+def planned(ctx):
+    return lambda: ctx.mlmc_run(GBM, CALL, 0.3, seed=3, persistent=True)
+
+
+def randomised(ctx, N=9001, precision=32):
+    return lambda: ctx.mlmc_rhee_glynn(MIL, CALL, 4, 4, 0.125, N, 3, precision=precision)
+
+
+def batch(ctx):
+    return lambda: ctx.mlmc_levels_batch(GBM, [CALL], 4, 2, [[900, 80, 9]], 5)
+
+
+@pytest.mark.parametrize("between", [randomised, batch])
+def test_planned_runs_keep_their_start_and_descriptor(between):
+    with A.Context(0) as ctx:
+        run, other = planned(ctx), between(ctx)
+        first = run()
+        other()
+        n = launched(run, other, run, other)
+        print(dict(n), flush=True)
+        assert n["persistent_kernel"] >= 6 and n["driver_update_plan_kernel"] >= 4    # the profiler sees them
+        assert n["driver_start_kernel"] == 0
+        assert not [k for k in n if k.startswith("Mem")], n
+        assert run()["N"] == first["N"]
