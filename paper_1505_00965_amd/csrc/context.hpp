@@ -170,9 +170,10 @@ void free_persistent(mlmc_ctx* ctx);
 
 // The randomised estimator's form in three launches after its draws
 // (persistent.hip): kCountCopies zeroed copies of sixteen device counts to draw
-// into, then the
-// samples of every level by its count, published with the counts.
+// into, then the samples of every level by its count, published with the
+// counts.  counts_published: a publish launch has cleared them.
 mlmc_status level_counts(mlmc_ctx* ctx, unsigned long long** counts);
+void counts_published(mlmc_ctx* ctx);
 mlmc_status run_counts(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int L, int M, uint64_t seed,
                        unsigned long long* counts);
 

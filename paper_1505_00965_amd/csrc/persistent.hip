@@ -492,9 +492,11 @@ mlmc_status run_counts(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p,
                        unsigned long long* counts)
 {
     const mlmc_status st = run_batch(ctx, m, &p, 1, L, M, seed, nullptr, counts, 0.0, 0.0);
-    if (!st) bufs_of(ctx)->counts_clean = true;
+    if (!st) counts_published(ctx);
     return st;
 }
+
+void counts_published(mlmc_ctx* ctx) { bufs_of(ctx)->counts_clean = true; }
 
 mlmc_status level_counts(mlmc_ctx* ctx, unsigned long long** counts)
 {

@@ -87,6 +87,7 @@ static mlmc_status run_levels(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_pay
     // the counts alone, published
     mlmc_status st = publish_groups(ctx, ctx->d_acc, 0, counts, false);
     if (st) return st;
+    counts_published(ctx);
     for (int l = 0; l <= L; ++l) N[l] = ctx->h_pub->count[l];
     static_assert(kRgLevels * kSpread <= kAccSlots, "one spread group per level");
     int clean = 0;

@@ -55,3 +55,16 @@ def test_planned_runs_keep_their_start_and_descriptor(between):
         assert n["driver_start_kernel"] == 0
         assert not [k for k in n if k.startswith("Mem")], n
         assert run()["N"] == first["N"]
+
+
+def test_counts_are_cleared_once():
+    """fp64 estimates read the counts back first; the launch that does clears
+    them, for the next estimate of either form."""
+    with A.Context(0) as ctx:
+        f64, f32 = randomised(ctx, 901, 64), randomised(ctx)
+        a, b = f64(), f32()
+        n = launched(f64, f32, f64, f64, f32)
+        print(dict(n), flush=True)
+        assert n["level_draw_kernel"] == 5
+        assert not [k for k in n if k.startswith("Mem")], n
+        assert f64()["N"] == a["N"] and f32()["N"] == b["N"]
