@@ -134,9 +134,12 @@ mlmc_status mlmc_set_stream(mlmc_ctx* ctx, void* hip_stream);
 const char* mlmc_last_error(const mlmc_ctx* ctx);
 /* Fix the level kernel's launch shape: block in {64,128,256,512,1024},
  * paths per thread ppt in {1,2,4}.  block = 0 returns to the tuned/default
- * choice.  Results do not depend on it (see determinism above).  GBM levels
- * whose paths are too few to fill the device run each path on several lanes
- * (a choice made from N alone, whatever the shape).                         */
+ * choice, which depends on N: fewer samples per lane, then smaller blocks, for
+ * launches that would leave compute units idle, and a kernel of its own for few
+ * long chains (mlmc_level_shape tells; neither under a fixed shape).  Results
+ * do not depend on it (see determinism above).  GBM levels whose paths are too
+ * few to fill the device run each path on several lanes (a choice made from N
+ * alone, whatever the shape).                                               */
 mlmc_status mlmc_set_launch(mlmc_ctx* ctx, int block, int ppt);
 
 /* Kernel timing with HIP events on the context's stream.  Slots:
@@ -184,9 +187,10 @@ mlmc_status mlmc_kernel_stats(mlmc_ctx* ctx, mlmc_kernel_stat* out);
  * level 6) and keeps the fastest for this (model kind, scheme,
  * antithetic flag, payoff, precision, M); later launches use it unless
  * mlmc_set_launch fixed a shape.  A launch with fewer samples than 256 lanes
- * per compute unit at the tuned ppt takes ppt 1, and a smaller launch halves
+ * per compute unit at the tuned ppt takes ppt 1, a smaller launch halves
  * ppt, then the block, until it has a block per compute unit and two waves
- * per SIMD.  Results are cached in the JSON file
+ * per SIMD, one whose fullest compute unit would then hold fewer samples halves
+ * ppt, and few long chains take their own kernel (mlmc_level_shape).  Results are cached in the JSON file
  * cache_path (or $MLMC_TUNE_CACHE; NULL/"" and no variable: no cache) under
  * a key of GPU architecture, compute-unit count and HIP runtime version, and
  * read back instead of measured when present.                             */
@@ -405,6 +409,10 @@ mlmc_status mlmc_autotune_run(mlmc_ctx* ctx, const mlmc_model* model, const mlmc
  * 1/2) 2^-24, L = the first l with u < sum_{k <= l} p_k.  Level l then runs
  * on its samples 0 .. N_l - 1 of the ordinary sampler (stream 0).
  * L_cap <= 15 and within the level limits of M; 0 < q < 1; 1 <= N <= 2^40.
+ * fp32 paths without the twin take one launch of the persistent all-levels
+ * sampler (shape: mlmc_set_persistent_launch; the level tuner's shapes are not
+ * used); fp64 paths, the twin, kernel timing and a shape fixed by
+ * mlmc_set_launch a launch per level.
  * Host output; MLMC_ENONFINITE as for mlmc_level.                          */
 typedef struct {
     double estimate;     /* (1/N) sum_l S1_l / p_l                          */

@@ -10,9 +10,9 @@
 // level in one launch of the all-levels sampler, planned on the device from
 // the histogram, so the host waits once (2^22 samples, Milstein, M = 4, seven
 // levels: 45 us; with the histogram read back and a launch per level 125).
-// Other estimates read the histogram back and run every level with a non-zero
-// count on the ordinary sampler's samples 0 .. n_l - 1, one launch each.  The
-// host forms
+// Other estimates, timed ones and any under a level shape that the caller fixed
+// read the histogram back and run every level with a non-zero count on the
+// ordinary sampler's samples 0 .. n_l - 1, one launch each.  The host forms
 //   estimate = (1/N) sum_l S1_l / p_l,  E[Z^2] = (1/N) sum_l S2_l / p_l^2.
 #include <hip/hip_runtime.h>
 
@@ -143,8 +143,8 @@ mlmc_status mlmc_rhee_glynn(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_p
     const unsigned grid = (unsigned)std::min<uint64_t>((nblk + 1023) / 1024, (uint64_t)ctx->num_cu);
     hipLaunchKernelGGL(level_draw_kernel, dim3(grid), dim3(1024), 0, ctx->stream, seed, N, law, d_counts);
     MLMC_HIP(ctx, hipGetLastError());
-    // stamped level launches belong to the per-level form
-    if (precision == 32 && !model->antithetic && !(ctx->timing && !ctx->timing_paused)) {
+    // stamped launches and a fixed level shape belong to the per-level form
+    if (precision == 32 && !model->antithetic && !ctx->launch_block && !(ctx->timing && !ctx->timing_paused)) {
         st = run_counts(ctx, *model, *payoff, L_cap, M, seed, d_counts);
         for (int l = 0; l <= L_cap; ++l) out->N[l] = ctx->h_pub->count[l];
     } else {

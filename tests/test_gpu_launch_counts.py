@@ -68,3 +68,22 @@ def test_counts_are_cleared_once():
         assert n["level_draw_kernel"] == 5
         assert not [k for k in n if k.startswith("Mem")], n
         assert f64()["N"] == a["N"] and f32()["N"] == b["N"]
+
+
+def test_fixed_level_shape_is_obeyed():
+    """A fixed level shape names the level kernels: the estimator runs those."""
+    with A.Context(0) as ctx:
+        f = randomised(ctx)
+        free = f()
+        ctx.set_launch(128, 1)
+        fixed = f()
+        n = launched(f)
+        print(dict(n), flush=True)
+        assert n["level_kernel"] + n["split_level_kernel"] + n["short_level_kernel"] == 5
+        assert n["persistent_kernel"] == n["plan_counts_kernel"] == 0
+        ctx.set_launch(0, 0)
+        assert launched(f)["persistent_kernel"] == 1
+        assert free["N"] == fixed["N"]
+        for l in range(5):
+            # the same samples in another order
+            assert abs(free["sum_y2"][l] - fixed["sum_y2"][l]) <= 1e-12 * free["sum_y2"][l]
