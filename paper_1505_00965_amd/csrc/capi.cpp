@@ -561,12 +561,21 @@ mlmc_status mlmc_ctx_create(int device, mlmc_ctx** out)
     ctx->num_cu = prop.multiProcessorCount;
     hipError_t e = hipSetDevice(device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->own_stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipMalloc(&ctx->d_acc, sizeof(LevelAcc) * kAccSlots);
-    if (e == hipSuccess) e = hipHostMalloc(&ctx->h_pub, sizeof(PublishMirror));
-    if (e == hipSuccess) std::memset(ctx->h_pub, 0, sizeof(PublishMirror));
-    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&ctx->h_pub_dev, ctx->h_pub, 0);
-    if (e == hipSuccess) e = hipMalloc(&ctx->d_tmp, sizeof(double) * 4 * MLMC_MAX_LEVELS);
-    if (e == hipSuccess) e = hipHostMalloc(&ctx->h_tmp, sizeof(double) * 4 * MLMC_MAX_LEVELS);
+    auto whole = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t acc = whole(sizeof(LevelAcc) * kAccSlots), pub = whole(sizeof(PublishMirror));
+    const size_t tmp = whole(sizeof(double) * 4 * MLMC_MAX_LEVELS);
+    if (e == hipSuccess) e = hipMalloc(&ctx->d_block, acc + tmp + persistent_device_bytes());
+    if (e == hipSuccess) e = hipHostMalloc(&ctx->h_block, pub + tmp + persistent_host_bytes());
+    if (e == hipSuccess) {
+        ctx->d_acc = (LevelAcc*)ctx->d_block;
+        ctx->d_tmp = (double*)(ctx->d_block + acc);
+        ctx->d_persist = ctx->d_block + acc + tmp;
+        ctx->h_pub = (PublishMirror*)ctx->h_block;
+        ctx->h_tmp = (double*)(ctx->h_block + pub);
+        ctx->h_persist = ctx->h_block + pub + tmp;
+        std::memset(ctx->h_pub, 0, sizeof(PublishMirror));
+        e = hipHostGetDevicePointer((void**)&ctx->h_pub_dev, ctx->h_pub, 0);
+    }
     if (e != hipSuccess) {
         mlmc_ctx_destroy(ctx);
         return e == hipErrorOutOfMemory ? MLMC_ENOMEM : MLMC_EDEVICE;
@@ -588,10 +597,8 @@ mlmc_status mlmc_ctx_destroy(mlmc_ctx* ctx)
         hipEventDestroy(t.stop);
     }
     for (auto e : ctx->event_pool) hipEventDestroy(e);
-    if (ctx->d_acc) hipFree(ctx->d_acc);
-    if (ctx->h_pub) hipHostFree(ctx->h_pub);
-    if (ctx->d_tmp) hipFree(ctx->d_tmp);
-    if (ctx->h_tmp) hipHostFree(ctx->h_tmp);
+    if (ctx->d_block) hipFree(ctx->d_block);
+    if (ctx->h_block) hipHostFree(ctx->h_block);
     if (ctx->own_stream) hipStreamDestroy(ctx->own_stream);
     delete ctx;
     return MLMC_OK;

@@ -33,7 +33,14 @@ struct mlmc_ctx {
     std::string err;
     int launch_block = 0, launch_ppt = 0;   // 0: tuned/default
     int persist_block = 0, persist_ppt = 0, persist_bpc = 0;
-    void* persist = nullptr;                // persistent-form buffers (persistent.hip)
+    // One device and one pinned host allocation hold every buffer of the context
+    // that does not grow: a context made for one call pays for two, not six.
+    char* d_block = nullptr;
+    char* h_block = nullptr;
+    // the persistent form's parts of them, and its state (persistent.hip)
+    char* d_persist = nullptr;
+    char* h_persist = nullptr;
+    void* persist = nullptr;
     // Level accumulators: kAccSlots records (payoff x level).  The first
     // acc_clean spread groups hold zeros (every call's publish launch folds and
     // clears the groups it used; 0 while a call runs and after one that failed).
@@ -164,7 +171,11 @@ void harvest_timing(mlmc_ctx* ctx);
 // stream (the rest stay pending until a later harvest).
 void harvest_ready(mlmc_ctx* ctx);
 
-// Release the driver state and the persistent batch buffers (idempotent).
+// Bytes of the persistent form's buffers (multiples of 256).
+size_t persistent_device_bytes();
+size_t persistent_host_bytes();
+
+// Release the driver state and the persistent form's (idempotent).
 void free_driver(mlmc_ctx* ctx);
 void free_persistent(mlmc_ctx* ctx);
 

@@ -188,14 +188,19 @@ struct PlannedProblem {
     int desc_state = 0;
 };
 
-// Device buffers of the persistent form, owned by the context.
+// Batch spread groups [kMaxSlots][kMaxLevels][kSpread], and behind them the
+// level draws of a randomised estimate: cleared by one launch where both are to be.
+constexpr int kGroupRecords = kMaxSlots * kMaxLevels * kSpread;
+constexpr int kCountRecords = (int)(sizeof(unsigned long long) * kCountCopies * kMaxLevels / sizeof(LevelAcc));
+static_assert(kCountRecords * sizeof(LevelAcc) == sizeof(unsigned long long) * kCountCopies * kMaxLevels,
+              "the counts are whole records");
+
+// State of the persistent form; the buffers are parts of the context's.
 struct PersistentBufs {
-    char* d_all = nullptr;            // the allocation that holds the device buffers
-    BatchDesc* h_desc = nullptr;      // both host descriptors
     PlannedProblem run, batch;
-    LevelAcc* d_acc = nullptr;        // batch spread groups [kMaxSlots][kMaxLevels][kSpread]
+    LevelAcc* d_acc = nullptr;
     bool acc_clean = false;           // they hold zeros (publish_groups clears what it folds)
-    unsigned long long* d_counts = nullptr;   // level draws of a randomised estimate
+    unsigned long long* d_counts = nullptr;
     bool counts_clean = false;        // they hold zeros
 };
 
@@ -225,50 +230,50 @@ static PersistentShape persistent_shape(const mlmc_ctx* ctx, PersistentFn fn, si
     return s;
 }
 
-static mlmc_status ensure_bufs(mlmc_ctx* ctx)
+// The persistent form's buffers cut from the context's two blocks (from null:
+// their sizes alone).
+static PersistentBufs cut_bufs(char* d, char* h, size_t* d_bytes, size_t* h_bytes)
 {
-    if (ctx->persist) return MLMC_OK;
-    auto* b = new (std::nothrow) PersistentBufs();
-    if (!b) return fail(ctx, MLMC_ENOMEM, "host allocation failed");
-    ctx->persist = b;
-    // one device allocation, cut into 256-byte pieces
-    size_t at = 0;
-    auto piece = [&](size_t bytes) {
-        const size_t p = at;
+    size_t da = 0, ha = 0;
+    auto cut = [](char* base, size_t& at, size_t bytes) {
+        char* p = base + at;
         at += (bytes + 255) / 256 * 256;
         return p;
     };
-    size_t desc[2], plan[2], head[2], split[2];
-    for (int k = 0; k < 2; ++k) {
-        desc[k] = piece(sizeof(BatchDesc));
-        plan[k] = piece(sizeof(PlanTable));
-        head[k] = piece(sizeof(unsigned) * kHeads * kHeadStride);
-        split[k] = piece(sizeof(unsigned) * kMaxSlots * kMaxLevels);
+    PersistentBufs b;
+    for (PlannedProblem* q : {&b.run, &b.batch}) {
+        q->d_desc = (BatchDesc*)cut(d, da, sizeof(BatchDesc));
+        q->h_desc = (BatchDesc*)cut(h, ha, sizeof(BatchDesc));
+        q->d_plan = (PlanTable*)cut(d, da, sizeof(PlanTable));
+        q->d_head = (unsigned*)cut(d, da, sizeof(unsigned) * kHeads * kHeadStride);
+        q->d_split = (unsigned*)cut(d, da, sizeof(unsigned) * kMaxSlots * kMaxLevels);
     }
-    const size_t counts = piece(sizeof(unsigned long long) * kCountCopies * kMaxLevels);
-    const size_t acc = piece(sizeof(LevelAcc) * kMaxSlots * kMaxLevels * kSpread);
-    hipError_t e = hipMalloc(&b->d_all, at);
-    if (e == hipSuccess) e = hipHostMalloc(&b->h_desc, 2 * sizeof(BatchDesc));
-    // the groups and the counts start at zero (the dispensers at each plan)
-    if (e == hipSuccess) e = hipMemsetAsync(b->d_all, 0, at, ctx->stream);
-    if (e == hipSuccess) {
-        for (int k = 0; k < 2; ++k) {
-            PlannedProblem& p = k ? b->batch : b->run;
-            p.d_desc = (BatchDesc*)(b->d_all + desc[k]);
-            p.h_desc = b->h_desc + k;
-            p.d_plan = (PlanTable*)(b->d_all + plan[k]);
-            p.d_head = (unsigned*)(b->d_all + head[k]);
-            p.d_split = (unsigned*)(b->d_all + split[k]);
-        }
-        b->d_counts = (unsigned long long*)(b->d_all + counts);
-        b->d_acc = (LevelAcc*)(b->d_all + acc);
-        b->acc_clean = b->counts_clean = true;
-    }
-    if (e != hipSuccess) {
-        // An incomplete set is released so that the next call starts over.
-        free_persistent(ctx);
-        return hip_fail(ctx, e, "persistent batch allocation");
-    }
+    b.d_acc = (LevelAcc*)cut(d, da, sizeof(LevelAcc) * (kGroupRecords + kCountRecords));
+    b.d_counts = (unsigned long long*)(b.d_acc + kGroupRecords);
+    if (d_bytes) *d_bytes = da;
+    if (h_bytes) *h_bytes = ha;
+    return b;
+}
+
+size_t persistent_device_bytes()
+{
+    size_t n;
+    cut_bufs(nullptr, nullptr, &n, nullptr);
+    return n;
+}
+
+size_t persistent_host_bytes()
+{
+    size_t n;
+    cut_bufs(nullptr, nullptr, nullptr, &n);
+    return n;
+}
+
+static mlmc_status ensure_bufs(mlmc_ctx* ctx)
+{
+    if (ctx->persist) return MLMC_OK;
+    ctx->persist = new (std::nothrow) PersistentBufs(cut_bufs(ctx->d_persist, ctx->h_persist, nullptr, nullptr));
+    if (!ctx->persist) return fail(ctx, MLMC_ENOMEM, "host allocation failed");
     return MLMC_OK;
 }
 
@@ -276,11 +281,7 @@ static PersistentBufs* bufs_of(mlmc_ctx* ctx) { return (PersistentBufs*)ctx->per
 
 void free_persistent(mlmc_ctx* ctx)
 {
-    auto* b = bufs_of(ctx);
-    if (!b) return;
-    if (b->d_all) hipFree(b->d_all);
-    if (b->h_desc) hipHostFree(b->h_desc);
-    delete b;
+    delete bufs_of(ctx);
     ctx->persist = nullptr;
 }
 
@@ -471,7 +472,7 @@ static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payo
     fill_desc(ctx, b->batch, s, m, p, np, L, M, b->d_acc, nullptr);
     mlmc_status st = upload_desc(ctx, b->batch);
     if (st) return st;
-    if (!b->acc_clean) MLMC_HIP(ctx, zero_records(b->d_acc, kMaxSlots * kMaxLevels * kSpread, ctx->stream));
+    if (!b->acc_clean) MLMC_HIP(ctx, zero_records(b->d_acc, kGroupRecords, ctx->stream));
     b->acc_clean = false;
     const BatchDesc* d = b->batch.d_desc;
     const int tix = timed_begin(ctx, 16, fine, coarse);
@@ -503,9 +504,11 @@ mlmc_status level_counts(mlmc_ctx* ctx, unsigned long long** counts)
     const mlmc_status st = ensure_bufs(ctx);
     if (st) return st;
     auto* b = bufs_of(ctx);
-    if (!b->counts_clean)
-        MLMC_HIP(ctx, hipMemsetAsync(b->d_counts, 0, sizeof(unsigned long long) * kCountCopies * kMaxLevels,
-                                     ctx->stream));
+    if (!b->counts_clean) {
+        LevelAcc* from = b->acc_clean ? b->d_acc + kGroupRecords : b->d_acc;
+        MLMC_HIP(ctx, zero_records(from, (int)(b->d_acc + kGroupRecords + kCountRecords - from), ctx->stream));
+        b->acc_clean = true;
+    }
     b->counts_clean = false;
     *counts = b->d_counts;
     return MLMC_OK;

@@ -13,8 +13,9 @@ CALL, MIL = A.payoff(**W.CALL), A.model(**dict(W.GBM_MODEL), scheme=1)
 GBM = A.model(**W.GBM_MODEL)
 
 
-def launched(*calls):
-    """Kernels and copies on the device during the calls, by name."""
+def launched(*calls, runtime=False):
+    """Kernels and copies on the device during the calls, by name; with
+    `runtime`, the calls of the HIP runtime instead."""
     import torch
     from torch.profiler import ProfilerActivity, profile
     torch.zeros(1, device="cuda")
@@ -26,7 +27,7 @@ def launched(*calls):
     names = Counter()
     for e in p.events():
         n = e.name.replace("void ", "").replace("mlmc::", "").split("(")[0].split("<")[0].strip()
-        if n.endswith("_kernel") or n.startswith("Mem"):
+        if n.startswith("hip") if runtime else n.endswith("_kernel") or n.startswith("Mem"):
             names[n] += 1
     return names
 
@@ -87,3 +88,18 @@ def test_fixed_level_shape_is_obeyed():
         for l in range(5):
             # the same samples in another order
             assert abs(free["sum_y2"][l] - fixed["sum_y2"][l]) <= 1e-12 * free["sum_y2"][l]
+
+
+@pytest.mark.parametrize("call", [randomised, batch, lambda c: lambda: c.mlmc_level(GBM, CALL, 2, 4, 1000, 7)])
+def test_context_of_one_call_allocates_twice(call):
+    """One device and one host allocation with the context, none at its first
+    call."""
+    def one():
+        with A.Context(0) as ctx:
+            call(ctx)()
+    one()
+    n = launched(one, runtime=True)
+    print(dict(n), flush=True)
+    assert n["hipLaunchKernel"] + n["hipExtLaunchKernel"] >= 2              # the profiler sees them
+    assert n["hipMalloc"] == n["hipHostMalloc"] == 1, n
+    assert n["hipFree"] == n["hipHostFree"] == 1, n
