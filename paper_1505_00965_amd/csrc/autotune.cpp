@@ -157,7 +157,7 @@ static float time_shape(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p
         hipEventRecord(a, ctx->stream);
         ctx->acc_clean = 0;   // the timed launches leave their sums in the records
         *st = enqueue_level(ctx, m, p, l, M, N, 12345, 0, precision, kStreamNormal, 1, ctx->d_acc,
-                            nullptr, nullptr, nullptr, true);
+                            nullptr, nullptr, nullptr);
         hipEventRecord(b, ctx->stream);
         if (hipEventSynchronize(b) != hipSuccess) *st = MLMC_EDEVICE;
         float ms = 0.f;

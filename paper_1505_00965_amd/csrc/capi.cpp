@@ -412,9 +412,8 @@ void harvest_ready(mlmc_ctx* ctx)
 static mlmc_status enqueue_segment(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int l,
                                    int M, uint64_t N, uint64_t seed, uint64_t offset, int precision,
                                    uint32_t stream, int coupled, LevelAcc* acc, double* d_pf,
-                                   double* d_pc, const mlmc_cv* cv, bool spread, uint64_t n_call)
+                                   double* d_pc, const mlmc_cv* cv, uint64_t n_call)
 {
-    const uint32_t mask = spread ? (uint32_t)(kSpread - 1) : 0u;
     const int dim = m.kind == MLMC_HESTON ? 2 : 1;
     if (cv) {
         if (precision != 32) return fail(ctx, MLMC_EINVAL, "the control variate runs in fp32 paths only");
@@ -426,7 +425,6 @@ static mlmc_status enqueue_segment(mlmc_ctx* ctx, const mlmc_model& m, const mlm
             return fail(ctx, MLMC_EINVAL, "network inputs do not match the model (2: GBM, 3: Heston)");
         const double nf = (double)level_steps(l, M);
         auto a = make_args<float>(m, p, l, M, N, seed, offset, stream, coupled, acc, d_pf, d_pc);
-        a.spread_mask = mask;
         set_counter_words(a, dim);
         const bool tab = cv_tabulated(cv);
         hipError_t e;
@@ -468,27 +466,24 @@ static mlmc_status enqueue_segment(mlmc_ctx* ctx, const mlmc_model& m, const mlm
     timed_kernel(ctx, l < 16 ? l : 15, (double)N * nf * twins,
                  (coupled && l > 0) ? (double)N * nf / M : 0.0, &t0, &t1);
     const hipError_t e = launch_plain_segment(m, p, l, M, N, seed, offset, precision, stream, coupled,
-                                              acc, d_pf, d_pc, spread, shape, ctx->stream, t0, t1);
+                                              acc, d_pf, d_pc, shape, ctx->stream, t0, t1);
     if (e != hipSuccess) return hip_fail(ctx, e, "level kernel launch");
     return MLMC_OK;
 }
 
 hipError_t launch_plain_segment(const mlmc_model& m, const mlmc_payoff& p, int l, int M, uint64_t N,
                                 uint64_t seed, uint64_t offset, int precision, uint32_t stream,
-                                int coupled, LevelAcc* acc, double* d_pf, double* d_pc, bool spread,
+                                int coupled, LevelAcc* acc, double* d_pf, double* d_pc,
                                 const LaunchShape& shape, hipStream_t st, hipEvent_t t0,
                                 hipEvent_t t1)
 {
-    const uint32_t mask = spread ? (uint32_t)(kSpread - 1) : 0u;
     const int dim = m.kind == MLMC_HESTON ? 2 : 1;
     if (precision == 64) {
         auto a = make_args<double>(m, p, l, M, N, seed, offset, stream, coupled, acc, d_pf, d_pc);
-        a.spread_mask = mask;
         set_counter_words(a, dim);
         return launch_level(m, p, M, 64, &a, shape, st, t0, t1);
     }
     auto a = make_args<float>(m, p, l, M, N, seed, offset, stream, coupled, acc, d_pf, d_pc);
-    a.spread_mask = mask;
     a.split = (uint32_t)shape.split;
     set_counter_words(a, dim);
     return launch_level(m, p, M, 32, &a, shape, st, t0, t1);
@@ -496,8 +491,7 @@ hipError_t launch_plain_segment(const mlmc_model& m, const mlmc_payoff& p, int l
 
 mlmc_status enqueue_level(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int l, int M,
                           uint64_t N, uint64_t seed, uint64_t offset, int precision, uint32_t stream,
-                          int coupled, LevelAcc* acc, double* d_pf, double* d_pc, const mlmc_cv* cv,
-                          bool spread)
+                          int coupled, LevelAcc* acc, double* d_pf, double* d_pc, const mlmc_cv* cv)
 {
     const uint64_t q = samples_per_unit(level_steps(l, M), m.kind == MLMC_HESTON ? 2 : 1);
     const uint64_t end = offset + N;
@@ -506,8 +500,7 @@ mlmc_status enqueue_level(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff&
         const uint64_t skip = first - offset;
         const mlmc_status st =
             enqueue_segment(ctx, m, p, l, M, stop - first, seed, first, precision, stream, coupled,
-                            acc, d_pf ? d_pf + skip : nullptr, d_pc ? d_pc + skip : nullptr, cv,
-                            spread, N);
+                            acc, d_pf ? d_pf + skip : nullptr, d_pc ? d_pc + skip : nullptr, cv, N);
         if (st) return st;
         first = stop;
     }
@@ -716,7 +709,7 @@ static mlmc_status level_common(mlmc_ctx* ctx, const mlmc_model* model, const ml
     st = claim_records(ctx, 1, &clean);
     if (st) return st;
     st = enqueue_level(ctx, *model, *payoff, l, M, N, seed, path_offset, precision, stream, coupled,
-                       ctx->d_acc, d_pf, d_pc, cv, true);
+                       ctx->d_acc, d_pf, d_pc, cv);
     if (st) return st;
     // dumps are read by the caller on any stream: wait for the stream itself
     return finish_level(ctx, *model, N, l, M, coupled, d_pf != nullptr, clean, out);

@@ -136,25 +136,24 @@ LaunchShape default_shape(const mlmc_model& m, const mlmc_payoff& p, int l, int 
 // counter word 2 (no control variate): arguments as for enqueue_level.
 hipError_t launch_plain_segment(const mlmc_model& m, const mlmc_payoff& p, int l, int M, uint64_t N,
                                 uint64_t seed, uint64_t offset, int precision, uint32_t stream,
-                                int coupled, LevelAcc* acc, double* d_pf, double* d_pc, bool spread,
-                                const LaunchShape& shape, hipStream_t st, hipEvent_t t0 = nullptr,
-                                hipEvent_t t1 = nullptr);
-// Enqueue one level into record `acc`, or with `spread` into the spread
-// group of kSpread records at `acc` (no zeroing, no sync).
+                                int coupled, LevelAcc* acc, double* d_pf, double* d_pc, const LaunchShape& shape,
+                                hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// Enqueue one level into the spread group of kSpread records at `acc` (no
+// zeroing, no sync).
 mlmc_status enqueue_level(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff& p, int l, int M,
                           uint64_t N, uint64_t seed, uint64_t offset, int precision, uint32_t stream,
                           int coupled, LevelAcc* acc, double* d_pf, double* d_pc,
-                          const mlmc_cv* cv, bool spread = false);
+                          const mlmc_cv* cv);
 // Zero `n` records with a fill kernel (safe inside graph capture).
 hipError_t zero_records(LevelAcc* acc, int n, hipStream_t st);
 // Zeros in the first n groups of the context's level records, by a fill launch
-// unless the last call left them so; release_records once the caller's sums
-// are published.
+// unless the last call left them so (`clean`: the groups that it did).
+mlmc_status claim_records(mlmc_ctx* ctx, int n, int* clean);
+// The same groups given back, once their sums are published and cleared.
+inline void release_records(mlmc_ctx* ctx, int n, int clean) { ctx->acc_clean = clean > n ? clean : n; }
 // Enqueue the launch that folds `n` spread groups into the context's mirror
 // and clears them (and, given counts, adds up and clears their copies), then
 // wait until the host sees it; with `sync`, for the stream instead.
-mlmc_status claim_records(mlmc_ctx* ctx, int n, int* clean);
-inline void release_records(mlmc_ctx* ctx, int n, int clean) { ctx->acc_clean = clean > n ? clean : n; }
 mlmc_status publish_groups(mlmc_ctx* ctx, LevelAcc* groups, int n, unsigned long long* counts, bool sync);
 
 // Bracket a launch with timing events when timing is on (no-op otherwise).

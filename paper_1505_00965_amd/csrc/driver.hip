@@ -244,7 +244,7 @@ mlmc_status mlmc_run(mlmc_ctx* ctx, const mlmc_model* model, const mlmc_payoff* 
                 const mlmc_cv* cv = (o.cv && (o.cv_levels <= 0 || l < o.cv_levels)) ? o.cv : nullptr;
                 st = enqueue_level(ctx, *model, *payoff, l, o.M, (uint64_t)h->dN[l], o.seed,
                                    (uint64_t)h->n[l], o.precision, kStreamNormal, 1,
-                                   ctx->d_drv_spread + l * kSpread, nullptr, nullptr, cv, true);
+                                   ctx->d_drv_spread + l * kSpread, nullptr, nullptr, cv);
                 if (st) return st;
             }
             hipEvent_t t0, t1;

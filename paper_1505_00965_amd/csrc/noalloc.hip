@@ -171,7 +171,7 @@ extern "C" mlmc_status mlmc_level_noalloc(const mlmc_model* model, const mlmc_pa
         const LaunchShape shape =
             default_shape(m, p, l, M, precision, stop - first, N, ds->num_cu, 0, 0, 0, 0);
         e = launch_plain_segment(m, p, l, M, stop - first, seed, first, precision, kStreamNormal, 1,
-                                 group, nullptr, nullptr, true, shape, st);
+                                 group, nullptr, nullptr, shape, st);
         first = stop;
     }
     if (e == hipSuccess) {

@@ -95,7 +95,7 @@ static mlmc_status run_levels(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_pay
     for (int l = 0; l <= L && !st; ++l) {
         if (!N[l]) continue;
         st = enqueue_level(ctx, m, p, l, M, N[l], seed, 0, precision, kStreamNormal, 1,
-                           ctx->d_acc + l * kSpread, nullptr, nullptr, nullptr, true);
+                           ctx->d_acc + l * kSpread, nullptr, nullptr, nullptr);
     }
     if (!st) st = publish_groups(ctx, ctx->d_acc, L + 1, nullptr, false);
     if (!st) release_records(ctx, L + 1, clean);
