@@ -9,17 +9,22 @@
 //   -2 ln u:  u = z 2^e with z in [0.69, 1.39) and a table of 64 intervals of
 //             z (1/c short enough that r = z/c - 1 is exact; c = 1 around
 //             z = 1, so small logarithms keep their relative accuracy), then
-//             a polynomial in r;
+//             a polynomial in r: the table-driven logarithm of P. T. P. Tang
+//             (ACM TOMS 16, 1990);
 //   cos, sin: a table of 64 angles and the exact residual, at most pi/64, by
-//             polynomials and the addition theorem;
-//   sqrt:     the hardware's reciprocal square root and Goldschmidt steps as
-//             in its correctly rounded expansion, without its scaling (the
-//             argument lies in [5.9e-8, 35]).
+//             polynomials and the addition theorem, the angles chosen so that
+//             the tabulated values are nearly exact (the accurate tables of S.
+//             Gal and B. Bachelis, ACM TOMS 17, 1991; the logarithm's too);
+//   sqrt:     the hardware's reciprocal square root and Goldschmidt's iteration
+//             with a last correction by the exact residual (P. W. Markstein,
+//             IBM J. Res. Dev. 34, 1990), without scaling (the argument lies in
+//             [5.9e-8, 35]).
 // Largest errors over all 2^24 values: -2 ln u 0.79 ulp, cos and sin 0.61 2^-53;
 // of 2^21 normals against 80-bit arithmetic, in units of rho 2^-53: 2.77, root
 // mean square 0.513 (the library routines: 2.77 and 0.515).
 // The 3 KiB of tables are copied into LDS by each block (load_normal_tables).
-// Coefficients: interpolation at Chebyshev nodes in 200-bit arithmetic.
+// tests/golden/make_normal_tables.py makes every constant (coefficients:
+// interpolation at Chebyshev nodes in 60-digit arithmetic).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
