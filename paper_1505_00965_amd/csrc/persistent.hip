@@ -31,9 +31,11 @@
 
 namespace mlmc {
 
-// Outstanding samples and first indices per (slot, level) of one batch.
+// Outstanding samples and first indices per (slot, level) of one batch, and
+// the blocks that its sampler is launched with.
 struct BatchRequest {
     double dN[kPairs], offset[kPairs];
+    unsigned blocks;
 };
 
 __global__ __launch_bounds__(64) void plan_kernel(const BatchDesc* d, BatchRequest q)
@@ -42,7 +44,9 @@ __global__ __launch_bounds__(64) void plan_kernel(const BatchDesc* d, BatchReque
     s.dN[threadIdx.x] = q.dN[threadIdx.x];
     s.offset[threadIdx.x] = q.offset[threadIdx.x];
     __syncthreads();
-    plan_body(plan_args(d), s.dN, s.offset);
+    PlanArgs a = plan_args(d);
+    a.grid_blocks = a.fit_blocks = q.blocks;
+    plan_body(a, s.dN, s.offset);
 }
 
 // The plan of a randomised estimate: the drawn samples per level, from 0.
@@ -463,7 +467,7 @@ static PersistentFn batch_sampler(const mlmc_ctx* ctx, const mlmc_model& m, cons
 // nothing.  counts: device counts of slot 0's samples per level instead of
 // the request (then published and cleared).
 static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payoff* p, int np, int L, int M,
-                             uint64_t seed, const BatchRequest* req, unsigned long long* counts, double fine,
+                             uint64_t seed, BatchRequest* req, unsigned long long* counts, double fine,
                              double coarse)
 {
     auto* b = bufs_of(ctx);
@@ -475,11 +479,17 @@ static mlmc_status run_batch(mlmc_ctx* ctx, const mlmc_model& m, const mlmc_payo
     if (!b->acc_clean) MLMC_HIP(ctx, zero_records(b->d_acc, kGroupRecords, ctx->stream));
     b->acc_clean = false;
     const BatchDesc* d = b->batch.d_desc;
+    unsigned blocks = (unsigned)(ctx->num_cu * s.blocks_per_cu);
+    if (req) {
+        // small: the blocks that fit (see kItems)
+        if (fine + coarse < kFewItems * kSmallItem * blocks) blocks = (unsigned)(ctx->num_cu * s.fit_per_cu);
+        req->blocks = blocks;
+    }
     const int tix = timed_begin(ctx, 16, fine, coarse);
     if (counts) hipLaunchKernelGGL(plan_counts_kernel, dim3(1), dim3(64), 0, ctx->stream, d, counts);
     else hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64), 0, ctx->stream, d, *req);
     MLMC_HIP(ctx, hipGetLastError());
-    hipLaunchKernelGGL(sampler, dim3(ctx->num_cu * s.blocks_per_cu), dim3(s.block), 0, ctx->stream, d, seed);
+    hipLaunchKernelGGL(sampler, dim3(blocks), dim3(s.block), 0, ctx->stream, d, seed);
     MLMC_HIP(ctx, hipGetLastError());
     timed_end(ctx, tix);
     static_assert(kMaxSlots * kMaxLevels <= kPublishGroups, "the mirror holds every pair");

@@ -25,17 +25,17 @@ constexpr int kPairs = kMaxSlots * kMaxLevels;
 // The grid is five blocks a compute unit, of which four fit at once where a
 // block takes more than 96 registers a lane (M = 2, batches of several payoff
 // kinds, Heston lookback) or 32 KB of LDS (the tabulated control variate); the
-// others start as blocks end.  In a plan of fewer than kItems items a block the
+// others start as blocks end.  In a plan of fewer than kFewItems items a block the
 // item of such a block would be a second round of the launch: the items are cut
-// for the blocks that fit, and the others leave.  us with every block taking an
-// item and so:
+// for the blocks that fit, and the others leave (a batch, whose size the host
+// knows, is launched without them).  us with every block taking an item and so:
 //   batch of 1e6 samples, lookback, lookback and Asian       46.4  43.0   68.2  65.1
 //   tabulated GBM, M = 2, RMSE 1e-4 S0, call and Asian       158   149    236   223
 // With more items each, the blocks that come later take theirs at the end,
 // where the deep levels' items, shorter than their steps say, close the launch
 // better than level 0's; grids of four took 554 -> 575 us (GBM call, M = 2,
 // RMSE 2e-5 S0) and 2330 -> 2408 (Heston lookback, M = 2, 5e-5).
-constexpr double kItems = 4.0, kItemsMost = 16.0, kItemSteps = 65536.0, kSmallItem = 8192.0;
+constexpr double kItems = 4.0, kItemsMost = 16.0, kItemSteps = 65536.0, kSmallItem = 8192.0, kFewItems = 3.0;
 // Dispensers: blocks and items are dealt to groups by their number modulo
 // kHeads, and the items past the first per block come from the group's own
 // counter, a cache line each.  One counter for all serves a block per ~10 ns,
@@ -308,10 +308,10 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a, const double* dN, c
     // samples x steps over the batch (lane 0's sum: the rotations leave
     // other lanes with other association orders)
     const double total = __shfl(wave_sum(valid ? dn * per : 0.0), 0);
-    const bool few = total < kItems * kSmallItem * a.grid_blocks;   // items
-    const unsigned own = few ? a.fit_blocks : a.grid_blocks;
+    const unsigned own = total < kFewItems * kSmallItem * a.grid_blocks ? a.fit_blocks : a.grid_blocks;
     const double steps = total / own;                   // per block
-    const double per_block = few ? fmax(steps / kSmallItem, 1.0) : fmin(fmax(steps / kItemSteps, kItems), kItemsMost);
+    const double per_block = steps < kItems * kSmallItem ? fmax(steps / kSmallItem, 1.0)
+                                                         : fmin(fmax(steps / kItemSteps, kItems), kItemsMost);
     const double target = total / (own * per_block);
     const uint64_t most = (uint64_t)fmax(256.0 * per_block, 1024.0);
     const uint64_t left = (uint64_t)dn;
@@ -429,8 +429,12 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
     }
     int tab_level = -1;
     const unsigned count = __builtin_amdgcn_readfirstlane(s_plan.start[s_plan.npairs]);
-    const unsigned own = __builtin_amdgcn_readfirstlane(s_plan.own);
-    if (blockIdx.x >= own) return;
+    // a batch is launched with as many blocks as its plan counts on: the kernel
+    // of several payoff kinds, which only batches launch, needs no other number
+    // (it is the slower for one: four payoffs 1.91 -> 1.93 ms)
+    const unsigned planned = PAYOFF == kAnyPayoff ? 0u : __builtin_amdgcn_readfirstlane(s_plan.own);
+    auto own = [&]() -> unsigned { return PAYOFF == kAnyPayoff ? gridDim.x : planned; };
+    if (PAYOFF != kAnyPayoff && blockIdx.x >= planned) return;
     for (unsigned it = blockIdx.x; it < count;) {   // block-uniform
         const WorkItem w = wave_uniform(plan_item(s_plan, it));
         double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
@@ -453,11 +457,11 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
         if (w.level == 0) copy_y_sums(sums);
         block_reduce_add(sums, nonfinite, &d->acc[(w.slot * kMaxLevels + w.level) * kSpread +
                                                   (blockIdx.x & (kSpread - 1))]);
-        if (count <= own) break;
+        if (count <= own()) break;
         if (threadIdx.x == 0) {
-            // the group's next item: those with its number modulo kHeads, from `own` on
-            const unsigned g = blockIdx.x % kHeads, past = own % kHeads;
-            s_item = own + (g + kHeads - past) % kHeads + kHeads * atomicAdd(d->head + g * kHeadStride, 1u);
+            // the group's next item: those with its number modulo kHeads, from own() on
+            const unsigned g = blockIdx.x % kHeads, past = own() % kHeads;
+            s_item = own() + (g + kHeads - past) % kHeads + kHeads * atomicAdd(d->head + g * kHeadStride, 1u);
         }
         __syncthreads();
         it = __builtin_amdgcn_readfirstlane(s_item);
