@@ -127,8 +127,10 @@ LaunchShape choose_shape(const mlmc_ctx* ctx, const mlmc_model& m, const mlmc_pa
 // (fixed_block != 0), else a tuned one (tuned_block != 0), else 256 threads
 // and 2 samples per lane; one sample per lane when fewer than 256 lanes per
 // compute unit would be busy; one- and two-step levels at most 2 blocks per
-// lane; GBM paths split across lanes when too few fill the device.  The
-// returned shape has no residency cap (num_cu = 0).
+// lane; GBM paths split across lanes when too few fill the device; unless the
+// shape is fixed, smaller blocks for small launches, fewer samples per lane by
+// the fullest compute unit, and the few-chains kernel.  The returned shape has
+// no residency cap (num_cu = 0) but the few-chains kernel's own.
 LaunchShape default_shape(const mlmc_model& m, const mlmc_payoff& p, int l, int M, int precision,
                           uint64_t N, uint64_t n_call, int num_cu, int fixed_block, int fixed_ppt,
                           int tuned_block, int tuned_ppt);

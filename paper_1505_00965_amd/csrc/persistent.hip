@@ -45,6 +45,7 @@ __global__ __launch_bounds__(64) void plan_kernel(const BatchDesc* d, BatchReque
     s.offset[threadIdx.x] = q.offset[threadIdx.x];
     __syncthreads();
     PlanArgs a = plan_args(d);
+    clear_heads(a);
     a.grid_blocks = a.fit_blocks = q.blocks;
     plan_body(a, s.dN, s.offset);
 }
@@ -58,7 +59,9 @@ __global__ __launch_bounds__(64) void plan_counts_kernel(const BatchDesc* d, con
     s.dN[threadIdx.x] = (double)n;
     s.offset[threadIdx.x] = 0.0;
     __syncthreads();
-    plan_body(plan_args(d), s.dN, s.offset);
+    const PlanArgs a = plan_args(d);
+    clear_heads(a);
+    plan_body(a, s.dN, s.offset);
 }
 
 // The adaptive run's first kernel when its spread groups are not known to
@@ -71,6 +74,7 @@ __global__ __launch_bounds__(256) void driver_start_kernel(DriverState* st, Leve
 {
     __shared__ DriverState s;
     const PlanArgs pa = plan_args(d);
+    clear_heads(pa);
     init_state(s, c);   // ends with a barrier
     plan_body(pa, s.dN, s.n);
     constexpr int kWords = sizeof(DriverState) / 8;
@@ -118,6 +122,7 @@ __global__ __launch_bounds__(512) void driver_update_plan_kernel(DriverState* st
     asm volatile("" ::"s"(pa.L), "s"(pa.M), "s"(pa.nslots), "s"(pa.dim), "s"(pa.split_ok), "s"(pa.num_cu),
                  "s"(pa.grid_blocks), "s"(pa.fit_blocks), "s"(pa.chunk), "s"(pa.block), "s"(pa.cond_slots), "s"(pa.plan),
                  "s"(pa.head), "s"(pa.split));
+    clear_heads(pa);
     // the sums of each group, in record order as the per-level form folds them
     y0 = wave_sum(y0);
     q0 = wave_sum(q0);

@@ -48,11 +48,13 @@ def same(a, b):
 
 # plans of no item, of one, of fewer items than resident blocks, between those
 # and the grid, of a few per block, and past the rule's end (32768 path steps a
-# block of the grid: 42e6) on either side
+# block of the grid: 42e6) on either side; items of 65536 steps (from 336e6 on)
+# and sixteen a block (from 1.34e9 on)
 @pytest.mark.parametrize("md", [W.GBM_MODEL, W.HESTON_MODEL])
 @pytest.mark.parametrize("N", [[0, 0, 0, 0], [1, 0, 0, 0], [70000, 5000, 700, 90], [3000000, 400000, 30000, 2000],
                                [9000000, 1300000, 300000, 60000], [20000000, 1900000, 400000, 50000],
-                               [21000000, 2100000, 500000, 60000], [130000000, 2, 0, 1]])
+                               [21000000, 2100000, 500000, 60000], [130000000, 2, 0, 1],
+                               [400000000, 1000, 0, 3], [1500000000, 70000, 999, 0]])
 def test_every_sample_once(gctx, md, N):
     m, M, L = A.model(**md), 4, 3
     for pays in ([P["lookback"]], [P["lookback"], P["call"]]):
