@@ -417,7 +417,7 @@ def persistent_batch(ctx, mlmc, W, reps=3):
     fine = sum(N[0][l] * 4**l for l in range(L + 1)) * len(pays)
 
     def time_batch():
-        ctx.mlmc_levels_batch(gm, pays, 4, L, N, seed=1)          # capture + warm
+        ctx.mlmc_levels_batch(gm, pays, 4, L, N, seed=1)          # warm
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for r in range(reps):

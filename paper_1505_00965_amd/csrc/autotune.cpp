@@ -1,6 +1,6 @@
 // Launch-shape autotuner: picks block size and samples per lane for the
 // level sampler (per model, payoff, precision, M and level class) and block
-// size, samples per lane and resident blocks per compute unit for the
+// size, samples per lane and blocks per compute unit for the
 // persistent kernel, by timing candidates with HIP events on the device
 // itself.  Results are results of measurement, so they are cached in a small
 // JSON file keyed by GPU architecture, compute-unit count and HIP runtime
@@ -273,7 +273,7 @@ mlmc_status mlmc_autotune_persistent(mlmc_ctx* ctx, const mlmc_model* model,
     int bb = 256, bp = 1, bc = 4;
     for (int b : blocks)
         for (int c : bpcs) {
-            if (b * c > 2048) continue;   // resident: at most 2048 threads per compute unit
+            if (b * c > 2048) continue;   // at most 2048 threads per compute unit
             for (int p : ppts) {
                 mlmc_status st = mlmc_set_persistent_launch(ctx, b, p, c);
                 double t[3] = {0, 0, 0};
@@ -343,7 +343,7 @@ mlmc_status mlmc_autotune_run(mlmc_ctx* ctx, const mlmc_model* model, const mlmc
     mlmc_run_result res;
     for (int b : blocks)
         for (int c : bpcs) {
-            if (b * c > 2048) continue;   // resident: at most 2048 threads per compute unit
+            if (b * c > 2048) continue;   // at most 2048 threads per compute unit
             for (int p : ppts) {
                 st = mlmc_set_persistent_launch(ctx, b, p, c);
                 double t[3] = {0, 0, 0};
