@@ -32,9 +32,11 @@
 // samples at least: every chunk takes the deepest level's chain twice, 0.5 ms
 // (Heston 0.9) at 4096 steps however few its samples, and kMaxPoints alone
 // holds 2432 of them there.  Adam step on levels 0..6, M = 4, ms, by
-// kMaxPoints alone, with at least 16384, 32768 and 65536 samples:
-//   16384 samples, GBM   20.9  11.3  11.3  11.3     131072, GBM  175  98  91  88
-//   16384, Heston        27.1  12.4  12.4  12.4     131072, Heston 223 111 100 95
+// kMaxPoints alone and with at least 32768 samples:
+//   16384 samples, GBM 20.9  11.6, Heston 27.1  12.9
+//   131072 samples     175   93,          223   102
+// (131072 with at least 16384, 32768 and 65536, the backward pass in one launch
+// a chunk: 98, 91 and 88, Heston 111, 100 and 95.)
 // 32768 there need 2.7 GB (Heston 3.6) of scratch, kept by the network.
 #include <hip/hip_runtime.h>
 
@@ -77,6 +79,7 @@ struct TrainArgs {
     int nlev, M;
     uint32_t n, stride, nrows;
     uint32_t first;         // position of the chunk in the batch
+    uint32_t task0, tasks;  // a backward launch's part of the chunk's (row, 64 samples) tasks
     uint64_t B, Bpad;       // batch size, row length of y
     uint64_t seed, offset;
     float S0, v0;
@@ -442,8 +445,12 @@ __device__ __forceinline__ void start_point_row(const TrainArgs& a, const CvKern
 }
 
 // Blocks 0 .. ns - 1: the start point's rows of gpart and (block 0, first
-// chunk) the loss.  Block ns + b: points of share b of the (row, 64 samples)
-// tasks.  A block's row is added to after the batch's first chunk.
+// chunk) the loss.  Block ns + b: points of share b of the launch's tasks.  A
+// block's row is added to after the batch's first launch: a chunk of more than
+// kMaxPoints takes several, so that no lane sums more points in fp32 than one
+// of that size gives it.  Gradients on levels 0..6 of 16384 and 32000 samples in
+// one launch lay 0.8e-6 to 4e-6 from those of chunks of kMaxPoints and of
+// launches per level, which lie 3.5e-7 to 4.5e-7 apart; so as far as those.
 template <int D>
 __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvKernelArgs c,
                                                                 const bf16x8* abwd, float* gpart, uint32_t ns,
@@ -457,6 +464,7 @@ __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvK
     __syncthreads();
     float* grow = gpart + (uint64_t)blockIdx.x * kGradRow;
     if (blockIdx.x < ns) {
+        if (a.task0) return;                    // in the chunk's first launch
         start_point_row<D>(a, c, sh, st, blockIdx.x, ns, grow);
         if (blockIdx.x == 0 && threadIdx.x == 0 && a.first == 0) {
             double t = 0.0;
@@ -490,9 +498,9 @@ __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvK
     // read by row) and its corner of a transposed read
     const int own = col * kRowPad;
     const int tr = (8 * h + ((lane & 15) >> 2)) * kRowPad + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    const uint32_t cw = a.stride / 64, total = a.nrows * cw;
-    const uint32_t t0 = (uint32_t)((uint64_t)total * b / nb);
-    const uint32_t t1 = (uint32_t)((uint64_t)total * (b + 1) / nb);
+    const uint32_t cw = a.stride / 64;
+    const uint32_t t0 = a.task0 + (uint32_t)((uint64_t)a.tasks * b / nb);
+    const uint32_t t1 = a.task0 + (uint32_t)((uint64_t)a.tasks * (b + 1) / nb);
     // a task's points: network inputs, coefficient, Y; with two inputs the
     // next task's loads are in flight while this one's points are worked off
     // (with three the registers for it would spill)
@@ -522,7 +530,7 @@ __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvK
         return p;
     };
     int buf = 0;
-    Points next = load(t0 < t1 ? t0 : 0);       // nb <= total: every block has a task, but in a short last chunk
+    Points next = load(t0 < t1 ? t0 : 0);       // every block has a task, but in a short last chunk
     for (uint32_t t = t0; t < t1; ++t) {
         // the network's constants are read from LDS at every point (see phi_eval_x)
         __asm__ volatile("" ::: "memory");
@@ -623,7 +631,7 @@ __global__ __launch_bounds__(128, 2) void train_backward_kernel(TrainArgs a, CvK
         }
     }
     // the block's row: a unit's sums over the 32 lanes of its half
-    const bool add = a.first != 0;              // a later chunk of the batch
+    const bool add = a.first != 0 || a.task0 != 0;
     auto put = [&](int i, float v) { grow[i] = add ? grow[i] + v : v; };
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -765,6 +773,7 @@ struct TrainPlan {
     TrainScratch s;
     uint64_t chunk;      // samples worked off at once
     uint32_t group;      // steps whose paths one launch makes (1 with chunks)
+    uint32_t parts;      // backward launches of a chunk
     int nb, ns;          // backward blocks: points, start point
     NetConsts nc;
     TrainPathsFn paths;
@@ -788,8 +797,13 @@ static void size_chunk(TrainPlan& t, int num_cu, uint64_t most, int nsteps)
     const uint64_t resident = (uint64_t)num_cu * kBwdBlocksPerCu, tasks = nrows * (t.chunk / 64);
     const uint64_t pairs = t.chunk * a.nlev;
     const double sc = kStartPairCost * (double)pairs, share = sc / (sc + kTaskCost * (double)tasks);
+    // (times the chunk's backward launches: the start point is worked off beside
+    // the first of them, and a block of it sums as many samples as in one of
+    // kMaxPoints)
+    t.parts = (uint32_t)std::max<uint64_t>(1, (nrows * t.chunk + kMaxPoints - 1) / kMaxPoints);
     t.ns = (int)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)(share * (double)resident + 0.5),
                                                           (pairs + 127) / 128, resident / 2}));
+    t.ns = (int)std::min<uint64_t>({(uint64_t)t.ns * t.parts, (pairs + 127) / 128, resident / 2});
     t.nb = (int)std::min<uint64_t>(tasks, resident - t.ns);
 }
 
@@ -904,10 +918,16 @@ static mlmc_status enqueue_loss_grad(mlmc_cv* cv, TrainPlan& t, uint64_t step, u
             hipLaunchKernelGGL(t.paths, dim3(blocks), dim3(256), 0, q, t.a, t.nc, 0);
             MLMC_HIP(ctx, hipGetLastError());
         }
-        const TrainArgs a = for_step(t.a, k);
-        hipLaunchKernelGGL(d3 ? train_backward_kernel<3> : train_backward_kernel<2>, dim3(t.nb + t.ns), dim3(128), 0,
-                           q, a, c, (const bf16x8*)cv->d_abwd, t.s.gpart, (uint32_t)t.ns, cv->d_loss, hist);
-        MLMC_HIP(ctx, hipGetLastError());
+        TrainArgs a = for_step(t.a, k);
+        const uint32_t total = a.nrows * (a.stride / 64);
+        for (uint32_t part = 0; part < t.parts; ++part) {
+            a.task0 = (uint32_t)((uint64_t)total * part / t.parts);
+            a.tasks = (uint32_t)((uint64_t)total * (part + 1) / t.parts) - a.task0;
+            if (part && !a.tasks) continue;
+            hipLaunchKernelGGL(d3 ? train_backward_kernel<3> : train_backward_kernel<2>, dim3(t.nb + t.ns), dim3(128),
+                               0, q, a, c, (const bf16x8*)cv->d_abwd, t.s.gpart, (uint32_t)t.ns, cv->d_loss, hist);
+            MLMC_HIP(ctx, hipGetLastError());
+        }
     }
     hipLaunchKernelGGL(train_update_kernel, dim3((cv->np + 31) / 32), dim3(1024), 0, q, (const float*)t.s.gpart,
                        t.nb + t.ns, cv->D, t.s.grad, adam ? *adam : AdamArgs{}, adam ? 1 : 0);
