@@ -23,8 +23,8 @@ constexpr int kPairs = kMaxSlots * kMaxLevels;
 // with four and 44 with one, a batch of 3e6 steps 67 and 63.
 //
 // The grid is five blocks a compute unit, of which four fit at once where a
-// block takes more than 96 registers a lane (M = 2, batches of several payoff
-// kinds, Heston lookback) or 32 KB of LDS (the tabulated control variate); the
+// block takes more than 96 registers a lane (GBM with M = 2, lookback, batches
+// of several payoff kinds) or 32 KB of LDS (the tabulated control variate); the
 // others start as blocks end.  In a plan of fewer than kFewItems items a block the
 // item of such a block would be a second round of the launch: the items are cut
 // for the blocks that fit, and the others leave (a batch, whose size the host
@@ -418,6 +418,17 @@ __device__ __forceinline__ WorkItem plan_item(const PlanTable& t, unsigned it)
     return w;
 }
 
+// The samplers that read from the plan how many blocks work: those of which
+// fewer than five may fit at once (see kItems).  Where five fit, the plan counts
+// on the whole grid; and the kernel of several payoff kinds runs batches alone,
+// which are launched with the plan's number.  Reading it there anyway costs
+// time through the code around it (four payoffs 1.91 -> 1.93 ms; 1000 Heston
+// paths of level 6, M = 4, digital, 398 -> 420 us).  Five fit of some kernels
+// with M = 2, too, but there it costs nothing (Heston, as before, 419 -> 424 us,
+// conditional digital 447 -> 425).  Either form does the whole plan with any grid.
+template <int MODEL, int M, int PAYOFF, bool CV>
+constexpr bool kPlansBlocks = PAYOFF != kAnyPayoff && (M == 2 || CV || PAYOFF == kLookback);
+
 // Block b < own takes item b first (the rest take none); later items come from
 // its group's dispenser until that has none left, so a launch with no more items
 // than such blocks (an empty one included) makes no atomics on it.  Each item
@@ -436,12 +447,10 @@ __device__ __forceinline__ void sample_items(const BatchDesc* d, float* s_tab, u
     }
     int tab_level = -1;
     const unsigned count = __builtin_amdgcn_readfirstlane(s_plan.start[s_plan.npairs]);
-    // a batch is launched with as many blocks as its plan counts on: the kernel
-    // of several payoff kinds, which only batches launch, needs no other number
-    // (it is the slower for one: four payoffs 1.91 -> 1.93 ms)
-    const unsigned planned = PAYOFF == kAnyPayoff ? 0u : __builtin_amdgcn_readfirstlane(s_plan.own);
-    auto own = [&]() -> unsigned { return PAYOFF == kAnyPayoff ? gridDim.x : planned; };
-    if (PAYOFF != kAnyPayoff && blockIdx.x >= planned) return;
+    unsigned planned = 0;
+    if constexpr (kPlansBlocks<MODEL, M, PAYOFF, CV>) planned = __builtin_amdgcn_readfirstlane(s_plan.own);
+    auto own = [&]() -> unsigned { return kPlansBlocks<MODEL, M, PAYOFF, CV> ? planned : gridDim.x; };
+    if (kPlansBlocks<MODEL, M, PAYOFF, CV> && blockIdx.x >= planned) return;
     for (unsigned it = blockIdx.x; it < count;) {   // block-uniform
         const WorkItem w = wave_uniform(plan_item(s_plan, it));
         double sums[kNumSums] = {0, 0, 0, 0, 0, 0};
